@@ -65,6 +65,20 @@ enum {
  * plan creation.  Those corrections run as extra matrix-core tiles on the
  * same operand windows; H and H^T use the same columns, so they stay exact
  * transposes of each other. */
+/* Where it is the faster one (a rule on the sizes at plan creation), a plan
+ * applies H and H^T in the spectral form: transforms along y and x and one
+ * product per lateral frequency, all in float32.  Operands and table are
+ * rounded to the precision's format exactly as above and then carried in
+ * float32 (the _SPLIT forms carry them whole), so a precision keeps its
+ * meaning and its results up to FP32 summation.  Results stay inside the
+ * footprint: an output is zero where every operand value within its footprint
+ * is, and non-finite operand values make the outputs of their footprint
+ * non-finite.  The spectra and the table per frequency take device memory (33
+ * GB at 320 x 320 x 128 with 40 pulses and 512 samples, 2.4 GB at 128 x 128 x
+ * 64 with 32 and 256); a plan for which they exceed a third of the free
+ * memory, or cannot be allocated, keeps the direct form.  The environment
+ * variable PSOAM_SPECTRAL=0 or 1 at plan creation forces the direct or (where
+ * it can run: at most 256 depths) the spectral form. */
 typedef enum {
   PSOAM_FP32 = 0,
   PSOAM_BF16 = 1,
@@ -373,7 +387,8 @@ int psoam_solve_batch(int32_t n, const psoam_plan* const* plans, const float* co
  * useful_macs = nonzero band entries h[z][jdy][jdx][t] with t in [0, Nt)
  * (the algorithmic multiply-adds of one A-scan of one pulse);
  * chunks = packed matrix-core tiles of the kernel the plan launches (the
- * run-packed tiles when the LDS-staged kernel is used); executed_macs =
+ * run-packed tiles when the LDS-staged kernel is used; spectral plans report
+ * the figures of their direct form); executed_macs =
  * chunks times the tile size (16 x 32 for 16-bit, 16 x 4 for FP32).
  * dir 0: H, dir 1: H^T. */
 typedef struct {
@@ -389,7 +404,8 @@ int psoam_plan_stats(const psoam_plan* plan, psoam_plan_info* info);
 
 /* Launch only the band-contraction kernel of H (dir 0: writes y) or of
  * S^T H^T (dir 1: writes c) on the padded operand the plan holds from its
- * last apply, on `stream`.  Used to time that kernel alone; its output
+ * last apply, on `stream` (spectral plans: everything after the operand's
+ * transform, along both axes for H and along x for H^T).  Used to time that kernel alone; its output
  * equals the matching apply's only after that apply ran on the same input. */
 int psoam_band_only(const psoam_plan* plan, int32_t dir, float* out, void* stream);
 
@@ -414,8 +430,11 @@ typedef struct {
  * for H, with or without four loader waves at 8 rows; 4, 8 or 12 rows and
  * operand shift 0 or 4 for H^T; 12 rows for one-part operands only), for an
  * FP32 plan the one with the per-tile instead
- * of the run-packed kernel, times each band kernel's solver form on `stream`
- * (HIP events, one warm-up and three timed launches on the zeroed operands),
+ * of the run-packed kernel, and for either the plan in the other form
+ * (spectral or direct; a spectral plan has no launch shapes of its own, and
+ * the report's rows are those its direct form would have), times each band
+ * kernel's solver form on `stream` (HIP events, one warm-up and three timed
+ * launches on the operands as allocated),
  * times the TV dual step on the plan's grid with each tile shape of the
  * kernel's list (8x8x32 with 512 threads, 4x8x32/256, 4x16x32/512,
  * 4x8x64/512, 8x8x32/1024; one warm-up and ten steps), and returns the plan

@@ -858,14 +858,15 @@ namespace {
 // shift, H's loader waves, and the tile of the TV dual step.  Measured per
 // process and cached in memory and on disk by device, geometry, precision
 // and a hash of the impulse-response table.
-constexpr int kTuneVersion = 4;  // bump when the kernels or the choices change meaning
+constexpr int kTuneVersion = 5;  // bump when the kernels or the choices change meaning
 
 struct Shape {
   int h_rows = 0, ht_rows = 0, tsh = 0, h_loadw = 0, tv = 0;
   int runs_h = 0, runs_ht = 0;  // FP32: run-packed (1) or per-tile (0) kernel
+  int spec = 0;                 // spectral (1) or direct (0) form
   bool operator==(const Shape& o) const {
     return h_rows == o.h_rows && ht_rows == o.ht_rows && tsh == o.tsh && h_loadw == o.h_loadw &&
-           tv == o.tv && runs_h == o.runs_h && runs_ht == o.runs_ht;
+           tv == o.tv && runs_h == o.runs_h && runs_ht == o.runs_ht && spec == o.spec;
   }
 };
 
@@ -908,7 +909,7 @@ std::string tune_file() {
   return std::string(home) + "/.cache/psoam/tune.txt";
 }
 
-// the last line "key<TAB>h_rows ht_rows tsh h_loadw tv runs_h runs_ht" of the file for key
+// the last line "key<TAB>h_rows ht_rows tsh h_loadw tv runs_h runs_ht spec" of the file for key
 bool disk_lookup(const std::string& key, Shape& out) {
   const std::string path = tune_file();
   if (path.empty()) return false;
@@ -921,8 +922,8 @@ bool disk_lookup(const std::string& key, Shape& out) {
     if (!tab || (size_t)(tab - line) != key.size() || key.compare(0, key.size(), line, key.size()))
       continue;
     Shape s;
-    if (std::sscanf(tab + 1, "%d %d %d %d %d %d %d", &s.h_rows, &s.ht_rows, &s.tsh, &s.h_loadw,
-                    &s.tv, &s.runs_h, &s.runs_ht) == 7 &&
+    if (std::sscanf(tab + 1, "%d %d %d %d %d %d %d %d", &s.h_rows, &s.ht_rows, &s.tsh, &s.h_loadw,
+                    &s.tv, &s.runs_h, &s.runs_ht, &s.spec) == 8 &&
         s.tv >= 0 && s.tv < tv_tile_count()) {
       out = s;
       found = true;
@@ -940,8 +941,8 @@ void disk_store(const std::string& key, const Shape& s) {
     if (path[i] == '/') (void)::mkdir(path.substr(0, i).c_str(), 0755);
   std::FILE* f = std::fopen(path.c_str(), "a");
   if (!f) return;
-  std::fprintf(f, "%s\t%d %d %d %d %d %d %d\n", key.c_str(), s.h_rows, s.ht_rows, s.tsh,
-               s.h_loadw, s.tv, s.runs_h, s.runs_ht);
+  std::fprintf(f, "%s\t%d %d %d %d %d %d %d %d\n", key.c_str(), s.h_rows, s.ht_rows, s.tsh,
+               s.h_loadw, s.tv, s.runs_h, s.runs_ht, s.spec);
   std::fclose(f);
 }
 
@@ -954,6 +955,7 @@ Shape shape_of(const psoam_plan* P) {
   s.tv = P->tv_tile;
   s.runs_h = P->fwd.runs32 ? 1 : 0;
   s.runs_ht = P->adj.runs32 ? 1 : 0;
+  s.spec = P->spec ? 1 : 0;
   return s;
 }
 
@@ -979,11 +981,16 @@ int time_launches(F&& launch, int reps, hipStream_t s, double* ms) {
 
 // average ms of the band kernel of direction dir in the solver's form
 // (dir 0: H with the residual epilogue, dir 1: S^T H^T), one warm-up launch
-int time_band(psoam_plan* P, int dir, hipStream_t s, double* ms) {
+// (with_switch: dir 0 with the pass that makes its operand)
+int time_band(psoam_plan* P, int dir, hipStream_t s, double* ms, bool with_switch = false) {
   SolveBufs B;
   if (int rc = ensure_solve_ws(P, B)) return rc;
   return time_launches(
       [&](int) {
+        if (with_switch && dir == 0) {
+          const hipError_t e = launch_switch_fwd(P, B.zb, s);
+          if (e != hipSuccess) return e;
+        }
         return dir == 0 ? launch_band(P, 1, nullptr, nullptr, P->d_partial, s)
                         : launch_band(P, 2, B.g, nullptr, nullptr, s);
       },
@@ -1013,7 +1020,7 @@ int build_shaped(const psoam_geom* g, const psoam_species* sp, const float* phi,
                  hipStream_t s, const Shape& want, psoam_plan** out) {
   const bool fp32 = prec == PSOAM_FP32;
   set_tune_choice(want.h_rows, want.ht_rows, want.tsh, want.h_rows ? want.h_loadw : -1,
-                  fp32 ? want.runs_h : -1, fp32 ? want.runs_ht : -1);
+                  fp32 ? want.runs_h : -1, fp32 ? want.runs_ht : -1, want.spec);
   const int rc = create_plan(g, sp, phi, t0, taps, sir_w, prec, s, out);
   clear_tune_choice();
   if (rc == PSOAM_OK) (*out)->tv_tile = want.tv;
@@ -1102,17 +1109,31 @@ int create_tuned(const psoam_geom* g, const psoam_species* sp, const float* phi,
   // alternatives: the other row counts and loader-wave settings for H; the
   // other row counts and shifts for H^T (each timed on the direction it changes)
   std::vector<std::pair<Shape, int>> alts;
-  if (base.h_rows)
+  // the other form of the band operator, with its own rules' shapes (compared
+  // with S's pass: the spectral form transforms its operand there)
+  double h_full = 0.0;
+  if (base.h_rows || fp32) {
+    rc = time_band(P, 0, s, &h_full, true);
+    if (rc != PSOAM_OK) {
+      free_plan(P);
+      return rc;
+    }
+    Shape o = base;
+    o.spec = base.spec ? 0 : 1;
+    // FP32 keeps the form that errs less (see the plan's rule)
+    if (!(o.spec && fp32 && g->f < kSpecMinFp32F)) alts.push_back({o, 3});
+  }
+  if (base.h_rows && !base.spec)
     for (int rows : {4, 8, 12})
       for (int lw : {0, 1})
         if ((rows != base.h_rows || lw != base.h_loadw) && !(rows != 8 && lw == 1))
           alts.push_back({Shape{rows, base.ht_rows, base.tsh, lw, base.tv}, 0});
-  if (base.ht_rows)
+  if (base.ht_rows && !base.spec)
     for (int rows : {4, 8, 12})
       for (int tsh : {0, 4})
         if (rows != base.ht_rows || tsh != base.tsh)
           alts.push_back({Shape{base.h_rows, rows, tsh, base.h_loadw, base.tv}, 1});
-  if (fp32 && (base.runs_h || base.runs_ht)) {
+  if (fp32 && !base.spec && (base.runs_h || base.runs_ht)) {
     // the other FP32 kernel, for both directions at once (timed on each)
     Shape o = base;
     o.runs_h = base.runs_h ? 0 : 1;
@@ -1123,15 +1144,29 @@ int create_tuned(const psoam_geom* g, const psoam_species* sp, const float* phi,
     psoam_plan* Q = nullptr;
     if ((rc = build_shaped(g, sp, phi, t0, taps, sir_w, prec, s, a.first, &Q))) break;
     const Shape got = shape_of(Q);
-    double ms = 0.0, ms2 = 0.0;
+    double ms = 0.0, ms2 = 0.0, full = 0.0;
     if (got == a.first) {  // it fitted
-      rc = time_band(Q, a.second == 2 ? 0 : a.second, s, &ms);
-      if (rc == PSOAM_OK && a.second == 2) rc = time_band(Q, 1, s, &ms2);
+      rc = time_band(Q, a.second >= 2 ? 0 : a.second, s, &ms);
+      if (rc == PSOAM_OK && a.second >= 2) rc = time_band(Q, 1, s, &ms2);
+      if (rc == PSOAM_OK && a.second == 3) rc = time_band(Q, 0, s, &full, true);
       ++r.candidates;
     }
     free_plan(Q);
     if (rc != PSOAM_OK) break;
     if (!(got == a.first)) continue;
+    if (a.second == 3) {
+      // it comes first: h_best and ht_best are still the base's
+      // (a tenth at least: 16-bit operands are rounded from sums that differ
+      // in their last bits between the forms)
+      if (ms <= h_best && ms2 <= ht_best && full + ms2 < 0.9 * (h_full + ht_best)) {
+        h_best = ms;
+        ht_best = ms2;
+        best.spec = a.first.spec;
+        // the spectral form has no launch shapes of its own to try
+        if (best.spec) break;
+      }
+      continue;
+    }
     if (a.second == 2) {
       if (ms < h_best) {
         h_best = ms;
@@ -1168,7 +1203,8 @@ int create_tuned(const psoam_geom* g, const psoam_species* sp, const float* phi,
     disk_store(key, best);
   }
   if (best.h_rows == base.h_rows && best.ht_rows == base.ht_rows && best.tsh == base.tsh &&
-      best.h_loadw == base.h_loadw && best.runs_h == base.runs_h && best.runs_ht == base.runs_ht) {
+      best.h_loadw == base.h_loadw && best.runs_h == base.runs_h && best.runs_ht == base.runs_ht &&
+      best.spec == base.spec) {
     P->tv_tile = best.tv;
     return done(P);
   }

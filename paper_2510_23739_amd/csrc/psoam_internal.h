@@ -100,6 +100,39 @@ inline size_t lds_meta_bytes(int F, int rows, int max_runs) {
   return sizeof(uint32_t) * ((size_t)(F + rows - 1) + (F + 1) + 6 * (size_t)max_runs) + 16;
 }
 
+// Spectral form of the band operator (psoam_spectral.hip): transform lengths
+// and radices per axis, the padded lengths of depth and time, the table per
+// frequency for both directions, the spectra, and the marks of nonzero and
+// non-finite operand values.
+struct SpecPlan {
+  int nx = 0, ny = 0;
+  int nsx = 0, nsy = 0;
+  int radx[4] = {}, rady[4] = {};
+  int lz = 0, lt = 0;     // Nz, Nt rounded up to 16
+  int np = 0;             // pairs of pulses
+  size_t nf = 0;          // frequencies of the half plane
+  int nblk = 0;           // 16 x 16 blocks of (t, z) per frequency
+  void* d_x = nullptr;    // [np][ny][nx][lz] complex: spectrum of S c
+  void* d_y = nullptr;    // [np][ny][nx][lt] complex: spectrum of y or r
+  void* d_r = nullptr;    // [np][Ny][nx][lt] complex: r transformed along x (H^T's operand)
+  void* d_g = nullptr;    // spectrum of H^T r (pairs of species after S^T, else of pulses)
+  float* d_tf = nullptr;  // [nf][nblk][2][64][4]: table of H (real, imaginary)
+  float* d_ta = nullptr;  // the same blocks in H^T's lane order
+  unsigned* d_mask = nullptr;  // [lt / 16] 16-depth blocks of each t tile
+  void* d_twx = nullptr;
+  void* d_twy = nullptr;
+  // marks of H's operand and H^T's: positions with a nonzero value, with a
+  // non-finite one, and what either reaches (one allocation)
+  void* d_marks = nullptr;
+  unsigned* d_at_b = nullptr;
+  unsigned* d_bad_b = nullptr;
+  unsigned char* d_near_b = nullptr;
+  unsigned* d_at_r = nullptr;
+  unsigned* d_bad_r = nullptr;
+  unsigned char* d_near_r = nullptr;
+  unsigned call_b = 0, call_r = 0;
+};
+
 struct Workspace {
   size_t bytes = 0;
   void* base = nullptr;
@@ -130,6 +163,9 @@ struct psoam_plan {
   void* d_rq_lo = nullptr;
   size_t bq_bytes = 0, rq_bytes = 0;
   psoam::BandTable fwd, adj;
+  // set: H and H^T run in the spectral form, and fwd / adj hold only the
+  // direct form's figures
+  psoam::SpecPlan* spec = nullptr;
   // solver scratch (allocated on first use, grown as needed)
   psoam::Workspace solve_ws;
   double* d_partial = nullptr;  // per-wave / per-block FP64 partial sums
@@ -184,7 +220,7 @@ namespace psoam {
 // of H and of H^T, 0 (per-tile) or 1 (run-packed); any other value leaves
 // that choice to the plan's own rules.  A choice that does not fit is ignored.
 void set_tune_choice(int rows_fwd, int rows_adj, int tsh, int loadw_fwd, int runs_fwd = -1,
-                     int runs_adj = -1);
+                     int runs_adj = -1, int spectral = -1);
 void clear_tune_choice();
 
 // Device stop gate of the calling thread: while a solve with device-side
@@ -214,6 +250,22 @@ hipError_t launch_band(const psoam_plan* P, int mode, float* out, const float* p
                        double* partial, hipStream_t s, float* yc = nullptr, double yc_beta = 0.0,
                        int yc_first = 0);
 size_t band_partials(const psoam_plan* P, int mode);
+
+// Spectral form (psoam_spectral.hip).  spec_build sets P->spec when the form
+// is predicted faster than the direct one (direct_us: one A and one A^T;
+// force: whenever the plan can run in it) and there is memory for it; taps_f
+// and taps_a are the band values of H and H^T as the plan's precision rounds
+// them; fact: the plan's temporal convolution runs in passes of its own.
+bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const float* taps_a,
+                bool force, double direct_us, bool fact, hipStream_t s);
+// smallest footprint at which an FP32 plan takes the spectral form
+constexpr int kSpecMinFp32F = 7;
+void spec_free(psoam_plan* P);
+size_t spec_partials(const psoam_plan* P);
+hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s);
+hipError_t spec_pack(const psoam_plan* P, const float* y, hipStream_t s);
+hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pmeas,
+                     double* partial, hipStream_t s, float* yc, double yc_beta, int yc_first);
 
 hipError_t launch_prox_l1(float* x, const float* z, int64_t n, float thresh, int nonneg,
                           hipStream_t s);

@@ -1310,15 +1310,21 @@ static inline unsigned blocks_for(size_t n, unsigned bs = 256) {
   return (unsigned)((n + bs - 1) / bs);
 }
 
+// operands rounded to FP16 (the spectral form carries split operands whole)
+static bool f16_operands(const psoam_plan* P) {
+  return P->d_f16 && !(P->spec && P->prec == PSOAM_FP16_SPLIT);
+}
+
 hipError_t launch_switch_fwd(const psoam_plan* P, const float* c, hipStream_t s) {
   const auto& g = P->g;
   const float* stab = P->d_stab;
-  if (P->d_f16) {
+  if (f16_operands(P)) {
     // |b_k| <= sum_s |S_v[k][s]| |c_s| <= srow max |c|
     hipError_t e = f16_amax(P, c, (int64_t)P->c_elems(), 0, s);
     if (e == hipSuccess) e = f16_scale(P, 0, P->srow, 0.0, s);
     if (e != hipSuccess) return e;
   }
+  if (P->spec) return spec_switch(P, c, s);
   const int vec = P->d_stab_o && (g.nz % 8) == 0 && ((uintptr_t)c & 15) == 0;
   switch (P->prec) {
     case PSOAM_FP32: {
@@ -1352,11 +1358,12 @@ hipError_t launch_switch_fwd(const psoam_plan* P, const float* c, hipStream_t s)
 
 hipError_t launch_pack_r(const psoam_plan* P, const float* y, hipStream_t s) {
   const auto& g = P->g;
-  if (P->d_f16) {
+  if (f16_operands(P)) {
     hipError_t e = f16_amax(P, y, (int64_t)P->y_elems(), 1, s);
     if (e == hipSuccess) e = f16_scale(P, 1, 1.0, 0.0, s);
     if (e != hipSuccess) return e;
   }
+  if (P->spec) return spec_pack(P, y, s);
   // 16-byte loads of the A-scans when every octet starts 16-byte aligned
   const int vec4 = ((uintptr_t)y & 15) == 0 && (g.nt & 3) == 0;
   switch (P->prec) {
@@ -1415,6 +1422,7 @@ static size_t band_blocks(const psoam_plan* P, int mode) {
 }
 
 size_t band_partials(const psoam_plan* P, int mode) {
+  if (P->spec) return spec_partials(P);
   const BandTable& T = (mode == 2) ? P->adj : P->fwd;
   return band_blocks(P, mode) * (use_lds(P, mode) ? T.rows : kWavesPerBlock);
 }
@@ -1552,6 +1560,13 @@ hipError_t launch_band(const psoam_plan* P, int mode, float* out, const float* p
   // the residual form with the A c recurrence is a kernel form of its own
   // (mode 3), so the plain residual form carries none of its registers
   if (mode == 1 && yc) mode = 3;
+  if (P->spec) {
+    if ((mode == 1 || mode == 3) && f16_operands(P)) {
+      const hipError_t e = f16_scale(P, 3, P->hrow * P->srow, 1.0, s);
+      if (e != hipSuccess) return e;
+    }
+    return spec_band(P, mode, out, pmeas, partial, s, mode == 3 ? yc : nullptr, yc_beta, yc_first);
+  }
   const BandTable& T = (mode == 2) ? P->adj : P->fwd;
   const bool split = P->prec == PSOAM_BF16_SPLIT || P->prec == PSOAM_FP16_SPLIT;
   const bool fp16 = P->prec == PSOAM_FP16 || P->prec == PSOAM_FP16_SPLIT;
@@ -2791,7 +2806,8 @@ static size_t eir_pack_lds(const psoam_plan* P, bool resid) {
 }
 
 bool eir_pack_fits(const psoam_plan* P, bool resid) {
-  if (!P->fact || P->prec == PSOAM_FP32) return false;
+  // the spectral form's operand is written by its own pass
+  if (!P->fact || P->prec == PSOAM_FP32 || P->spec) return false;
   // PSOAM_EIR_PACK=0 keeps the two-pass form (row pass, then pack_r16)
   if (const char* ev = std::getenv("PSOAM_EIR_PACK"))
     if (ev[0] == '0') return false;

@@ -27,6 +27,7 @@ struct TuneChoice {
   int tsh = -1;
   int loadw = -1;  // H's loader waves: 0 off, 1 on where they can run, else the rules
   int runs[2] = {-1, -1};  // FP32: 0 per-tile kernel, 1 run kernel, else the rules
+  int spectral = -1;       // 0 direct form, 1 spectral form, else the rules
 };
 thread_local TuneChoice g_tune;
 
@@ -70,13 +71,14 @@ struct Group {
 void set_error(const std::string& msg) { g_last_error = msg; }
 
 void set_tune_choice(int rows_fwd, int rows_adj, int tsh, int loadw_fwd, int runs_fwd,
-                     int runs_adj) {
+                     int runs_adj, int spectral) {
   g_tune.rows[0] = rows_fwd;
   g_tune.rows[1] = rows_adj;
   g_tune.tsh = tsh;
   g_tune.loadw = loadw_fwd;
   g_tune.runs[0] = runs_fwd;
   g_tune.runs[1] = runs_adj;
+  g_tune.spectral = spectral;
 }
 
 void clear_tune_choice() { g_tune = TuneChoice(); }
@@ -102,8 +104,10 @@ const char* last_error_cstr() { return g_last_error.c_str(); }
 // refine: per column (z, jdy, jdx), 1 where the refined BF16 form adds the
 // low-order part of the column's band values as a second layer of groups
 // (null for every other precision).
+// counts: the figures only, no device tables (a plan that runs in the spectral
+// form, or is about to choose its form).
 static int build_table(psoam_plan* P, int dir, const int32_t* t0, const float* taps,
-                       const uint8_t* refine, BandTable& T) {
+                       const uint8_t* refine, BandTable& T, bool counts) {
   const auto& g = P->g;
   const int F = P->F, W = P->W;
   const bool half = P->prec != PSOAM_FP32;
@@ -242,7 +246,7 @@ static int build_table(psoam_plan* P, int dir, const int32_t* t0, const float* t
   }
   const int n_chunks = T.h_start[n_mt];
   T.n_chunks = n_chunks;
-  {
+  if (!counts) {
     std::vector<int> off((size_t)n_chunks * 4, 0);
     std::vector<float> vals((size_t)n_chunks * 64 * gw, 0.0f);
     for (int tile = 0; tile < n_mt; ++tile)
@@ -402,7 +406,7 @@ static int build_table(psoam_plan* P, int dir, const int32_t* t0, const float* t
   if (!half) {
     if (n_l >= 0xffff || F >= 0xffff) return PSOAM_OK;
     T.runs32 = true;
-    return upload_runs();
+    return counts ? PSOAM_OK : upload_runs();
   }
   // staged row windows for a workgroup of `rows` output rows (waves): the
   // union of the octet ranges of the dy values j - r, r < rows
@@ -506,7 +510,7 @@ static int build_table(psoam_plan* P, int dir, const int32_t* t0, const float* t
   T.lds_ok = n_l < 0xffff && F < 0xffff &&
              (rows == 12 ? lds12 : rows == 8 ? lds8 : lds4) <= (size_t)kLdsMaxBytes &&
              !(force_global && force_global[0] == '1');
-  if (!T.lds_ok) return PSOAM_OK;
+  if (!T.lds_ok || counts) return PSOAM_OK;
   PSOAM_HIP(hipMalloc(&T.d_win, sizeof(uint32_t) * win.size()));
   PSOAM_HIP(hipMemcpy(T.d_win, win.data(), sizeof(uint32_t) * win.size(), hipMemcpyHostToDevice));
   return upload_runs();
@@ -600,6 +604,7 @@ void free_plan(psoam_plan* P) {
     if (b) (void)hipFree(b);
   free_table(P->fwd);
   free_table(P->adj);
+  spec_free(P);
   void* bufs[] = {P->d_phi, P->d_stab, P->d_stab_t, P->d_stab_o, P->d_bq, P->d_bq_lo, P->d_rq, P->d_rq_lo,
                   P->solve_ws.base, P->r3_ws.base, P->yc_ws.base, P->d_partial, P->d_scalars, P->d_f16,
                   P->d_f16acc, P->d_ctl, P->d_trace};
@@ -648,9 +653,85 @@ static int adj_window_octets(const psoam_geom& g, const int32_t* t0, const float
   return best;
 }
 
+// 1 spectral, 0 direct, -1 the sizes decide.  PSOAM_SPECTRAL=1 or 0 forces one
+// (tests and timing compare both); the autotuner's choice comes next; any
+// switch of the direct form's kernels means that form.
+static int spectral_choice() {
+  if (const char* e = std::getenv("PSOAM_SPECTRAL")) {
+    if (e[0] == '0') return 0;
+    if (e[0] == '1') return 1;
+  }
+  if (g_tune.spectral >= 0) return g_tune.spectral;
+  for (const char* n : {"PSOAM_BAND_GLOBAL", "PSOAM_LDS_ROWS", "PSOAM_LDS_LOADW", "PSOAM_HALF_BLOCK",
+                        "PSOAM_ADJ_SHIFT", "PSOAM_FP32_RUNS", "PSOAM_EIR_PACK"})
+    if (std::getenv(n)) return 0;
+  return -1;
+}
+
+// The refined form's low-order parts, as its packing applies them: a group
+// (direction 0: 8 depths of one offset in a tile of 16 samples; 1: 8 samples
+// in a tile of 16 depths) with a selected nonzero low part carries the low
+// parts of all its entries.
+static void add_low_parts(const psoam_plan* P, const int32_t* t0, const float* tab,
+                          const uint8_t* refine, int dir, std::vector<float>& eff) {
+  const auto& g = P->g;
+  const int F = P->F, W = P->W;
+  const int n_l = (dir == 0 ? P->Lz : P->Lt) / 8;
+  const int n_mt = ((dir == 0 ? g.nt : g.nz) + 15) / 16;
+  const size_t n_off = (size_t)F * F;
+  std::vector<uint8_t> mark((size_t)n_mt * n_off * n_l, 0);
+  auto low = [](float v) { return v - from_bf16(to_bf16(v)); };
+  auto each = [&](auto&& f) {
+    for (int z = 0; z < g.nz; ++z)
+      for (size_t o = 0; o < n_off; ++o) {
+        const size_t col = (size_t)z * n_off + o;
+        for (int j = 0; j < W; ++j) {
+          const int t = t0[col] + j;
+          if (tab[col * W + j] == 0.0f || t < 0 || t >= g.nt) continue;
+          const size_t tile = dir == 0 ? t / 16 : z / 16;
+          const size_t l = dir == 0 ? z / 8 : (t + P->tsh) / 8;
+          f(col, col * W + j, (tile * n_off + o) * n_l + l);
+        }
+      }
+  };
+  each([&](size_t col, size_t i, size_t m) {
+    if (refine[col] && low(tab[i]) != 0.0f) mark[m] = 1;
+  });
+  each([&](size_t, size_t i, size_t m) {
+    if (mark[m]) eff[i] += from_bf16(to_bf16(low(tab[i])));
+  });
+}
+
+// Predicted time of one A and one A^T in the direct form, microseconds.  A fit
+// to 710 geometries from 6 x 4 to 256 x 256 (footprints 3 to 41, 1 to 40
+// pulses; half of the predictions within 13%, 90% within 27%): a start-up, the
+// matrix-core products, the chunks a wave runs in series, the staged rows, the
+// A-scans' bytes, and S^T with the exponentials of a per-voxel fluence.
+static double direct_pair_us(const psoam_plan* P) {
+  const auto& g = P->g;
+  const bool half = P->prec != PSOAM_FP32;
+  const bool split = P->prec == PSOAM_BF16_SPLIT || P->prec == PSOAM_FP16_SPLIT;
+  double blocks = P->NB;
+  if (g.n_pulses <= P->Kp - 8) blocks -= 0.5;
+  const double pos = (double)((g.nx + 15) / 16 * 16) * g.ny;
+  double products = 0.0, serial = 0.0;
+  for (const BandTable* T : {&P->fwd, &P->adj}) {
+    const double c = half && T->lds_ok ? T->l_chunks : T->n_chunks;
+    products += 1e-6 * c * pos * blocks;
+    serial += P->NB * c / T->n_mtiles;
+  }
+  const double rows = 2.0 * P->NB * (P->F + 3);
+  const double mb = 4e-6 * g.nx * g.ny * (double)g.n_pulses * (g.nt + g.nz);
+  const double vox = g.phi_per_voxel ? (double)P->NB * g.n_species : 0.0;
+  if (!half) return 39.3 + 19.1 * products + 0.44 * serial + 0.74 * rows + 0.85 * mb + 44.0 * vox;
+  if (split) return 50.6 + 43.8 * products + 0.19 * serial + 4.4 * rows + 1.07 * mb + 51.0 * vox;
+  return 26.1 + 9.6 * products + 0.21 * serial + 0.96 * rows + 0.97 * mb + 29.0 * vox;
+}
+
 static int create_plan_impl(const psoam_geom* gp, const psoam_species* sp, const float* phi,
                             const int32_t* t0, const float* taps, int32_t sir_w, int32_t prec,
-                            hipStream_t stream, int diag, bool build_op, psoam_plan** out) {
+                            hipStream_t stream, int diag, bool build_op, psoam_plan** out,
+                            bool fact = false) {
   if (!out) return fail(PSOAM_EINVAL, "plan_create: out is NULL");
   *out = nullptr;
   if (!gp || !sp || !phi || !t0 || !taps) return fail(PSOAM_EINVAL, "plan_create: NULL argument");
@@ -818,22 +899,12 @@ static int create_plan_impl(const psoam_geom* gp, const psoam_species* sp, const
   const size_t esz = half ? 2 : 4;
   P->bq_bytes = (size_t)P->Yp * P->Xp * P->ps_b * esz;
   P->rq_bytes = (size_t)P->Yp * P->Xp * P->ps_r * esz;
-  PLAN_HIP(hipMalloc(&P->d_bq, P->bq_bytes));
-  PLAN_HIP(hipMalloc(&P->d_rq, P->rq_bytes));
-  PLAN_HIP(hipMemsetAsync(P->d_bq, 0, P->bq_bytes, stream));
-  PLAN_HIP(hipMemsetAsync(P->d_rq, 0, P->rq_bytes, stream));
   if (prec == PSOAM_FP16 || prec == PSOAM_FP16_SPLIT) {
     const float init[8] = {kFp16Scale, 1.0f / kFp16Scale, kFp16Scale, 1.0f / kFp16Scale, 0, 0, 0, 0};
     PLAN_HIP(hipMalloc(&P->d_f16, sizeof(init)));
     PLAN_HIP(hipMemcpy(P->d_f16, init, sizeof(init), hipMemcpyHostToDevice));
     PLAN_HIP(hipMalloc(&P->d_f16acc, 4 * sizeof(unsigned)));
     PLAN_HIP(hipMemset(P->d_f16acc, 0, 4 * sizeof(unsigned)));
-  }
-  if (split) {
-    PLAN_HIP(hipMalloc(&P->d_bq_lo, P->bq_bytes));
-    PLAN_HIP(hipMalloc(&P->d_rq_lo, P->rq_bytes));
-    PLAN_HIP(hipMemsetAsync(P->d_bq_lo, 0, P->bq_bytes, stream));
-    PLAN_HIP(hipMemsetAsync(P->d_rq_lo, 0, P->rq_bytes, stream));
   }
   // refined BF16: the fewest columns, by decreasing squared rounding error of
   // their band values, that hold 90% of the table's squared rounding error
@@ -894,10 +965,48 @@ static int create_plan_impl(const psoam_geom* gp, const psoam_species* sp, const
         }
     tab = tq.data();
   }
-  rc = build_table(P, 0, t0, tab, rf, P->fwd);
-  if (rc != PSOAM_OK) return bail(rc);
-  rc = build_table(P, 1, t0, tab, rf, P->adj);
-  if (rc != PSOAM_OK) return bail(rc);
+  // the spectral form, where it is the faster one (a switch that names one of
+  // the direct form's kernels keeps the direct form)
+  const int spectral = spectral_choice();
+  if (spectral != 0) {
+    if ((rc = build_table(P, 0, t0, tab, rf, P->fwd, true)) != PSOAM_OK) return bail(rc);
+    if ((rc = build_table(P, 1, t0, tab, rf, P->adj, true)) != PSOAM_OK) return bail(rc);
+    // the band values as the direct form's matrix cores would read them
+    std::vector<float> ef, ea;
+    const float *pf = taps, *pa = taps;
+    if (half && !split) {
+      const size_t n = (size_t)g.nz * g.f * g.f * sir_w;
+      ef.resize(n);
+      for (size_t i = 0; i < n; ++i)
+        ef[i] = prec == PSOAM_FP16 ? from_f16(to_f16(tab[i])) : from_bf16(to_bf16(tab[i]));
+      pf = pa = ef.data();
+      if (rf) {
+        ea = ef;
+        add_low_parts(P, t0, tab, rf, 0, ef);
+        add_low_parts(P, t0, tab, rf, 1, ea);
+        pa = ea.data();
+      }
+    }
+    spec_build(P, t0, pf, pa, spectral == 1, direct_pair_us(P), fact, stream);
+  }
+  if (!P->spec) {
+    PLAN_HIP(hipMalloc(&P->d_bq, P->bq_bytes));
+    PLAN_HIP(hipMalloc(&P->d_rq, P->rq_bytes));
+    PLAN_HIP(hipMemsetAsync(P->d_bq, 0, P->bq_bytes, stream));
+    PLAN_HIP(hipMemsetAsync(P->d_rq, 0, P->rq_bytes, stream));
+    if (split) {
+      PLAN_HIP(hipMalloc(&P->d_bq_lo, P->bq_bytes));
+      PLAN_HIP(hipMalloc(&P->d_rq_lo, P->rq_bytes));
+      PLAN_HIP(hipMemsetAsync(P->d_bq_lo, 0, P->bq_bytes, stream));
+      PLAN_HIP(hipMemsetAsync(P->d_rq_lo, 0, P->rq_bytes, stream));
+    }
+  }
+  if (!P->spec) {
+    rc = build_table(P, 0, t0, tab, rf, P->fwd, false);
+    if (rc != PSOAM_OK) return bail(rc);
+    rc = build_table(P, 1, t0, tab, rf, P->adj, false);
+    if (rc != PSOAM_OK) return bail(rc);
+  }
   PLAN_HIP(hipStreamSynchronize(stream));
 #undef PLAN_HIP
   *out = P;
@@ -1043,7 +1152,7 @@ int create_plan_factorised(const psoam_geom* gp, const psoam_species* sp, const 
     for (int j = 0; j < count[col]; ++j) taps[col * width + j] = spr[col];
   }
   psoam_plan* P = nullptr;
-  if (int rc = create_plan_impl(&g, sp, phi, t0.data(), taps.data(), width, prec, stream, 0, true, &P))
+  if (int rc = create_plan_impl(&g, sp, phi, t0.data(), taps.data(), width, prec, stream, 0, true, &P, true))
     return rc;
   P->fact = 1;
   P->eir.n = sh->n_eir;

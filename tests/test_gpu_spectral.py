@@ -1,0 +1,229 @@
+"""The spectral form of the band operator (transforms along x and y, one
+product per lateral frequency) against the direct form and the FP64 oracle:
+transform lengths of every radix, grids narrower than the footprint, odd and
+even lengths on both axes, depths and samples on either side of the 16-wide
+tiles, more depths than samples, one pulse and odd pulse counts, every
+precision, per-depth and per-voxel fluence, pulse volumes, the separable and
+the factorised operator, the residual form inside a solve, and operands with
+zero and with non-finite values.
+
+Tolerances.  Both forms take the same rounded operands and table, so A and
+A^T of the two differ by FP32 summation only; each is within the operator
+bound TOL_OP["fp32"] of the exact sums over those operands, so the two are
+within twice that of each other.  (The split forms drop the product of their
+low parts in the direct form: TOL_OP of that precision.)
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_common import TOL_OP, nan_buf, oracle_S, say, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+# nx, ny, nz, pulses, nt, f, species, per-voxel fluence
+SHAPES = {
+    "one voxel": (1, 1, 1, 1, 1, 1, 1, False),
+    "footprint wider than grid": (3, 5, 17, 2, 33, 15, 2, False),
+    "tile edges": (16, 15, 16, 16, 32, 5, 3, False),
+    "past tile edges": (17, 33, 33, 17, 49, 7, 3, True),
+    "more depths than samples": (12, 9, 90, 3, 20, 9, 2, True),
+    "even by odd lengths": (40, 38, 20, 5, 40, 15, 2, False),
+    "many depths": (9, 8, 200, 33, 70, 3, 1, False),
+    "most pulses": (8, 11, 24, 64, 30, 5, 8, True),
+    "long line": (150, 6, 9, 4, 24, 31, 2, False),
+}
+
+
+def _inputs(shape, seed=5):
+    nx, ny, nz, k, nt, f, ns, voxel = shape
+    rng = np.random.default_rng(seed)
+    t0, taps = synth.random_table(nz, f, nt, 7, rng, t0_lo=-5, t0_hi=nt + 2)
+    phi = rng.uniform(0.2, 1.0, size=(ny, nx, nz) if voxel else nz).astype(np.float32)
+    sp = synth.Species(tuple(rng.uniform(0.1, 1.0, ns)), tuple(rng.uniform(-0.5, 1.0, ns)),
+                       tuple(rng.uniform(1.0, 9.0, ns)), 1.0 if voxel else 0.0)
+    return rng, t0, taps, phi, sp
+
+
+def _plan(monkeypatch, form, shape, t0, taps, phi, sp, prec, **kw):
+    import paper_2510_23739_amd as pk
+    monkeypatch.setenv("PSOAM_SPECTRAL", form)
+    nx, ny, nz, k, nt, f, _, _ = shape
+    return pk.Plan(nx, ny, nz, k, nt, f, phi, sp, t0, taps, prec=prec, **kw)
+
+
+def _rel(a, b):
+    return oracle.rel_err(a.cpu().numpy(), b.cpu().numpy())
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp16", "bf16_split", "bf16_refined"])
+@pytest.mark.parametrize("name", SHAPES)
+def test_matches_direct_form(name, prec, monkeypatch):
+    torch = torch_cuda()
+    shape = SHAPES[name]
+    nx, ny, nz, k, nt, f, ns, voxel = shape
+    rng, t0, taps, phi, sp = _inputs(shape)
+    say(f"[spectral] {name} {prec}")
+    c = torch.from_numpy(rng.standard_normal((ns, ny, nx, nz)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.standard_normal((k, ny, nx, nt)).astype(np.float32)).cuda()
+    out = []
+    for form in "01":
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, prec)
+        # twice: the second call's marks must not see the first one's
+        plan.apply_A(torch.ones_like(c))
+        plan.apply_AT(torch.ones_like(y))
+        a = plan.apply_A(c, nan_buf(plan.y_shape))
+        at = plan.apply_AT(y, nan_buf(plan.c_shape))
+        x, _ = plan.solve(y, k1=2, k2=2, lambda_tv=1e-3, alpha1=1e-3)
+        out.append((a, at, x))
+        plan.close()
+    tol = TOL_OP[prec] if prec.endswith("split") else 2 * TOL_OP["fp32"]
+    e = [_rel(s, d) for s, d in zip(out[1], out[0])]
+    say(f"   A {e[0]:.2e}  A^T {e[1]:.2e}  two iterations {e[2]:.2e}")
+    assert e[0] <= tol and e[1] <= tol
+    # the second iteration's residual is rounded again (one unit of the format)
+    assert e[2] <= max(tol, {"fp32": tol, "bf16_split": tol, "fp16": 2.0 ** -11}.get(prec, 2.0 ** -8))
+    if prec == "fp32":
+        cfg = synth.Config("s", nx=nx, ny=ny, nz=nz, n_species=ns, n_pulses=k, nt=nt, f=f, k1=1)
+        S = oracle_S(cfg, phi, sp)
+        ea = oracle.rel_err(out[1][0].cpu().numpy(), oracle.apply_A(c.cpu().numpy(), S, t0, taps, nt))
+        et = oracle.rel_err(out[1][1].cpu().numpy(), oracle.apply_AT(y.cpu().numpy(), S, t0, taps, nz))
+        say(f"   oracle: A {ea:.2e}  A^T {et:.2e}")
+        assert ea <= TOL_OP["fp32"] and et <= TOL_OP["fp32"]
+
+
+@pytest.mark.parametrize("n", [*range(8, 33), 45, 50, 54, 64, 80, 81, 90, 100, 125, 144, 243, 343, 500])
+def test_transform_lengths(n, monkeypatch):
+    """Grids one row wide whose transforms take every radix and stage count."""
+    torch = torch_cuda()
+    shape = (n - 1, 2, 5, 2, 20, 3, 1, False)
+    rng, t0, taps, phi, sp = _inputs(shape, seed=n)
+    say(f"[spectral] length {n}")
+    c = torch.from_numpy(rng.standard_normal((1, 2, n - 1, 5)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.standard_normal((2, 2, n - 1, 20)).astype(np.float32)).cuda()
+    out = []
+    for form in "01":
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "fp32")
+        out.append((plan.apply_A(c), plan.apply_AT(y)))
+        plan.close()
+    e = [_rel(s, d) for s, d in zip(out[1], out[0])]
+    assert max(e) <= 2 * TOL_OP["fp32"], e
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16"])
+@pytest.mark.parametrize("form", ["acoustic", "separable", "factorised", "traced"])
+def test_other_operators(form, prec, monkeypatch):
+    """Pulse volumes, the separable and the factorised operator, and the
+    objective's recurrence, spectral against direct."""
+    torch = torch_cuda()
+    import paper_2510_23739_amd as pk
+    shape = (21, 18, 19, 7, 40, 9, 3, False)
+    nx, ny, nz, k, nt, f, ns, _ = shape
+    rng, t0, taps, phi, sp = _inputs(shape)
+    say(f"[spectral] {form} {prec}")
+    out = []
+    for s in "01":
+        monkeypatch.setenv("PSOAM_SPECTRAL", s)
+        if form == "acoustic":
+            plan = pk.Plan.acoustic(nx, ny, nz, k, nt, f, t0, taps, prec=prec)
+        elif form == "factorised":
+            eir, origin = synth.eir_taps()
+            plan = pk.Plan.factorised(nx, ny, nz, k, nt, f, phi, sp, synth.spr_table(nz, f), eir, origin,
+                                      *synth.shell_geometry(nz, nt), prec=prec)
+        else:
+            plan = pk.Plan(nx, ny, nz, k, nt, f, phi, sp, t0, taps, prec=prec, separable=form == "separable")
+        g = torch.Generator(device="cuda").manual_seed(3)
+        c = torch.randn(plan.c_shape, device="cuda", generator=g)
+        y = torch.randn(plan.y_shape, device="cuda", generator=g)
+        a, at = plan.apply_A(c, nan_buf(plan.y_shape)), plan.apply_AT(y, nan_buf(plan.c_shape))
+        if form == "traced":
+            x, _, tr = plan.solve(y, k1=4, k2=2, alpha1=1e-3, trace=True)
+            out.append((a, at, x, torch.tensor(tr, dtype=torch.float64)))
+        else:
+            out.append((a, at, plan.solve(y, k1=2, k2=2, alpha1=1e-3)[0]))
+        plan.close()
+    e = [_rel(p, q) for p, q in zip(out[1], out[0])]
+    say(f"   {e}")
+    assert max(e[:2]) <= 2 * TOL_OP["fp32"]
+    assert max(e[2:]) <= (2.0 ** -11 if prec == "fp16" else 4 * TOL_OP["fp32"])
+
+
+@pytest.mark.parametrize("voxel", [False, True])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_bad_values_stay_in_their_footprint(bad, voxel, monkeypatch):
+    """A non-finite concentration or sample reaches the outputs of its
+    footprint and no others, zeros reach nothing, and the next call is clean."""
+    torch = torch_cuda()
+    shape = (24, 22, 10, 5, 30, 7, 2, voxel)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    say(f"[spectral] non-finite {bad} voxel {voxel}")
+    plan = _plan(monkeypatch, "1", shape, t0, taps, phi, sp, "fp32")
+    c = torch.zeros(plan.c_shape, device="cuda")
+    c[1, 9, 14, 3] = 1.0
+    clean = plan.apply_A(c)
+    near = torch.zeros(22, 24, dtype=torch.bool, device="cuda")
+    near[6:13, 11:18] = True
+    assert torch.isfinite(clean).all() and (clean[:, ~near] == 0).all() and (clean[:, near] != 0).any()
+    c[0, 9, 14, 4] = bad
+    y = plan.apply_A(c)
+    assert not torch.isfinite(y[:, 9, 14]).all()
+    assert (y[:, ~near] == 0).all()
+    c[0, 9, 14, 4] = 0.0
+    assert torch.equal(plan.apply_A(c), clean)
+    r = torch.zeros(plan.y_shape, device="cuda")
+    r[4, 3, 20, 8] = bad
+    r[2, 18, 4, 11] = 1.0
+    g = plan.apply_AT(r)
+    far = torch.ones(22, 24, dtype=torch.bool, device="cuda")
+    far[0:7, 17:24] = False
+    far[15:22, 1:8] = False
+    assert not torch.isfinite(g[:, 3, 20]).all() and (g[:, far] == 0).all()
+    assert torch.isfinite(g[:, 15:22, 1:8]).all()
+    r[4, 3, 20, 8] = 0.0
+    g = plan.apply_AT(r)
+    assert torch.isfinite(g).all() and (g[:, 0:7, 17:24] == 0).all()
+    plan.close()
+
+
+def test_replayed_calls_forget(monkeypatch):
+    """A captured A and A^T replayed on other inputs: nothing of an earlier
+    replay's reach or bad values stays."""
+    torch = torch_cuda()
+    shape = (24, 22, 10, 5, 30, 7, 2, False)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    plan = _plan(monkeypatch, "1", shape, t0, taps, phi, sp, "fp32")
+    c, y = torch.zeros(plan.c_shape, device="cuda"), torch.zeros(plan.y_shape, device="cuda")
+    a, g = torch.empty_like(y), torch.empty_like(c)
+    plan.apply_A(c, a)
+    plan.apply_AT(y, g)
+    s = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        plan.apply_A(c, a, stream=s)
+        plan.apply_AT(y, g, stream=s)
+    for i, v in enumerate((1.0, float("nan"), 2.0, 1.0)):
+        c.zero_()
+        y.zero_()
+        c[0, 3 + 4 * i, 5, 4] = v
+        y[1, 17 - 4 * i, 12, 9] = v
+        graph.replay()
+        ra, rg = a.clone(), g.clone()
+        assert torch.equal(torch.nan_to_num(plan.apply_A(c, a), -1.0), torch.nan_to_num(ra, -1.0)), i
+        assert torch.equal(torch.nan_to_num(plan.apply_AT(y, g), -1.0), torch.nan_to_num(rg, -1.0)), i
+        assert torch.isfinite(ra).all() == torch.isfinite(c).all()
+    plan.close()
+
+
+def test_more_depths_than_the_product_holds(monkeypatch):
+    """Beyond 256 depths the plan keeps the direct form whatever is asked for."""
+    torch = torch_cuda()
+    shape = (9, 7, 260, 3, 20, 3, 2, False)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    c = torch.from_numpy(rng.standard_normal((2, 7, 9, 260)).astype(np.float32)).cuda()
+    out = []
+    for form in "01":
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "fp32")
+        out.append(plan.apply_A(c))
+        plan.close()
+    assert torch.equal(out[0], out[1])
