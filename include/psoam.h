@@ -184,8 +184,9 @@ int psoam_prox_tv(const psoam_plan* plan, float* x, const float* z, float theta,
 
 /* psoam_prox_tv for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same dual iteration and result, bit for bit, with its three dual
- * buffers in a static device array of the library instead of a workspace.
+ * the same dual iteration and result, bit for bit, with its three or
+ * (where they fit) four dual buffers in a static device array of the library
+ * instead of a workspace.
  * Limit: S*Ny*Nx*Nz <= 3728256 species-voxels (the array holds 128 MiB on
  * every GPU the library runs on, until the process ends); larger grids get
  * EINVAL and use psoam_prox_tv.  The call allocates nothing; its first call

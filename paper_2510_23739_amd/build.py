@@ -20,7 +20,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libpsoam.so")
-SOURCES = ["psoam_kernels.hip", "psoam_spectral.hip", "psoam_plan.cpp", "psoam_api.cpp"]
+SOURCES = ["psoam_kernels.hip", "psoam_spectral.hip", "psoam_tvmarch.hip", "psoam_plan.cpp", "psoam_api.cpp"]
 # the matrix-core calibration loop of the kernel micro-benchmark, a library of its own
 CALIB_LIB = os.path.join(PKG, "libpsoam_calib.so")
 CALIB_SOURCES = ["calib.hip"]

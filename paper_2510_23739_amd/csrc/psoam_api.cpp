@@ -61,13 +61,13 @@ struct SolveBufs {
   float* xi;
   float* g;
   float* zb;
-  float* u[3];
+  float* u[4];
   float* w;
 };
 
 int ensure_solve_ws(psoam_plan* P, SolveBufs& B) {
   const size_t sv = P->c_elems();
-  const size_t need = sizeof(float) * sv * (5 + 9 + 1) + 256 * 16;
+  const size_t need = sizeof(float) * sv * (5 + 12 + 1) + 256 * 16;
   if (P->solve_ws.bytes < need) {
     if (P->solve_ws.base) PSOAM_HIP(hipFree(P->solve_ws.base));
     P->solve_ws.base = nullptr;
@@ -88,9 +88,10 @@ int ensure_solve_ws(psoam_plan* P, SolveBufs& B) {
   if (!P->d_ctl) PSOAM_HIP(hipMalloc(&P->d_ctl, sizeof(int) * 4));
   auto align = [](char* p) { return (float*)(((uintptr_t)p + 255) & ~(uintptr_t)255); };
   char* p = (char*)P->solve_ws.base;
-  float** slots[] = {&B.cprev, &B.cnext, &B.xi, &B.g, &B.zb, &B.u[0], &B.u[1], &B.u[2], &B.w};
-  const size_t lens[] = {sv, sv, sv, sv, sv, 3 * sv, 3 * sv, 3 * sv, sv};
-  for (int i = 0; i < 9; ++i) {
+  float** slots[] = {&B.cprev, &B.cnext, &B.xi, &B.g, &B.zb, &B.u[0], &B.u[1], &B.u[2],
+                     &B.u[3], &B.w};
+  const size_t lens[] = {sv, sv, sv, sv, sv, 3 * sv, 3 * sv, 3 * sv, 3 * sv, sv};
+  for (int i = 0; i < 10; ++i) {
     float* a = align(p);
     *slots[i] = a;
     p = (char*)(a + lens[i]);
@@ -119,15 +120,15 @@ struct GateGuard {
   GateGuard& operator=(const GateGuard&) = delete;
 };
 
-// x = prox of theta*TV at z by n_inner dual steps (u buffers given), then the
-// final map (mode 0 plain, 1 max(.,0), 2 max(. - th1, 0)).  u_start: dual
-// start (null = 0).  Returns the buffer holding the last dual iterate via
-// *u_last (null if n_inner == 0).
+// x = prox of theta*TV at z by n_inner dual steps, then the final map (mode 0
+// plain, 1 max(.,0), 2 max(. - th1, 0)).  u: four dual buffers; without the
+// fourth (null) every step is a launch of its own.  u_start: dual start (null
+// = 0).  Returns the buffer holding the last dual iterate via *u_last (null if
+// n_inner == 0).
 int tv_prox_core(const psoam_plan* P, float* x, const float* z, float theta, int n_inner,
-                 int mode, float th1, float* const u[3], float* w, const float* u_start,
-                 bool literal, const float** u_last, hipStream_t s) {
+                 int mode, float th1, float* const u[4], const float* u_start, bool literal,
+                 const float** u_last, hipStream_t s) {
   const float inv_mu = (float)inv_mu_tv(P->g);
-  (void)w;  // the fused dual step keeps w on chip; the workspace slot stays in the layout
   if (u_last) *u_last = nullptr;
   if (n_inner <= 0 || theta == 0.0f) {
     PSOAM_HIP(launch_tv_final(P, x, z, nullptr, mode, th1, s));
@@ -136,25 +137,27 @@ int tv_prox_core(const psoam_plan* P, float* x, const float* z, float theta, int
   double t = 1.0, beta_prev = 0.0;
   const float* cur = u_start;   // u_j
   const float* prev = nullptr;  // u_{j-1}
-  int slot = 0;
-  for (int j = 0; j < n_inner; ++j) {
-    // eta_j = u_j + beta_{j-1} (u_j - u_{j-1})
-    float* nxt = u[slot];
-    if (nxt == cur || nxt == prev) {
-      slot = (slot + 1) % 3;
-      nxt = u[slot];
-      if (nxt == cur || nxt == prev) {
-        slot = (slot + 1) % 3;
-        nxt = u[slot];
-      }
+  for (int j = 0; j < n_inner;) {
+    // eta_j = u_j + beta_{j-1} (u_j - u_{j-1}), the next k steps of it
+    const int k = u[3] ? tv_march_steps(P, n_inner - j) : 1;
+    float beta[kTvMaxSteps] = {};
+    for (int i = 0; i < k; ++i) {
+      beta[i] = (float)beta_prev;
+      momentum_step(t, beta_prev, literal);
     }
-    PSOAM_HIP(launch_tv_step(P, nxt, z, cur, prev, (float)beta_prev, inv_mu, theta, s));
-    slot = (slot + 1) % 3;
-    double beta;
-    momentum_step(t, beta, literal);
-    beta_prev = beta;
-    prev = cur;
-    cur = nxt;
+    float* out[2] = {};  // buffers that hold neither u_j nor u_{j-1}
+    for (int i = 0, n = 0; i < 4 && n < 2; ++i)
+      if (u[i] && u[i] != cur && u[i] != prev) out[n++] = u[i];
+    if (k == 1) {
+      PSOAM_HIP(launch_tv_step(P, out[0], z, cur, prev, beta[0], inv_mu, theta, s));
+      prev = cur;
+      cur = out[0];
+    } else {
+      PSOAM_HIP(launch_tv_march(P, k, out[0], out[1], z, cur, prev, beta, inv_mu, theta, s));
+      prev = out[0];
+      cur = out[1];
+    }
+    j += k;
   }
   PSOAM_HIP(launch_tv_final(P, x, z, cur, mode, th1, s));
   if (u_last) *u_last = cur;
@@ -496,7 +499,7 @@ int solve_one(psoam_plan* P, int op, const float* p, float* c, const psoam_solve
   double t = 1.0, f_prev = 0.0;
   bool have_f = false;
   const float* u_warm = nullptr;
-  float* uw[3] = {B.u[0], B.u[1], B.u[2]};
+  float* uw[4] = {B.u[0], B.u[1], B.u[2], B.u[3]};
   if ((rc = prepare_p(P, op, p, s))) return rc;
   // device stopping tests: no host read inside the loop; every kernel of
   // an iteration after the one whose test fires returns at once
@@ -530,19 +533,12 @@ int solve_one(psoam_plan* P, int op, const float* p, float* c, const psoam_solve
     if (r3)
       rc = r3_prox_core(P, B.cnext, B.zb, th3, o->k2, RB, literal, s);
     else
-      rc = tv_prox_core(P, B.cnext, B.zb, th_tv, o->k2, 2, th_l1, uw, B.w,
+      rc = tv_prox_core(P, B.cnext, B.zb, th_tv, o->k2, 2, th_l1, uw,
                         o->warm_inner ? u_warm : nullptr, literal, &u_last, s);
     if (rc) return rc;
-    if (o->warm_inner && u_last) {
-      // keep the last dual iterate out of the next call's rotation
-      u_warm = u_last;
-      int keep = 0;
-      for (int i = 0; i < 3; ++i)
-        if (uw[i] == u_last) keep = i;
-      std::swap(uw[keep], uw[2]);
-      // uw[2] is now the warm start; the next call writes uw[0], uw[1] and may
-      // reuse uw[2] only after it stops being needed.
-    }
+    // the last dual iterate starts the next prox, which writes it only once it
+    // is neither u_j nor u_{j-1}
+    if (o->warm_inner && u_last) u_warm = u_last;
     double beta;
     momentum_step(t, beta, literal);
     PSOAM_HIP(launch_momentum(B.xi, B.cnext, B.cprev, (float)beta, sv, P->d_partial, s));
@@ -658,12 +654,12 @@ int enqueue_iteration(BatchItem& it, hipStream_t s) {
   const float th_l1 = (float)(it.alpha1 * o->lambda_l1);
   if (int rc = enqueue_grad(P, kOpA, B.xi, it.p, B.g, s)) return rc;
   PSOAM_HIP(launch_axpby(B.zb, B.xi, B.g, 1.0f, (float)(-it.alpha1), sv, s));
-  float* uw[3] = {B.u[0], B.u[1], B.u[2]};
+  float* uw[4] = {B.u[0], B.u[1], B.u[2], B.u[3]};
   if (o->lambda_tvs > 0.0) {
     const float th3[3] = {th_tv, (float)(it.alpha1 * o->lambda_tvs), th_l1};
     if (int rc = r3_prox_core(P, B.cnext, B.zb, th3, o->k2, it.RB, literal, s)) return rc;
-  } else if (int rc = tv_prox_core(P, B.cnext, B.zb, th_tv, o->k2, 2, th_l1, uw, B.w, nullptr,
-                                   literal, nullptr, s)) {
+  } else if (int rc = tv_prox_core(P, B.cnext, B.zb, th_tv, o->k2, 2, th_l1, uw, nullptr, literal,
+                                   nullptr, s)) {
     return rc;
   }
   const bool eps2 = it.dev && o->eps2 > 0.0;
@@ -1300,7 +1296,7 @@ int psoam_prox_l1(float* x, const float* z, int64_t n, float thresh, int32_t non
 
 size_t psoam_prox_tv_ws_bytes(const psoam_plan* plan) {
   if (!plan) return 0;
-  return sizeof(float) * plan->c_elems() * 10 + 4 * 256;
+  return sizeof(float) * plan->c_elems() * 12 + 4 * 256;
 }
 
 int psoam_prox_tv(const psoam_plan* plan, float* x, const float* z, float theta,
@@ -1316,10 +1312,10 @@ int psoam_prox_tv(const psoam_plan* plan, float* x, const float* z, float theta,
   float* u0 = (float*)ws;
   float* u1 = align(u0 + 3 * sv);
   float* u2 = align(u1 + 3 * sv);
-  float* w = align(u2 + 3 * sv);
-  float* u[3] = {u0, u1, u2};
+  float* u3 = align(u2 + 3 * sv);
+  float* u[4] = {u0, u1, u2, u3};
   // z and x may alias: keep z intact until the final map, which reads z[v] only at v
-  return tv_prox_core(plan, x, z, theta, n_inner, nonneg ? 1 : 0, 0.0f, u, w, nullptr, false,
+  return tv_prox_core(plan, x, z, theta, n_inner, nonneg ? 1 : 0, 0.0f, u, nullptr, false,
                       nullptr, S(stream));
 }
 
@@ -1462,11 +1458,13 @@ int psoam_prox_tv_noalloc(const psoam_plan* plan, float* x, const float* z, floa
                                   "species-voxels); use psoam_prox_tv with a workspace");
   float* base = nullptr;
   if (int rc = noalloc_scratch(plan->device, &base)) return rc;
-  float* u[3] = {base, base + set, base + 2 * set};
+  // grids that fill the array to three sets take single steps
+  float* u[4] = {base, base + set, base + 2 * set,
+                 4 * set <= kNoAllocFloats ? base + 3 * set : nullptr};
   // the dual iteration writes every dual it reads (the first step starts from
   // u = 0 without reading memory), so the buffer needs no clearing
-  return tv_prox_core(plan, x, z, theta, n_inner, nonneg ? 1 : 0, 0.0f, u, nullptr, nullptr,
-                      false, nullptr, S(stream));
+  return tv_prox_core(plan, x, z, theta, n_inner, nonneg ? 1 : 0, 0.0f, u, nullptr, false,
+                      nullptr, S(stream));
 }
 
 const char* psoam_last_error(void) { return last_error_cstr(); }

@@ -133,6 +133,12 @@ struct SpecPlan {
   unsigned call_b = 0, call_r = 0;
 };
 
+// Launch shape of the marching TV kernel (psoam_tvmarch.hip): positions per
+// thread (0: none fits), columns and rows a workgroup writes, and their counts
+struct TvMarchShape {
+  int p = 0, tx = 0, ty = 0, txb = 0, tyb = 0;
+};
+
 struct Workspace {
   size_t bytes = 0;
   void* base = nullptr;
@@ -150,6 +156,8 @@ struct psoam_plan {
   int Yp, Xp;
   int Lz, Lt;       // contracted lengths of the H operand (z) and H^T operand (t), in samples
   int tsh = 0;      // 16-bit H^T operand: sample t is stored at t + tsh (0 or 4)
+  int tv_march = 0; // most TV dual steps a launch of the marching kernel takes (0: tiles only)
+  psoam::TvMarchShape tv_shape[5];  // its launch shape for 2, 3 and 4 steps
   int tv_tile = 0;  // tile shape of the TV dual step (index into the kernel's shape list)
   size_t ps_b, ps_r;  // elements per padded position of the H / H^T operands
   int device;
@@ -275,6 +283,16 @@ hipError_t launch_prox_l1(float* x, const float* z, int64_t n, float thresh, int
 hipError_t launch_tv_step(const psoam_plan* P, float* u_next, const float* z, const float* u_cur,
                           const float* u_prev, float beta, float inv_mu, float theta,
                           hipStream_t s);
+constexpr int kTvMaxSteps = 4;
+// chooses the plan's tv_march and tv_shape
+void tv_march_plan(psoam_plan* P);
+// k = tv_march_steps(P, left) of the `left` remaining steps in one launch (1:
+// launch_tv_step): u_{j+k-1} into ua, u_{j+k} into ub, both apart from u_cur
+// and u_prev; beta: the weights of the k steps
+int tv_march_steps(const psoam_plan* P, int left);
+hipError_t launch_tv_march(const psoam_plan* P, int k, float* ua, float* ub, const float* z,
+                           const float* u_cur, const float* u_prev, const float* beta, float inv_mu,
+                           float theta, hipStream_t s);
 // tile shapes of the TV dual step: count, and (y, x, z, threads) of shape i
 int tv_tile_count();
 void tv_tile_dims(int i, int* d);

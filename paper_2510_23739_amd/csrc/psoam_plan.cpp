@@ -803,10 +803,15 @@ static int create_plan_impl(const psoam_geom* gp, const psoam_species* sp, const
     if (const char* e = std::getenv("PSOAM_ADJ_SHIFT")) P->tsh = e[0] == '4' ? 4 : 0;
     if (g_tune.tsh == 0 || g_tune.tsh == 4) P->tsh = g_tune.tsh;  // the autotuner's choice
   }
-  // PSOAM_TV_TILE=i takes tile shape i of the TV dual step (tests run each)
+  tv_march_plan(P);
+  // PSOAM_TV_TILE=i takes tile shape i of the TV dual step, one step a launch
+  // (tests run each); PSOAM_TV_MARCH=1 to 4 bounds the steps of a launch
+  if (const char* e = std::getenv("PSOAM_TV_MARCH"))
+    if (const int k = std::atoi(e); k >= 1 && k <= kTvMaxSteps && (k < 2 || P->tv_shape[k].p)) P->tv_march = k;
   if (const char* e = std::getenv("PSOAM_TV_TILE")) {
     const int t = std::atoi(e);
     if (t >= 0 && t < tv_tile_count()) P->tv_tile = t;
+    P->tv_march = 0;
   }
   P->Lt = (g.nt + 15) / 16 * 16 + (P->tsh ? 16 : 0);
   P->ps_b = (size_t)P->Lz * P->Kp;
