@@ -73,8 +73,8 @@ enum {
  * meaning and its results up to FP32 summation.  Results stay inside the
  * footprint: an output is zero where every operand value within its footprint
  * is, and non-finite operand values make the outputs of their footprint
- * non-finite.  The spectra and the table per frequency take device memory (33
- * GB at 320 x 320 x 128 with 40 pulses and 512 samples, 2.4 GB at 128 x 128 x
+ * non-finite.  The spectra and the table per frequency take device memory (23
+ * GB at 320 x 320 x 128 with 40 pulses and 512 samples, 1.6 GB at 128 x 128 x
  * 64 with 32 and 256); a plan for which they exceed a third of the free
  * memory, or cannot be allocated, keeps the direct form.  The environment
  * variable PSOAM_SPECTRAL=0 or 1 at plan creation forces the direct or (where

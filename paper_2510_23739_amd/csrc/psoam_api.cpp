@@ -334,7 +334,7 @@ int enqueue_grad(psoam_plan* P, int op, const float* x, const float* p, float* g
     PSOAM_HIP(launch_band(P, 2, g, nullptr, nullptr, s));
   } else {
     PSOAM_HIP(launch_switch_fwd(P, x, s));
-    PSOAM_HIP(launch_band(P, 1, nullptr, p, P->d_partial, s));
+    PSOAM_HIP(launch_band(P, 1, nullptr, p, P->d_partial, s, nullptr, 0.0, 0, false));
     PSOAM_HIP(launch_band(P, 2, g, nullptr, nullptr, s));
   }
   return PSOAM_OK;
@@ -516,7 +516,7 @@ int solve_one(psoam_plan* P, int op, const float* p, float* c, const psoam_solve
   if (rec) {
     // H's residual form at xi_0 = c_0, which also stores A c_0
     PSOAM_HIP(launch_switch_fwd(P, B.xi, s));
-    PSOAM_HIP(launch_band(P, 1, nullptr, p, P->d_partial, s, yc, 0.0, 1));
+    PSOAM_HIP(launch_band(P, 1, nullptr, p, P->d_partial, s, yc, 0.0, 1, false));
   }
   for (int k = 0; k < o->k1; ++k) {
     // gradient A^T (A xi - p); with the recurrence H at xi_k ran at the end

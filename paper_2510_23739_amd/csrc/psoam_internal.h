@@ -108,7 +108,8 @@ struct SpecPlan {
   int nx = 0, ny = 0;
   int nsx = 0, nsy = 0;
   int radx[4] = {}, rady[4] = {};
-  int lz = 0, lt = 0;     // Nz, Nt rounded up to 16
+  int lz = 0;             // Nz rounded up to 16
+  int tlo = 0, lt = 0;    // samples transformed: first, count (multiples of 16)
   int np = 0;             // pairs of pulses
   size_t nf = 0;          // frequencies of the half plane
   int nblk = 0;           // 16 x 16 blocks of (t, z) per frequency
@@ -253,10 +254,11 @@ hipError_t launch_pack_r(const psoam_plan* P, const float* y, hipStream_t s);
 // mode 0: y = H b (writes y);  mode 1: r = H b - p (p may be null), written into the
 // H^T operand, sum r^2 into partial[]; mode 2: c = S^T H^T r (writes c).
 // Mode 1 with yc: also A c = (H b + yc_beta yc) / (1 + yc_beta) (H b alone
-// when yc_first) written back to yc, and the partials sum (A c - p)^2
+// when yc_first) written back to yc, and the partials sum (A c - p)^2.
+// sums: the partials are going to be read
 hipError_t launch_band(const psoam_plan* P, int mode, float* out, const float* pmeas,
                        double* partial, hipStream_t s, float* yc = nullptr, double yc_beta = 0.0,
-                       int yc_first = 0);
+                       int yc_first = 0, bool sums = true);
 size_t band_partials(const psoam_plan* P, int mode);
 
 // Spectral form (psoam_spectral.hip).  spec_build sets P->spec when the form
@@ -273,7 +275,8 @@ size_t spec_partials(const psoam_plan* P);
 hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s);
 hipError_t spec_pack(const psoam_plan* P, const float* y, hipStream_t s);
 hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pmeas,
-                     double* partial, hipStream_t s, float* yc, double yc_beta, int yc_first);
+                     double* partial, hipStream_t s, float* yc, double yc_beta, int yc_first,
+                     bool sums);
 
 hipError_t launch_prox_l1(float* x, const float* z, int64_t n, float thresh, int nonneg,
                           hipStream_t s);

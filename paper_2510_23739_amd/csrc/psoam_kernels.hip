@@ -1556,7 +1556,8 @@ static hipError_t launch_band_mode(const psoam_plan* P, BandArgs& A, dim3 grid, 
 }
 
 hipError_t launch_band(const psoam_plan* P, int mode, float* out, const float* pmeas,
-                       double* partial, hipStream_t s, float* yc, double yc_beta, int yc_first) {
+                       double* partial, hipStream_t s, float* yc, double yc_beta, int yc_first,
+                       bool sums) {
   // the residual form with the A c recurrence is a kernel form of its own
   // (mode 3), so the plain residual form carries none of its registers
   if (mode == 1 && yc) mode = 3;
@@ -1565,7 +1566,8 @@ hipError_t launch_band(const psoam_plan* P, int mode, float* out, const float* p
       const hipError_t e = f16_scale(P, 3, P->hrow * P->srow, 1.0, s);
       if (e != hipSuccess) return e;
     }
-    return spec_band(P, mode, out, pmeas, partial, s, mode == 3 ? yc : nullptr, yc_beta, yc_first);
+    return spec_band(P, mode, out, pmeas, partial, s, mode == 3 ? yc : nullptr, yc_beta, yc_first,
+                     sums);
   }
   const BandTable& T = (mode == 2) ? P->adj : P->fwd;
   const bool split = P->prec == PSOAM_BF16_SPLIT || P->prec == PSOAM_FP16_SPLIT;

@@ -35,8 +35,8 @@
 //   spec_reach      which outputs nonzero and non-finite operand values reach
 //
 // The transforms and the products are bound by HBM: at 320 x 320 x 128 (40
-// pulses, 512 samples, 360 x 360 frequencies) a spectrum of y is 10.6 GB and
-// the table 5 GB.
+// pulses, 512 samples of which band entries meet 256, 360 x 360 frequencies) a
+// spectrum of y is 5.3 GB and the table 5 GB.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -170,7 +170,8 @@ __device__ __forceinline__ float reached(float v, unsigned char near) {
 
 struct Geo {
   int ny, nx, nyp, nxp;  // grid and transform lengths
-  int nz, nt, lz, lt;    // lengths and their multiples of 16
+  int nz, nt, lz, lt;    // depths, samples; transformed depths and samples (multiples of 16)
+  int tlo;               // first transformed sample
   int nk, np;            // pulses, pairs
   int r, f;
 };
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
   const RowAt at = row_at(G.ny, G.lt);
   const RowMarks W = row_marks(raw, D.n);
   const size_t mrow = (size_t)at.iy * G.nx;
-  const int t = at.l0 + (threadIdx.x & 15);
+  const int tl = at.l0 + (threadIdx.x & 15), t = G.tlo + tl;
   const bool tok = t < G.nt;
   const int k0 = 2 * at.p, k1 = k0 + 1;
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
   fft::first_stage<-1>(D, L, load);
   store_hits(W, D.n, M, mrow, 0, 0, G.nx);
   fft::middle_stages<-1>(D, L);
-  float2* o = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + t;
+  float2* o = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + tl;
   fft::last_stage<-1>(D, L, fft::strided_out(o, G.lt, G.nxp));
 }
 
@@ -338,14 +339,14 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_out(const float2* __restri
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.lt);
-  const int t = at.l0 + (threadIdx.x & 15);
+  const int tl = at.l0 + (threadIdx.x & 15), t = G.tlo + tl;
   const int k0 = 2 * at.p, k1 = k0 + 1;
   const RowMarks W = row_marks(raw, D.n);
   const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
   const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
   load_near(W, D.n, M, mrow, p0, p1, G.nx);
   if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + t;
+  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + tl;
   fft::first_stage<1>(D, L, fft::strided(i, G.lt, G.nxp));
   fft::middle_stages<1>(D, L);
   const size_t o = ((size_t)k0 * grid + (size_t)at.iy * G.nx) * G.nt + t;
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_resid(
   __shared__ double sh[kFftThreads / 64];
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.lt);
-  const int t = at.l0 + (threadIdx.x & 15);
+  const int tl = at.l0 + (threadIdx.x & 15), t = G.tlo + tl;
   const int k0 = 2 * at.p, k1 = k0 + 1;
   const bool two = k1 < G.nk;
   const RowMarks W = row_marks(raw, D.n);
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_resid(
   load_near(W, D.n, M, mrow, p0, p1, G.nx);
   if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + t;
+  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + tl;
   fft::first_stage<1>(D, L, fft::strided(i, G.lt, G.nxp));
   fft::middle_stages<1>(D, L);
   const size_t plane = grid * G.nt;
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_resid(
     mark_points<R>(W, D.n, MR, mrow, mrow, false, x0, step, v);
   });
   store_hits(W, D.n, MR, mrow, 0, 0, G.nx);
-  float2* ov = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + t;
+  float2* ov = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + tl;
   fft::dit_stages(D, L, fft::strided_out(ov, G.lt, G.nxp));
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
@@ -452,6 +453,57 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_resid(
     for (int w = 0; w < kFftThreads / 64; ++w) s += sh[w];
     partial[blockIdx.x] = s;
   }
+}
+
+// The samples no band entry meets (half of them at 320 x 320 x 128 with 512
+// samples and at 128 x 128 x 64 with 256) are not transformed: y is zero there,
+// H^T does not read them, and the objective takes their p^2.  Bound by memory
+// (the zeros are written at 5.5 TB/s: 0.77 ms of 4.2 GB at the larger size).
+// With every sample transformed spec_x_resid took 7.2 ms at that size, without
+// them 3.6 ms; at the smaller one an A took 1.01 and 0.80 ms, an A^T 0.87 and
+// 0.61.
+__global__ __launch_bounds__(256) void spec_idle_zero(float* __restrict__ y, size_t rows, int nt,
+                                                      int lo, int hi,
+                                                      const int* __restrict__ gate) {
+  if (gate && *gate) return;  // a device stop test has ended the solve
+  const int idle = nt - (hi - lo);
+  const size_t n = rows * idle;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+    const size_t r = i / idle;
+    const int j = (int)(i - r * idle);
+    y[r * nt + (j < lo ? j : j + hi - lo)] = 0.0f;
+  }
+}
+// the same where rows and bounds are multiples of four samples
+__global__ __launch_bounds__(256) void spec_idle_zero4(f32x4* __restrict__ y, size_t rows, int nt4,
+                                                       int lo4, int hi4,
+                                                       const int* __restrict__ gate) {
+  if (gate && *gate) return;  // a device stop test has ended the solve
+  const unsigned idle = (unsigned)(nt4 - (hi4 - lo4));
+  for (size_t r = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += (size_t)gridDim.x * 4)
+    for (unsigned j = threadIdx.x & 63; j < idle; j += 64)
+      y[r * nt4 + (j < (unsigned)lo4 ? j : j + hi4 - lo4)] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+}
+constexpr int kIdleSums = 1024;
+__global__ __launch_bounds__(256) void spec_idle_sums(const float* __restrict__ pm, size_t rows,
+                                                      int nt, int lo, int hi,
+                                                      double* __restrict__ partial,
+                                                      const int* __restrict__ gate) {
+  if (gate && *gate) return;  // a device stop test has ended the solve
+  __shared__ double sh[4];
+  double ss = 0.0;
+  const int idle = nt - (hi - lo);
+  if (pm)
+    for (size_t r = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += (size_t)kIdleSums * 4)
+      for (int j = threadIdx.x & 63; j < idle; j += 64) {
+        const double v = (double)pm[r * nt + (j < lo ? j : j + hi - lo)];
+        ss += v * v;
+      }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  if (threadIdx.x == 0) partial[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
 // c-side output of H^T: the pair's two volumes (species after S^T, or pulses)
@@ -938,6 +990,7 @@ Geo geo_of(const psoam_plan* P) {
   G.nt = P->g.nt;
   G.lz = Q.lz;
   G.lt = Q.lt;
+  G.tlo = Q.tlo;
   G.nk = P->g.n_pulses;
   G.np = Q.np;
   G.r = P->R;
@@ -1025,7 +1078,7 @@ int adj_pairs(const psoam_plan* P) {
 
 size_t spec_partials(const psoam_plan* P) {
   const SpecPlan& Q = *P->spec;
-  return (size_t)Q.np * P->g.ny * (Q.lt / 16);
+  return (size_t)Q.np * P->g.ny * (Q.lt / 16) + kIdleSums;
 }
 
 hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s) {
@@ -1074,7 +1127,8 @@ hipError_t spec_pack(const psoam_plan* P, const float* y, hipStream_t s) {
 }
 
 hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pmeas,
-                     double* partial, hipStream_t s, float* yc, double yc_beta, int yc_first) {
+                     double* partial, hipStream_t s, float* yc, double yc_beta, int yc_first,
+                     bool sums) {
   SpecPlan& Q = *P->spec;
   const Geo G = geo_of(P);
   const FftDim X = dim_of(Q, 1), Y = dim_of(Q, 0);
@@ -1094,6 +1148,20 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
                 (const float2*)Q.d_y, (float2*)Q.d_y, G.nxp, G.lt, G.nyp, G.nyp, G.nyp, G.ny, Y,
                 gate_now()));
     const size_t nb = (size_t)Q.np * G.ny * (G.lt / 16);
+    // samples [tlo, thi) are transformed
+    const int thi = std::min(G.nt, G.tlo + G.lt);
+    const size_t rows = (size_t)G.nk * G.ny * G.nx;
+    if (mode == 0 && thi - G.tlo < G.nt) {
+      if (G.nt % 4 == 0 && thi % 4 == 0)  // (y is 16-byte aligned)
+        SPEC_HIP(go(spec_idle_zero4, std::min<size_t>((rows + 3) / 4, 16384), 256, 0, s, (f32x4*)out,
+                    rows, G.nt / 4, G.tlo / 4, thi / 4, gate_now()));
+      else
+        SPEC_HIP(go(spec_idle_zero, std::min<size_t>((rows * 64 + 255) / 256, 16384), 256, 0, s, out,
+                    rows, G.nt, G.tlo, thi, gate_now()));
+    }
+    if (mode != 0 && sums)
+      SPEC_HIP(go(spec_idle_sums, (size_t)kIdleSums, 256, 0, s, pmeas, rows, G.nt, G.tlo, thi,
+                  partial + nb, gate_now()));
     if (mode == 0)
       return go(spec_x_out, nb, kFftThreads, row_lds(G.nxp), s, (const float2*)Q.d_y, out, G, X, MB,
                 gate_now());
@@ -1163,11 +1231,11 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   const auto& g = P->g;
   FftDim X, Y;
   if (!choose_length(g.nx + P->R, X) || !choose_length(g.ny + P->R, Y)) return false;
-  const int lz = (g.nz + 15) / 16 * 16, lt = (g.nt + 15) / 16 * 16;
+  const int lz = (g.nz + 15) / 16 * 16;
   if (lz > 256) return false;  // the product holds every depth in registers
-  const int F = P->F, W = P->W, ntt = lt / 16;
+  const int F = P->F, W = P->W;
   // the 16 x 16 blocks of (t, z) with a nonzero entry at any offset
-  std::vector<unsigned> mask(ntt, 0);
+  std::vector<unsigned> mask((g.nt + 15) / 16, 0);
   for (int z = 0; z < g.nz; ++z)
     for (size_t o = 0; o < (size_t)F * F; ++o) {
       const size_t col = (size_t)z * F * F + o;
@@ -1177,6 +1245,12 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
           mask[t >> 4] |= 1u << (z >> 4);
       }
     }
+  // the range of tiles that any block meets
+  while (mask.size() > 1 && mask.back() == 0) mask.pop_back();
+  int tb0 = 0;
+  while (tb0 + 1 < (int)mask.size() && mask[tb0] == 0) ++tb0;
+  mask.erase(mask.begin(), mask.begin() + tb0);
+  const int ntt = (int)mask.size(), lt = 16 * ntt;
   int nblk = 0;
   for (unsigned m : mask) nblk += __builtin_popcount(m);
   const int np = (g.n_pulses + 1) / 2;
@@ -1203,15 +1277,15 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   if (need > free_b / 3) return false;
   if (!force) {
     // Predicted time of one A and one A^T: the launches, and the bytes of all
-    // passes at 4.2 TB/s (a fit to the same 710 geometries as the direct
-    // form's: half of the predictions within 11%, 90% within 32%).  At 128 x
-    // 128 x 64 with 32 pulses and a footprint of 31 the pair takes 1.9 ms
-    // against the direct form's 41 ms in FP32 and 3.2 ms in BF16; at 97 x 95 x
-    // 16 with a footprint of 7 it takes 0.83 ms against 0.28 ms in BF16.
+    // passes at 4.0 TB/s (a fit to 400 random geometries: half of the
+    // predictions within 13%, 90% within 28%).  At 128 x 128 x 64 with 32
+    // pulses and a footprint of 31 the pair takes 1.4 ms against the direct
+    // form's 41 ms in FP32 and 3.2 ms in BF16; at 97 x 95 x 16 with a
+    // footprint of 7 and 64 samples it takes 0.8 ms against 0.28 ms in BF16.
     const double a = 2.0 * np * g.ny * X.n * lz * 8 + 2.0 * xb + tb + 2.0 * yb + 2.0 * rb;
     const double at = 2.0 * rb + 2.0 * yb + tb + 4.0 * gb;
-    const double y = 4.0 * g.n_pulses * grid * g.nt;
-    const double us = 54.0 + 0.239e-6 * (a + at + (fact ? 4.0 : 2.0) * y);
+    const double y = 4.0 * g.n_pulses * grid;  // a sample of every A-scan
+    const double us = 62.0 + 0.248e-6 * (a + at + y * (g.nt + lt) + (fact ? 2.0 : 0.0) * y * g.nt);
     // 16-bit operands are rounded from sums that differ in their last FP32
     // bits between the forms: the change has to be worth it
     const bool rounds = rnd_of(P) != kRndNone;
@@ -1236,6 +1310,7 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   }
   Q.lz = lz;
   Q.lt = lt;
+  Q.tlo = 16 * tb0;
   Q.np = np;
   Q.nf = nf;
   Q.nblk = nblk;
@@ -1310,7 +1385,7 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
         for (int zb = 0; zb < lz / 16 && ok; ++zb) {
           if (!(mask[tt] >> zb & 1u)) continue;
           hipLaunchKernelGGL(spec_table_x, dim3(kxn, F), dim3(256), 0, stream, d_t0, d_taps, F, W,
-                             g.nz, g.nt, tt, zb, X.n, d_p);
+                             g.nz, g.nt, tb0 + tt, zb, X.n, d_p);
           hipLaunchKernelGGL(spec_table_y, dim3(kxn, (Y.n + kTabY - 1) / kTabY), dim3(256), 0, stream,
                              d_p, F, Y.n, X.n, blk, nblk, scale, tf, ta);
           check(hipGetLastError());

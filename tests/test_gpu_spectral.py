@@ -149,6 +149,37 @@ def test_other_operators(form, prec, monkeypatch):
     assert max(e[2:]) <= (2.0 ** -11 if prec == "fp16" else 4 * TOL_OP["fp32"])
 
 
+@pytest.mark.parametrize("nt", [120, 121, 130, 33])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_samples_no_band_entry_meets(nt, prec, monkeypatch):
+    """A-scans longer than the band on both sides (nt a multiple of four or
+    not, and one with no idle samples): zeros in y, nothing from them in A^T,
+    their p^2 in the objective."""
+    torch = torch_cuda()
+    shape = (20, 17, 12, 5, nt, 7, 2, False)
+    rng, _, _, phi, sp = _inputs(shape)
+    t0, taps = synth.sir_table(12, 7, nt)
+    say(f"[spectral] idle samples nt {nt} {prec}")
+    c = torch.from_numpy(rng.standard_normal((2, 17, 20, 12)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.standard_normal((5, 17, 20, nt)).astype(np.float32)).cuda()
+    out = []
+    for form in "01":
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, prec)
+        a, g = plan.apply_A(c, nan_buf(plan.y_shape)), plan.apply_AT(y, nan_buf(plan.c_shape))
+        res = [a, g]
+        for direct in "10":
+            monkeypatch.setenv("PSOAM_OBJ_DIRECT", direct)
+            x, _, tr = plan.solve(y, k1=4, k2=2, alpha1=1e-2, trace=True)
+            res += [x, torch.tensor(tr, dtype=torch.float64)]
+        out.append(res)
+        plan.close()
+    e = [_rel(p, q) for p, q in zip(out[1], out[0])]
+    say(f"   {e}")
+    assert max(e[:2]) <= 2 * TOL_OP["fp32"]
+    assert max(e[2:]) <= (2.0 ** -8 if prec == "bf16" else 4 * TOL_OP["fp32"])
+    assert torch.equal(out[1][2], out[1][4])
+
+
 @pytest.mark.parametrize("voxel", [False, True])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
 def test_bad_values_stay_in_their_footprint(bad, voxel, monkeypatch):
