@@ -23,6 +23,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 // Every multiply-add of a transform is written out: left to the compiler, two
 // kernels with the same transform could round differently (the residual with
 // and without the objective's recurrence gives the same iterates, bit for bit).
@@ -39,6 +41,14 @@ struct FftDim {
   int n = 0, ns = 0;
   int rad[kFftMaxStages] = {1, 1, 1, 1};
   const float2* tw = nullptr;   // [n] exp(-2 pi i j / n)
+  int m[kFftMaxStages] = {1, 1, 1, 1};  // n / (r_0 ... r_i): between a butterfly's points
+  void derive() {
+    for (int i = 0, p = 1; i < ns; ++i) m[i] = n / (p *= rad[i]);
+  }
+  // largest byte offset of a butterfly's first point on a line of this pitch
+  size_t reach(size_t pitch) const {
+    return (size_t)std::max(m[0], n / rad[ns - 1]) * pitch + 128;
+  }
 };
 
 namespace fft {
@@ -212,19 +222,61 @@ __device__ __forceinline__ Lds carve(unsigned char* raw, const FftDim& D) {
   return L;
 }
 
+// Integer arithmetic costs as much as the transform where it is left to 64-bit
+// and 32-bit multiplies (a quarter of the rate) and divisions: indices below
+// fit 24 bits, a division is a float multiply (exact for b < 2^20, the reciprocal
+// being good to an ulp: (b + 1/2) / m is 1/2m away from the next integer), and a point in memory is a scalar base
+// plus a 32-bit offset that a butterfly computes once.  That and the cheaper
+// marks took a third of the vector instructions out, and tiles that share lines
+// on one XCD a third of the reads; us before and after at 320 x 320 x 128 (256
+// samples, 40 pulses): residual 3660 -> 3150, y -> spectrum 2440 -> 2115,
+// spectrum -> y 2500 -> 1990, S c 1500 -> 1205; at 128 x 128 x 64 (160 samples,
+// 32 pulses) 330 -> 340, 196 -> 178, 214 -> 194 and 104 -> 73.  The larger size
+// is at 4.2 to 4.5 TB/s, a copy's 4.9.
+__device__ __forceinline__ int mul24(int a, int b) { return (int)__umul24((unsigned)a, (unsigned)b); }
+__device__ __forceinline__ float inv_of(int m) { return __builtin_amdgcn_rcpf((float)m); }
+__device__ __forceinline__ int div_by(int b, float inv) { return (int)(((float)b + 0.5f) * inv); }
+template <class T>
+__device__ __forceinline__ T& lds_at(T* base, unsigned byte) {
+  return *(T*)((char*)base + byte);
+}
+
 // natural index of the first output (q = 0) of butterfly b of the last stage
-__device__ __forceinline__ int rev_index(const FftDim& D, int b) {
-  int k = 0;
+__device__ __forceinline__ int rev_index(const FftDim& D, int nb, int b) {
+  int k = 0, w = nb;  // r1 ... r_{s-1}
   // b = ((k1 r2 + k2) r3 + k3): peel the last digit first
-  int w = D.n / D.rad[D.ns - 1];  // r1 ... r_{s-1}
   for (int i = D.ns - 2; i >= 0; --i) {
     const int r = D.rad[i];
-    const int q = b / r;
-    w /= r;
-    k += w * (b - q * r);
+    const float inv = inv_of(r);
+    const int q = div_by(b, inv);
+    w = div_by(w, inv);
+    k += mul24(w, b - mul24(q, r));
     b = q;
   }
   return k;
+}
+
+// Byte offsets of points i0 + q step (q < R) on a line of n points `pitch`
+// bytes apart; those past the end are its last point's.  lane: this lane's
+// offset at a point, top: that of the last lane.
+template <int R>
+__device__ __forceinline__ void offsets(unsigned pitch, unsigned lane, unsigned top, int i0, int step,
+                                        int n, unsigned (&off)[R]) {
+  const unsigned o = (unsigned)i0 * pitch + lane;
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int c = q * step < n ? q * step : n - 1;
+    const unsigned last = (unsigned)(n - 1 - c) * pitch + top;
+    off[q] = (unsigned)c * pitch + (o < last ? o : last);
+  }
+}
+template <class T>
+__device__ __forceinline__ T& at(T* base, unsigned byte) {
+  return *(T*)((char*)base + byte);
+}
+template <class T>
+__device__ __forceinline__ const T& at(const T* base, unsigned byte) {
+  return *(const T*)((const char*)base + byte);
 }
 
 // stage 0 of the natural-order side: load(radix, first index, step, points)
@@ -237,56 +289,75 @@ __device__ __forceinline__ void first_stage(const FftDim& D, const Lds& L, Load&
   __syncthreads();
   with_radix(D.rad[0], [&](auto rc) {
     constexpr int R = decltype(rc)::value;
-    const int m = D.n / R;
+    const int m = D.m[0];
+    const unsigned mb = (unsigned)m * (kFftLanes * sizeof(float2));
     for (int b = row; b < m; b += kFftRows) {
       float2 v[R];
       load(rc, b, m, v);
       Dft<R, SIGN>::run(v);
+      float2* a = L.a + b * kFftLanes + lane;
+      unsigned t = 0;
 #pragma unroll
-      for (int q = 0; q < R; ++q)
-        L.a[(b + q * m) * kFftLanes + lane] = q ? twmul<SIGN>(v[q], L.tw[q * b]) : v[q];
+      for (int q = 0; q < R; ++q, t += 8u * b)
+        lds_at(a, q * mb) = q ? twmul<SIGN>(v[q], lds_at(L.tw, t)) : v[q];
     }
   });
   __syncthreads();
 }
 
-// points of a strided line in HBM; those from index n on are zero (and their
-// loads read the last one)
-__device__ __forceinline__ auto strided(const float2* line, size_t stride, int n) {
+// points of a strided line in HBM (base: its first column; those from index n
+// on are zero); FULL: n is the line's length
+template <bool FULL>
+__device__ __forceinline__ auto strided(const float2* base, unsigned pitch, int n) {
+  const unsigned lane = (threadIdx.x & 15) * 8;
   return [=](auto rc, int i0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
+    if constexpr (FULL) {
+      const unsigned o = (unsigned)i0 * pitch + lane;
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int i = i0 + q * step;
-      v[q] = line[(size_t)(i < n ? i : n - 1) * stride];
+      for (int q = 0; q < R; ++q) v[q] = at(base + (size_t)(q * step) * (pitch / 8), o);
+    } else {
+      const unsigned o = (unsigned)i0 * pitch + lane;
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const int c = q * step < n ? q * step : n - 1;
+        const unsigned last = (unsigned)(n - 1 - c) * pitch + 120;
+        v[q] = at(base + (size_t)c * (pitch / 8), o < last ? o : last);
+      }
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (i0 >= n - q * step) v[q] = {0.0f, 0.0f};
     }
-#pragma unroll
-    for (int q = 0; q < R; ++q)
-      if (i0 + q * step >= n) v[q] = {0.0f, 0.0f};
   };
 }
 
 // stages 1 .. ns - 2, in place; DIT applies the twiddles before the butterfly
 template <int SIGN, bool DIT>
 __device__ __forceinline__ void middle_stage(const FftDim& D, const Lds& L, int s, int p) {
-  // p = r_0 ... r_{s-1}: n / p points are left per block
+  // p = r_0 ... r_{s-1}
   const int lane = threadIdx.x & 15, row = threadIdx.x >> 4;
   with_radix(D.rad[s], [&](auto rc) {
     constexpr int R = decltype(rc)::value;
-    const int len = D.n / p, m = len / R, nb = D.n / R;
+    const int m = D.m[s], nb = p * m, p8 = 8 * p;
+    const float inv = inv_of(m);
+    const unsigned mb = (unsigned)m * (kFftLanes * sizeof(float2));
     for (int b = row; b < nb; b += kFftRows) {
-      const int blk = b / m, j = b - blk * m;
-      float2* a = L.a + (blk * len + j) * kFftLanes + lane;
+      // block b / m of R m points, point j of it
+      const int blk = div_by(b, inv), skip = mul24(blk, m), j = b - skip;
+      float2* a = L.a + (b + skip * (R - 1)) * kFftLanes + lane;
+      const unsigned tj = (unsigned)mul24(p8, j);
       float2 v[R];
+      unsigned t = 0;
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        v[q] = a[q * m * kFftLanes];
-        if (DIT && q) v[q] = twmul<SIGN>(v[q], L.tw[p * q * j]);
+      for (int q = 0; q < R; ++q) v[q] = lds_at(a, q * mb);
+      if constexpr (DIT) {
+#pragma unroll
+        for (int q = 1; q < R; ++q) v[q] = twmul<SIGN>(v[q], lds_at(L.tw, t += tj));
       }
       Dft<R, SIGN>::run(v);
 #pragma unroll
       for (int q = 0; q < R; ++q)
-        a[q * m * kFftLanes] = (!DIT && q) ? twmul<SIGN>(v[q], L.tw[p * q * j]) : v[q];
+        lds_at(a, q * mb) = (!DIT && q) ? twmul<SIGN>(v[q], lds_at(L.tw, t += tj)) : v[q];
     }
   });
   __syncthreads();
@@ -314,20 +385,21 @@ __device__ __forceinline__ void last_stage(const FftDim& D, const Lds& L, Store&
 #pragma unroll
       for (int q = 0; q < R; ++q) v[q] = a[q * kFftLanes];
       Dft<R, SIGN>::run(v);
-      store(rc, rev_index(D, b), nb, v);
+      store(rc, rev_index(D, nb, b), nb, v);
     }
   });
 }
 
 // results of a strided line in HBM, those before index n
-__device__ __forceinline__ auto strided_out(float2* line, size_t stride, int n) {
+template <bool FULL>
+__device__ __forceinline__ auto strided_out(float2* base, unsigned pitch, int n) {
+  const unsigned lane = (threadIdx.x & 15) * 8;
   return [=](auto rc, int i0, int step, const float2* v) {
     constexpr int R = decltype(rc)::value;
+    const unsigned o = (unsigned)i0 * pitch + lane;
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int i = i0 + q * step;
-      if (i < n) line[(size_t)i * stride] = v[q];
-    }
+    for (int q = 0; q < R; ++q)
+      if (FULL || i0 < n - q * step) at(base + (size_t)(q * step) * (pitch / 8), o) = v[q];
   };
 }
 
@@ -345,7 +417,7 @@ __device__ __forceinline__ void turn_stage(const FftDim& D, const Lds& L, Change
 #pragma unroll
       for (int q = 0; q < R; ++q) v[q] = a[q * kFftLanes];
       Dft<R, 1>::run(v);
-      change(rc, rev_index(D, b), nb, v);
+      change(rc, rev_index(D, nb, b), nb, v);
       Dft<R, -1>::run(v);
 #pragma unroll
       for (int q = 0; q < R; ++q) a[q * kFftLanes] = v[q];
@@ -358,21 +430,21 @@ __device__ __forceinline__ void turn_stage(const FftDim& D, const Lds& L, Change
 // to store (as last_stage's)
 template <class Store>
 __device__ __forceinline__ void dit_stages(const FftDim& D, const Lds& L, Store&& store) {
-  int p = D.n / D.rad[D.ns - 1];
-  for (int s = D.ns - 2; s >= 1; --s) {
-    p /= D.rad[s];
-    middle_stage<-1, true>(D, L, s, p);
-  }
+  for (int s = D.ns - 2; s >= 1; --s)
+    middle_stage<-1, true>(D, L, s, (int)((unsigned)D.n / (unsigned)(D.m[s] * D.rad[s])));
   const int lane = threadIdx.x & 15, row = threadIdx.x >> 4;
   with_radix(D.rad[0], [&](auto rc) {
     constexpr int R = decltype(rc)::value;
-    const int m = D.n / R;
+    const int m = D.m[0];
+    const unsigned mb = (unsigned)m * (kFftLanes * sizeof(float2));
     for (int b = row; b < m; b += kFftRows) {
+      float2* a = L.a + b * kFftLanes + lane;
       float2 v[R];
+      unsigned t = 0;
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        v[q] = L.a[(b + q * m) * kFftLanes + lane];
-        if (q) v[q] = twmul<-1>(v[q], L.tw[q * b]);
+      for (int q = 0; q < R; ++q, t += 8u * b) {
+        v[q] = lds_at(a, q * mb);
+        if (q) v[q] = twmul<-1>(v[q], lds_at(L.tw, t));
       }
       Dft<R, -1>::run(v);
       store(rc, b, m, v);

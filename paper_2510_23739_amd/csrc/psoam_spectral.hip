@@ -93,41 +93,55 @@ enum Near { kNearSome = 1, kNearBad = 2 };
 // after the line and its twiddles) and go out once, and the reach of a row's
 // columns comes in once: a mark or a look at one never waits for HBM.
 struct RowMarks {
-  unsigned char* hit;   // [2][n]
-  unsigned char* near;  // [2][n]
+  unsigned char* hit;  // [2][n]
+  signed char* near;   // [2][n]
 };
 __device__ __forceinline__ RowMarks row_marks(unsigned char* raw, int n) {
   unsigned char* a = raw + (size_t)n * (kFftLanes + 1) * sizeof(float2);
-  return RowMarks{a, a + 2 * n};
+  return RowMarks{a, (signed char*)a + 2 * n};
 }
 __host__ __device__ constexpr size_t row_lds(int n) {
   return (size_t)n * ((kFftLanes + 1) * sizeof(float2) + 4);
 }
 // One butterfly's operand values v (R positions x0, x0 + step, ..): the 16
-// lanes of a position join their nonzero bits and its first lane writes the
-// byte (every position belongs to one butterfly); non-finite values, which
-// are rare, are marked in HBM and become zero.  two: the planes differ.
+// lanes of a position (a DPP row) join their nonzero bits and lane q writes
+// position q's byte (every position belongs to one butterfly); non-finite
+// values, which are rare, are marked in HBM and become zero.  two: the planes
+// differ.
+__device__ __forceinline__ unsigned row_or(unsigned h) {
+  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x128, 0xf, 0xf, true);  // row_ror:8
+  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x124, 0xf, 0xf, true);
+  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x122, 0xf, 0xf, true);
+  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x121, 0xf, 0xf, true);
+  return h;
+}
 template <int R>
 __device__ __forceinline__ void mark_points(const RowMarks& W, int n, const Marks& M, size_t row0,
                                             size_t row1, bool two, int x0, int step, float2* v) {
-  const int sh = threadIdx.x & 48;
+  const int lane = threadIdx.x & 15;
+  const int at = x0 + fft::mul24(lane, step);
   bool bad = false;
-  unsigned h0 = 0, h1 = 0;
+  unsigned h0 = 0;
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    bad |= !(finite_(v[q].x) && finite_(v[q].y));
-    const bool a = v[q].x != 0.0f, b = v[q].y != 0.0f;
-    if (((__ballot(two ? a : a || b) >> sh) & 0xffffu) != 0) h0 |= 1u << q;
-    if (two && ((__ballot(b) >> sh) & 0xffffu) != 0) h1 |= 1u << q;
+    // zero where both are, not finite where either is not (or the sum overflows)
+    const float s = fabsf(v[q].x) + fabsf(v[q].y);
+    bad |= !finite_(s);
+    h0 |= s != 0.0f ? 1u << q : 0u;
   }
-  if ((threadIdx.x & 15) == 0) {
+  if (two) {
+    unsigned h1 = 0;
+    h0 = 0;
 #pragma unroll
-    for (int q = 0; q < R; ++q) W.hit[x0 + q * step] = (unsigned char)(h0 >> q & 1u);
-    if (two) {
-#pragma unroll
-      for (int q = 0; q < R; ++q) W.hit[n + x0 + q * step] = (unsigned char)(h1 >> q & 1u);
+    for (int q = 0; q < R; ++q) {
+      h0 |= v[q].x != 0.0f ? 1u << q : 0u;
+      h1 |= v[q].y != 0.0f ? 1u << q : 0u;
     }
+    h1 = row_or(h1);
+    if (lane < R) W.hit[n + at] = (unsigned char)(h1 >> lane & 1u);
   }
+  h0 = row_or(h0);
+  if (lane < R) W.hit[at] = (unsigned char)(h0 >> lane & 1u);
   if (bad) {
 #pragma unroll
     for (int q = 0; q < R; ++q) {
@@ -142,11 +156,43 @@ __device__ __forceinline__ void mark_points(const RowMarks& W, int n, const Mark
     }
   }
 }
+// The reach of the row's columns as bytes to and a value with: all ones where a
+// nonzero value reaches, 0 where none does (and past the grid), kReachBad where
+// a non-finite one does.
+constexpr signed char kReachBad = 127;
+__device__ __forceinline__ signed char reach_of(unsigned char near) {
+  return near & kNearBad ? kReachBad : near & kNearSome ? (signed char)-1 : (signed char)0;
+}
 __device__ __forceinline__ void load_near(const RowMarks& W, int n, const Marks& M, size_t row,
                                           size_t p0, size_t p1, int nx) {
-  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads) {
-    W.near[x] = M.near[p0 + row + x];
-    W.near[n + x] = M.near[p1 + row + x];
+  for (int x = (int)threadIdx.x; x < n; x += kFftThreads) {
+    W.near[x] = x < nx ? reach_of(M.near[p0 + row + x]) : (signed char)0;
+    if (p1 != p0) W.near[n + x] = x < nx ? reach_of(M.near[p1 + row + x]) : (signed char)0;
+  }
+}
+// a butterfly's results, zero or NaN where the reach says so
+template <int R>
+__device__ __forceinline__ void reach_points(const RowMarks& W, int n, bool two, int x0, int step,
+                                             float2* v) {
+  int r0[R], r1[R], most = 0;
+#pragma unroll
+  for (int q = 0; q < R; ++q) r0[q] = r1[q] = W.near[x0 + q * step];
+  if (two) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) r1[q] = W.near[n + x0 + q * step];
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    most = max(most, max(r0[q], r1[q]));
+    v[q].x = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].x) & r0[q]);
+    v[q].y = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].y) & r1[q]);
+  }
+  if (most > 0) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      if (r0[q] > 0) v[q].x = __builtin_nanf("");
+      if (r1[q] > 0) v[q].y = __builtin_nanf("");
+    }
   }
 }
 // (after a barrier) marks of the row into planes p0 and, where it differs, p1
@@ -164,9 +210,6 @@ __device__ __forceinline__ void clear_row(const Marks& M, size_t row, size_t p0,
     if (p1 != p0) M.at[p1 + row + x] = M.bad[p1 + row + x] = 0u;
   }
 }
-__device__ __forceinline__ float reached(float v, unsigned char near) {
-  return near & kNearBad ? __builtin_nanf("") : near & kNearSome ? v : 0.0f;
-}
 
 struct Geo {
   int ny, nx, nyp, nxp;  // grid and transform lengths
@@ -177,13 +220,21 @@ struct Geo {
 };
 
 // ------------------------------------------------------------ x transforms
-// Block: 16 columns (depths or samples l0 .. l0 + 15) of row iy of pair p.
+// Block: 16 columns (depths or samples l0 .. l0 + 15) of row iy of pair p.  On
+// the grid's side 16 columns are half of a 128-byte line, so neighbouring tiles
+// go to one XCD at about the same time: blocks are dealt to the 8 XCDs
+// round-robin, so of 8 kNear successive ones kNear neighbours are 8 apart.
 struct RowAt {
   int p, iy, l0;
+  int b;  // its number in that order
 };
+constexpr int kTilesNear = 4;
 __device__ __forceinline__ RowAt row_at(int ny, int l) {
   int b = (int)blockIdx.x;
+  const int g = 8 * kTilesNear, first = b / g * g;
+  if (first + g <= (int)gridDim.x) b = first + (b & 7) * kTilesNear + ((b - first) >> 3);
   RowAt a;
+  a.b = b;
   const int tiles = l >> 4;
   a.l0 = (b % tiles) * 16;
   b /= tiles;
@@ -212,7 +263,9 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_switch(
   const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
   const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
   const size_t vol = (size_t)G.ny * G.nx * G.nz;
-  const size_t row = (size_t)at.iy * G.nx * G.nz + (zok ? z : 0);
+  const size_t row = (size_t)at.iy * G.nx * G.nz + at.l0;
+  const unsigned pitch = 4u * (unsigned)G.nz, lane = zok ? (threadIdx.x & 15) * 4 : 0,
+                 top = 4u * (unsigned)min(15, G.nz - 1 - at.l0);
   const float sc = RND == kRndF16 ? f16[0] : 1.0f, inv = RND == kRndF16 ? f16[1] : 1.0f;
   float w[2][kMaxSpecies];
   if constexpr (SRC == kSrcDepth) {
@@ -222,33 +275,39 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_switch(
       w[1][s] = (zok && s < sw.ns && k1 < G.nk) ? stab_t[((size_t)k1 * sw.ns + s) * G.nz + z] : 0.0f;
     }
   }
-  // loads past the grid read its last column (their values are dropped)
-  const int xlast = G.nx - 1;
   auto load = [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
-    size_t i[R];
+    // points of a volume's row; past the grid they are its last column (their
+    // values are dropped)
+    unsigned off[R];
+    fft::offsets(pitch, lane, top, x0, step, G.nx, off);
+    auto get = [&](const float* volume, float (&to)[R]) {
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int x = x0 + q * step;
-      i[q] = row + (size_t)(x < G.nx ? x : xlast) * G.nz;
-      v[q] = {0.0f, 0.0f};
-    }
+      for (int q = 0; q < R; ++q) to[q] = fft::at(volume + row, off[q]);
+    };
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[q] = {0.0f, 0.0f};
     if constexpr (SRC == kSrcDiag) {
       const size_t o0 = k0 < sw.ns ? (size_t)k0 * vol : 0, o1 = k1 < sw.ns ? (size_t)k1 * vol : 0;
-      const float p0 = phi[zok ? z : 0];
+      float c0[R], c1[R], ph[R];
+      get(c + o0, c0);
+      get(c + o1, c1);
+      if (sw.per_voxel) {
+        get(phi, ph);
+      } else {
+        const float pz = phi[zok ? z : 0];
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        const float ph = sw.per_voxel ? phi[i[q]] : p0;
-        v[q] = {k0 < sw.ns ? ph * c[o0 + i[q]] : 0.0f, k1 < sw.ns ? ph * c[o1 + i[q]] : 0.0f};
+        for (int q = 0; q < R; ++q) ph[q] = pz;
       }
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        v[q] = {k0 < sw.ns ? ph[q] * c0[q] : 0.0f, k1 < sw.ns ? ph[q] * c1[q] : 0.0f};
     } else if constexpr (SRC == kSrcDepth) {
 #pragma unroll
       for (int s = 0; s < kMaxSpecies; ++s)
         if (s < sw.ns) {
-          const float* cs = c + (size_t)s * vol;
           float cv[R];
-#pragma unroll
-          for (int q = 0; q < R; ++q) cv[q] = cs[i[q]];
+          get(c + (size_t)s * vol, cv);
 #pragma unroll
           for (int q = 0; q < R; ++q) {
             v[q].x = __builtin_fmaf(w[0][s], cv[q], v[q].x);
@@ -257,13 +316,10 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_switch(
         }
     } else {
       float ph[R];
-#pragma unroll
-      for (int q = 0; q < R; ++q) ph[q] = phi[i[q]];
+      get(phi, ph);
       for (int s = 0; s < sw.ns; ++s) {
-        const float* cs = c + (size_t)s * vol;
         float cv[R];
-#pragma unroll
-        for (int q = 0; q < R; ++q) cv[q] = cs[i[q]];
+        get(c + (size_t)s * vol, cv);
 #pragma unroll
         for (int q = 0; q < R; ++q) {
           v[q].x = __builtin_fmaf(spec_coef(sw, ph[q], k0, s), cv[q], v[q].x);
@@ -283,8 +339,8 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_switch(
   fft::first_stage<-1>(D, L, load);
   store_hits(W, D.n, M, mrow, p0, p1, G.nx);
   fft::middle_stages<-1>(D, L);
-  float2* o = out + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lz + z;
-  fft::last_stage<-1>(D, L, fft::strided_out(o, G.lz, G.nxp));
+  float2* o = out + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lz + at.l0;
+  fft::last_stage<-1>(D, L, fft::strided_out<true>(o, 8u * G.lz, G.nxp));
 }
 
 template <int RND>
@@ -304,18 +360,18 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
   const int k0 = 2 * at.p, k1 = k0 + 1;
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
   const size_t plane = (size_t)G.ny * G.nx * G.nt;
-  const float* y0 = y + (size_t)k0 * plane + (size_t)at.iy * G.nx * G.nt + (tok ? t : 0);
+  const int t0 = G.tlo + at.l0;  // (inside the row: the tiles end with its last sample's)
+  const float* y0 = y + (size_t)k0 * plane + (size_t)at.iy * G.nx * G.nt + t0;
   const float* y1 = k1 < G.nk ? y0 + plane : y0;
-  const int xlast = G.nx - 1;
+  const unsigned pitch = 4u * (unsigned)G.nt, lane = tok ? (threadIdx.x & 15) * 4 : 0,
+                 top = 4u * (unsigned)min(15, G.nt - 1 - t0);
   // loads past the grid read its last position (their values are dropped)
   auto load = [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
+    unsigned off[R];
+    fft::offsets(pitch, lane, top, x0, step, G.nx, off);
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int x = x0 + q * step;
-      const size_t i = (size_t)(x < G.nx ? x : xlast) * G.nt;
-      v[q] = {y0[i], y1[i]};
-    }
+    for (int q = 0; q < R; ++q) v[q] = {fft::at(y0, off[q]), fft::at(y1, off[q])};
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const bool ok = tok && x0 + q * step < G.nx;
@@ -327,8 +383,8 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
   fft::first_stage<-1>(D, L, load);
   store_hits(W, D.n, M, mrow, 0, 0, G.nx);
   fft::middle_stages<-1>(D, L);
-  float2* o = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + tl;
-  fft::last_stage<-1>(D, L, fft::strided_out(o, G.lt, G.nxp));
+  float2* o = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + at.l0;
+  fft::last_stage<-1>(D, L, fft::strided_out<true>(o, 8u * G.lt, G.nxp));
 }
 
 // y = H b of the pair's two pulses
@@ -346,19 +402,25 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_out(const float2* __restri
   const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
   load_near(W, D.n, M, mrow, p0, p1, G.nx);
   if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + tl;
-  fft::first_stage<1>(D, L, fft::strided(i, G.lt, G.nxp));
+  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + at.l0;
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.lt, G.nxp));
   fft::middle_stages<1>(D, L);
-  const size_t o = ((size_t)k0 * grid + (size_t)at.iy * G.nx) * G.nt + t;
-  fft::last_stage<1>(D, L, [&](auto rc, int x0, int step, const float2* v) {
+  float* y0 = y + ((size_t)k0 * grid + (size_t)at.iy * G.nx) * G.nt + G.tlo + at.l0;
+  float* y1 = y0 + grid * G.nt;
+  const unsigned pitch = 4u * (unsigned)G.nt, lane = (threadIdx.x & 15) * 4;
+  const bool two = k1 < G.nk;
+  fft::last_stage<1>(D, L, [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
+    reach_points<R>(W, D.n, p1 != p0, x0, step, v);
+    const unsigned o = (unsigned)x0 * pitch + lane;
+    if (t >= G.nt) return;
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int x = x0 + q * step;
-      if (x >= G.nx || t >= G.nt) continue;
-      y[o + (size_t)x * G.nt] = reached(v[q].x, W.near[x]);
-      if (k1 < G.nk) y[o + grid * G.nt + (size_t)x * G.nt] = reached(v[q].y, W.near[D.n + x]);
-    }
+    for (int q = 0; q < R; ++q)
+      if (x0 < G.nx - q * step) {
+        const unsigned oq = o + (unsigned)(q * step) * pitch;
+        fft::at(y0, oq) = v[q].x;
+        if (two) fft::at(y1, oq) = v[q].y;
+      }
   });
 }
 
@@ -367,8 +429,9 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_out(const float2* __restri
 // along x again, the two butterflies on either side of r in registers.  REC:
 // also A c of the iterate by the momentum recurrence, whose (A c - p)^2 the
 // sums are then (see BandArgs::yc).
+// (four workgroups a CU: 128 registers)
 template <int RND, bool REC>
-__global__ __launch_bounds__(kFftThreads) void spec_x_resid(
+__global__ __launch_bounds__(kFftThreads, 4) void spec_x_resid(
     const float2* __restrict__ in, const float* __restrict__ pm, const float* __restrict__ f16,
     float2* __restrict__ out, float* __restrict__ yc, float yc_beta, float yc_inv, int yc_first,
     double* __restrict__ partial, Geo G, FftDim D, Marks M, Marks MR,
@@ -387,53 +450,60 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_resid(
   load_near(W, D.n, M, mrow, p0, p1, G.nx);
   if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + tl;
-  fft::first_stage<1>(D, L, fft::strided(i, G.lt, G.nxp));
+  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + at.l0;
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.lt, G.nxp));
   fft::middle_stages<1>(D, L);
   const size_t plane = grid * G.nt;
-  const size_t o = ((size_t)k0 * grid + (size_t)at.iy * G.nx) * G.nt + t;
-  // loads past the grid or the last pulse read inside it (values dropped)
-  const size_t oc = o - (t < G.nt ? 0 : t), second = two ? plane : 0;
-  const int xlast = G.nx - 1;
+  // the row's samples t0 .. of both pulses (of k0 alone: its own again); loads
+  // past the grid read inside it (values dropped)
+  const int t0 = G.tlo + at.l0;
+  const size_t row0 = ((size_t)k0 * grid + (size_t)at.iy * G.nx) * G.nt + t0,
+               row1 = row0 + (two ? plane : 0);
+  const bool tok = t < G.nt;
+  const unsigned pitch = 4u * (unsigned)G.nt, lane = tok ? (threadIdx.x & 15) * 4 : 0,
+                 top = 4u * (unsigned)min(15, G.nt - 1 - t0);
   double ss = 0.0;
   fft::turn_stage(D, L, [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
+    unsigned off[R];
+    fft::offsets(pitch, lane, top, x0, step, G.nx, off);
     float2 pv[R];
     float2 yo[REC ? R : 1];
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const int x = x0 + q * step;
-      const size_t a = oc + (size_t)(x < G.nx ? x : xlast) * G.nt;
+      auto get = [&](const float* a) {
+        return float2{fft::at(a + row0, off[q]), fft::at(a + row1, off[q])};
+      };
       pv[q] = {0.0f, 0.0f};
-      if (pm) pv[q] = {pm[a], pm[a + second]};
+      if (pm) pv[q] = get(pm);
       if constexpr (REC) {
         yo[q] = {0.0f, 0.0f};
-        if (!yc_first) yo[q] = {yc[a], yc[a + second]};
+        if (!yc_first) yo[q] = get(yc);
       }
     }
+    reach_points<R>(W, D.n, p1 != p0, x0, step, v);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const int x = x0 + q * step;
-      const bool in = x < G.nx && t < G.nt;
-      const int xn = in ? x : 0;
-      const float2 w = {reached(v[q].x, W.near[xn]), two ? reached(v[q].y, W.near[D.n + xn]) : 0.0f};
+      const bool in = tok && x0 < G.nx - q * step;
+      const float2 w = {v[q].x, two ? v[q].y : 0.0f};
       if (!two) pv[q].y = 0.0f;
       float2 d = {w.x - pv[q].x, w.y - pv[q].y};
-      if (in) {
-        if constexpr (REC) {
+      if constexpr (REC) {
+        if (in) {
           float2 n = w;
           if (!yc_first)
             n = {__builtin_fmaf(yc_beta, yo[q].x, w.x) * yc_inv,
                  __builtin_fmaf(yc_beta, yo[q].y, w.y) * yc_inv};
-          const size_t a = o + (size_t)x * G.nt;
-          yc[a] = n.x;
-          if (two) yc[a + plane] = n.y;
+          fft::at(yc + row0, off[q]) = n.x;
+          if (two) fft::at(yc + row1, off[q]) = n.y;
           const double e0 = (double)n.x - (double)pv[q].x,
                        e1 = two ? (double)n.y - (double)pv[q].y : 0.0;
           ss += e0 * e0 + e1 * e1;
-        } else {
-          ss += (double)d.x * (double)d.x + (double)d.y * (double)d.y;
         }
+      } else {
+        // (a product of floats is exact in FP64, so its sum rounds once)
+        const double e0 = in ? (double)d.x : 0.0, e1 = in ? (double)d.y : 0.0;
+        ss += __builtin_fma(e0, e0, e1 * e1);
       }
       d.x = in ? rnd<RND>(d.x, sc, inv) : 0.0f;
       d.y = in ? rnd<RND>(d.y, sc, inv) : 0.0f;
@@ -442,8 +512,8 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_resid(
     mark_points<R>(W, D.n, MR, mrow, mrow, false, x0, step, v);
   });
   store_hits(W, D.n, MR, mrow, 0, 0, G.nx);
-  float2* ov = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + tl;
-  fft::dit_stages(D, L, fft::strided_out(ov, G.lt, G.nxp));
+  float2* ov = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + at.l0;
+  fft::dit_stages(D, L, fft::strided_out<true>(ov, 8u * G.lt, G.nxp));
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
@@ -451,7 +521,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_resid(
   if (threadIdx.x == 0) {
     double s = 0.0;
     for (int w = 0; w < kFftThreads / 64; ++w) s += sh[w];
-    partial[blockIdx.x] = s;
+    partial[at.b] = s;
   }
 }
 
@@ -521,23 +591,32 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_vox(const float2* __restri
   const RowMarks W = row_marks(raw, D.n);
   load_near(W, D.n, M, (size_t)at.iy * G.nx, 0, 0, G.nx);
   if (at.l0 == 0 && at.p == 0) clear_row(M, (size_t)at.iy * G.nx, 0, 0, G.nx);
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lz + z;
-  fft::first_stage<1>(D, L, fft::strided(i, G.lz, G.nxp));
+  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lz + at.l0;
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.lz, G.nxp));
   fft::middle_stages<1>(D, L);
   const size_t vol = (size_t)G.ny * G.nx * G.nz;
-  const size_t o = (size_t)at.iy * G.nx * G.nz + z;
+  const size_t row = (size_t)at.iy * G.nx * G.nz + at.l0;
+  const unsigned pitch = 4u * (unsigned)G.nz, lane = (threadIdx.x & 15) * 4;
   const int v0 = 2 * at.p, v1 = v0 + 1;
-  fft::last_stage<1>(D, L, [&](auto rc, int x0, int step, const float2* v) {
+  fft::last_stage<1>(D, L, [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
+    if (z >= G.nz) return;
+    const unsigned o = (unsigned)x0 * pitch + lane;
+    const float pz = phi_mode == 1 ? phi[z] : 1.0f;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const int x = x0 + q * step;
-      if (x >= G.nx || z >= G.nz) continue;
-      const size_t a = o + (size_t)x * G.nz;
-      const float ph = phi_mode == 2 ? phi[a] : phi_mode == 1 ? phi[z] : 1.0f;
-      c[(size_t)v0 * vol + a] = reached(ph * v[q].x, W.near[x]);
-      if (v1 < nvol) c[(size_t)v1 * vol + a] = reached(ph * v[q].y, W.near[x]);
+      const bool in = x0 < G.nx - q * step;
+      const float ph = phi_mode == 2 && in ? fft::at(phi + row, o + (unsigned)(q * step) * pitch) : pz;
+      v[q] = {ph * v[q].x, ph * v[q].y};
     }
+    reach_points<R>(W, D.n, false, x0, step, v);
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (x0 < G.nx - q * step) {
+        const unsigned oq = o + (unsigned)(q * step) * pitch;
+        fft::at(c + (size_t)v0 * vol + row, oq) = v[q].x;
+        if (v1 < nvol) fft::at(c + (size_t)v1 * vol + row, oq) = v[q].y;
+      }
   });
 }
 
@@ -584,12 +663,14 @@ __global__ __launch_bounds__(kFftThreads) void spec_y(const float2* in, float2* 
   b /= tiles;
   const int kx = b % nxp, p = b / nxp;
   const size_t step = (size_t)nxp * l;
-  const size_t col = (size_t)kx * l + l0 + (threadIdx.x & 15);
+  const unsigned pitch = 8u * (unsigned)step;
+  const size_t col = (size_t)kx * l + l0;
   const float2* i = in + (size_t)p * rows_in * step + col;
-  fft::first_stage<SIGN>(D, L, fft::strided(i, step, n_in));
+  // (the grid's side is the shorter one)
+  fft::first_stage<SIGN>(D, L, fft::strided<(SIGN > 0)>(i, pitch, n_in));
   fft::middle_stages<SIGN>(D, L);
   float2* o = out + (size_t)p * rows_out * step + col;
-  fft::last_stage<SIGN>(D, L, fft::strided_out(o, step, n_out));
+  fft::last_stage<SIGN>(D, L, fft::strided_out<(SIGN < 0)>(o, pitch, n_out));
 }
 
 // ------------------------------------------------- products per frequency
@@ -1015,6 +1096,7 @@ FftDim dim_of(const SpecPlan& Q, int axis) {
   D.ns = axis ? Q.nsx : Q.nsy;
   for (int i = 0; i < kFftMaxStages; ++i) D.rad[i] = axis ? Q.radx[i] : Q.rady[i];
   D.tw = (const float2*)(axis ? Q.d_twx : Q.d_twy);
+  D.derive();
   return D;
 }
 
@@ -1267,6 +1349,14 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   const size_t tb = (nf * nblk + 2) * 512 * sizeof(float);
   const size_t pb = (size_t)(X.n / 2 + 1) * F * 256 * sizeof(double2);
   const size_t grid = (size_t)g.ny * g.nx;
+  // the transforms' offsets within a line are 32 bits, its positions 20
+  X.derive();
+  Y.derive();
+  const size_t most = (size_t)std::max(lz, lt) * 8;
+  if (std::max({X.n * std::max<size_t>(most, 4 * (size_t)std::max(g.nt, g.nz)),
+                Y.reach(most * X.n)}) >= (1ull << 32) ||
+      std::max(X.n, Y.n) >= (1 << 20))
+    return false;
   // launch grids are 32-bit counts of blocks
   if (nf >= (1u << 31) || (size_t)np * X.n * (lt / 16) >= (1u << 31)) return false;
   size_t free_b = 0, total_b = 0;
