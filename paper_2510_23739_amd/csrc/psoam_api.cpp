@@ -424,13 +424,10 @@ int enqueue_power(psoam_plan* P, int op, SolveBufs& B, const psoam_solve_opts* o
   } else {
     PSOAM_HIP(launch_fill(w, 1.0f, sv, s));
   }
-  PSOAM_HIP(launch_dot(w, w, sv, P->d_partial, P->d_scalars + 1, s));
-  PSOAM_HIP(launch_scale_by_rnorm(v, w, P->d_scalars + 1, sv, s));
+  PSOAM_HIP(launch_power_step(v, false, w, sv, P->d_partial, P->d_scalars, s));
   for (int i = 0; i < o->n_power; ++i) {
     if (int rc = enqueue_grad(P, op, v, nullptr, w, s)) return rc;
-    PSOAM_HIP(launch_dot(v, w, sv, P->d_partial, P->d_scalars + 0, s));
-    PSOAM_HIP(launch_dot(w, w, sv, P->d_partial, P->d_scalars + 1, s));
-    PSOAM_HIP(launch_scale_by_rnorm(v, w, P->d_scalars + 1, sv, s));
+    PSOAM_HIP(launch_power_step(v, true, w, sv, P->d_partial, P->d_scalars, s));
   }
   return PSOAM_OK;
 }

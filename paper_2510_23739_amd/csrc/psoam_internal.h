@@ -313,9 +313,9 @@ hipError_t launch_sum_partials(const double* partial, size_t n, double* out, hip
 //   out[0] = sum |grad c| (TV), out[1] = sum |c|
 hipError_t launch_tv_l1_sums(const psoam_plan* P, const float* c, double* partial,
                              double* out, hipStream_t s);
-// v = w / sqrt(*norm2)  (norm2 on device)
-hipError_t launch_scale_by_rnorm(float* v, const float* w, const double* norm2, int64_t n,
-                                 hipStream_t s);
+// out[0] = <v, w> (0 without dot_v), out[1] = |w|^2, v = w / |w|; partial: 2048 doubles
+hipError_t launch_power_step(float* v, bool dot_v, const float* w, int64_t n, double* partial,
+                             double* out, hipStream_t s);
 hipError_t launch_fill(float* x, float v, int64_t n, hipStream_t s);
 // xi_next = c_next + beta (c_next - c_prev); partial sums of |xi_next - xi|^2 and |xi|^2
 hipError_t launch_momentum(float* xi, const float* c_next, const float* c_prev, float beta,
