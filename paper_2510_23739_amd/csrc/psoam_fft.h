@@ -321,7 +321,9 @@ __device__ __forceinline__ auto strided(const float2* base, unsigned pitch, int 
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const int c = q * step < n ? q * step : n - 1;
-        const unsigned last = (unsigned)(n - 1 - c) * pitch + 120;
+        // (a plane may pass 4 GiB, a butterfly's first point does not)
+        const size_t end = (size_t)(n - 1 - c) * pitch + 120;
+        const unsigned last = end < 0xffffffffu ? (unsigned)end : 0xffffffffu;
         v[q] = at(base + (size_t)c * (pitch / 8), o < last ? o : last);
       }
 #pragma unroll

@@ -258,3 +258,32 @@ def test_more_depths_than_the_product_holds(monkeypatch):
         out.append(plan.apply_A(c))
         plan.close()
     assert torch.equal(out[0], out[1])
+
+
+def test_planes_beyond_four_gibibytes(monkeypatch):
+    """A pair's spectrum of 5.2 GB (1125 x 1125 frequencies, 512 samples, of
+    which entries meet the first and the last tiles): offsets along y pass 32
+    bits."""
+    torch = torch_cuda()
+    shape = (1100, 1100, 4, 1, 512, 3, 1, False)
+    rng, _, _, phi, sp = _inputs(shape)
+    t0 = np.zeros((4, 3, 3), np.int32)
+    t0[3] = 500
+    taps = np.zeros((4, 3, 3, 4), np.float32)
+    taps[[0, 3]] = rng.standard_normal((2, 3, 3, 4)).astype(np.float32)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    c = torch.randn((1, 1100, 1100, 4), device="cuda", generator=g)
+    y = torch.randn((1, 1100, 1100, 512), device="cuda", generator=g)
+    out = []
+    for form in "01":
+        say(f"[spectral] planes beyond 4 GiB, form {form}")
+        free = torch.cuda.mem_get_info()[0]
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "bf16")
+        if form == "1":
+            if free - torch.cuda.mem_get_info()[0] < 10e9:
+                plan.close()
+                pytest.skip("no memory for the spectra")
+        out.append((plan.apply_A(c), plan.apply_AT(y)))
+        plan.close()
+    for a, b in zip(*out):
+        assert float((a - b).norm() / a.norm()) <= 2 * TOL_OP["fp32"]
