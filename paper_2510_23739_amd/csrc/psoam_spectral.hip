@@ -1190,6 +1190,14 @@ hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s) {
             (const float2*)Q.d_x, (float2*)Q.d_x, G.nxp, G.lz, G.nyp, G.nyp, G.ny, G.nyp, Y, gate_now());
 }
 
+// The reach of r's marks, beside the pass that made r: what follows only reads
+// it, so that H^T may run again on the same r.
+static hipError_t reach_r(const psoam_plan* P, hipStream_t s) {
+  const Geo G = geo_of(P);
+  const Marks M = marks_r(P);
+  return go(spec_reach, (size_t)M.planes * G.ny, 256, (size_t)G.nx, s, M, G.ny, G.nx, G.r, gate_now());
+}
+
 hipError_t spec_pack(const psoam_plan* P, const float* y, hipStream_t s) {
   SpecPlan& Q = *P->spec;
   const Geo G = geo_of(P);
@@ -1202,10 +1210,11 @@ hipError_t spec_pack(const psoam_plan* P, const float* y, hipStream_t s) {
               gate_now());
   };
   switch (rnd_of(P)) {
-    case kRndBf16: return x(spec_x_pack<kRndBf16>);
-    case kRndF16: return x(spec_x_pack<kRndF16>);
-    default: return x(spec_x_pack<kRndNone>);
+    case kRndBf16: SPEC_HIP(x(spec_x_pack<kRndBf16>)); break;
+    case kRndF16: SPEC_HIP(x(spec_x_pack<kRndF16>)); break;
+    default: SPEC_HIP(x(spec_x_pack<kRndNone>)); break;
   }
+  return reach_r(P, s);
 }
 
 hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pmeas,
@@ -1256,13 +1265,13 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
     };
     const bool rec = yc != nullptr;
     switch (rnd_of(P)) {
-      case kRndBf16: return rec ? r(spec_x_resid<kRndBf16, true>) : r(spec_x_resid<kRndBf16, false>);
-      case kRndF16: return rec ? r(spec_x_resid<kRndF16, true>) : r(spec_x_resid<kRndF16, false>);
-      default: return rec ? r(spec_x_resid<kRndNone, true>) : r(spec_x_resid<kRndNone, false>);
+      case kRndBf16: SPEC_HIP(rec ? r(spec_x_resid<kRndBf16, true>) : r(spec_x_resid<kRndBf16, false>)); break;
+      case kRndF16: SPEC_HIP(rec ? r(spec_x_resid<kRndF16, true>) : r(spec_x_resid<kRndF16, false>)); break;
+      default: SPEC_HIP(rec ? r(spec_x_resid<kRndNone, true>) : r(spec_x_resid<kRndNone, false>)); break;
     }
+    return reach_r(P, s);
   }
   const Marks MR = marks_r(P);
-  SPEC_HIP(go(spec_reach, (size_t)G.ny, 256, (size_t)G.nx, s, MR, G.ny, G.nx, G.r, gate_now()));
   SPEC_HIP(go(spec_y<-1>, (size_t)Q.np * G.nxp * (G.lt / 16), kFftThreads, fft_lds(G.nyp), s,
               (const float2*)Q.d_r, (float2*)Q.d_y, G.nxp, G.lt, G.ny, G.nyp, G.ny, G.nyp, Y,
               gate_now()));

@@ -217,6 +217,27 @@ def test_bad_values_stay_in_their_footprint(bad, voxel, monkeypatch):
     plan.close()
 
 
+@pytest.mark.parametrize("voxel", [False, True])
+@pytest.mark.parametrize("form", ["0", "1"])
+def test_band_only_repeats_the_apply(form, voxel, monkeypatch):
+    """The band kernels alone, on the operands that an A and an A^T left, give
+    what those gave, as often as they are launched."""
+    torch = torch_cuda()
+    shape = (24, 22, 10, 5, 30, 7, 2, voxel)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    say(f"[spectral] band only, form {form} voxel {voxel}")
+    plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "fp32")
+    c = torch.from_numpy(rng.standard_normal(plan.c_shape).astype(np.float32)).cuda()
+    y = torch.zeros(plan.y_shape, device="cuda")
+    y[3, 5, 6] = 1.0
+    a, g = plan.apply_A(c), plan.apply_AT(y)
+    assert (g != 0).any()
+    for _ in range(2):
+        assert torch.equal(plan.band_only(0, nan_buf(plan.y_shape)), a)
+        assert torch.equal(plan.band_only(1, nan_buf(plan.c_shape)), g)
+    plan.close()
+
+
 def test_replayed_calls_forget(monkeypatch):
     """A captured A and A^T replayed on other inputs: nothing of an earlier
     replay's reach or bad values stays."""
