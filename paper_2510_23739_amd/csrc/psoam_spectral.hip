@@ -354,10 +354,11 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.lt);
   const RowMarks W = row_marks(raw, D.n);
-  const size_t mrow = (size_t)at.iy * G.nx;
   const int tl = at.l0 + (threadIdx.x & 15), t = G.tlo + tl;
   const bool tok = t < G.nt;
   const int k0 = 2 * at.p, k1 = k0 + 1;
+  const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
+  const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
   const size_t plane = (size_t)G.ny * G.nx * G.nt;
   const int t0 = G.tlo + at.l0;  // (inside the row: the tiles end with its last sample's)
@@ -378,10 +379,10 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
       v[q].x = ok ? rnd<RND>(v[q].x, sc, inv) : 0.0f;
       v[q].y = ok && k1 < G.nk ? rnd<RND>(v[q].y, sc, inv) : 0.0f;
     }
-    mark_points<R>(W, D.n, M, mrow, mrow, false, x0, step, v);
+    mark_points<R>(W, D.n, M, p0 + mrow, p1 + mrow, p1 != p0, x0, step, v);
   };
   fft::first_stage<-1>(D, L, load);
-  store_hits(W, D.n, M, mrow, 0, 0, G.nx);
+  store_hits(W, D.n, M, mrow, p0, p1, G.nx);
   fft::middle_stages<-1>(D, L);
   float2* o = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + at.l0;
   fft::last_stage<-1>(D, L, fft::strided_out<true>(o, 8u * G.lt, G.nxp));
@@ -447,6 +448,7 @@ __global__ __launch_bounds__(kFftThreads, 4) void spec_x_resid(
   const RowMarks W = row_marks(raw, D.n);
   const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
   const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
+  const size_t r0 = MR.planes == 1 ? 0 : k0 * grid, r1 = MR.planes > k1 ? k1 * grid : r0;
   load_near(W, D.n, M, mrow, p0, p1, G.nx);
   if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
@@ -509,9 +511,9 @@ __global__ __launch_bounds__(kFftThreads, 4) void spec_x_resid(
       d.y = in ? rnd<RND>(d.y, sc, inv) : 0.0f;
       v[q] = d;
     }
-    mark_points<R>(W, D.n, MR, mrow, mrow, false, x0, step, v);
+    mark_points<R>(W, D.n, MR, r0 + mrow, r1 + mrow, r1 != r0, x0, step, v);
   });
-  store_hits(W, D.n, MR, mrow, 0, 0, G.nx);
+  store_hits(W, D.n, MR, mrow, r0, r1, G.nx);
   float2* ov = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + at.l0;
   fft::dit_stages(D, L, fft::strided_out<true>(ov, 8u * G.lt, G.nxp));
 #pragma unroll
@@ -588,16 +590,19 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_vox(const float2* __restri
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.lz);
   const int z = at.l0 + (threadIdx.x & 15);
+  const int v0 = 2 * at.p, v1 = v0 + 1;
   const RowMarks W = row_marks(raw, D.n);
-  load_near(W, D.n, M, (size_t)at.iy * G.nx, 0, 0, G.nx);
-  if (at.l0 == 0 && at.p == 0) clear_row(M, (size_t)at.iy * G.nx, 0, 0, G.nx);
+  // (planes of their own: volumes are pulses)
+  const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
+  const size_t p0 = M.planes == 1 ? 0 : v0 * grid, p1 = M.planes > v1 ? v1 * grid : p0;
+  load_near(W, D.n, M, mrow, p0, p1, G.nx);
+  if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
   const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lz + at.l0;
   fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.lz, G.nxp));
   fft::middle_stages<1>(D, L);
   const size_t vol = (size_t)G.ny * G.nx * G.nz;
   const size_t row = (size_t)at.iy * G.nx * G.nz + at.l0;
   const unsigned pitch = 4u * (unsigned)G.nz, lane = (threadIdx.x & 15) * 4;
-  const int v0 = 2 * at.p, v1 = v0 + 1;
   fft::last_stage<1>(D, L, [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
     if (z >= G.nz) return;
@@ -609,7 +614,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_vox(const float2* __restri
       const float ph = phi_mode == 2 && in ? fft::at(phi + row, o + (unsigned)(q * step) * pitch) : pz;
       v[q] = {ph * v[q].x, ph * v[q].y};
     }
-    reach_points<R>(W, D.n, false, x0, step, v);
+    reach_points<R>(W, D.n, p1 != p0, x0, step, v);
 #pragma unroll
     for (int q = 0; q < R; ++q)
       if (x0 < G.nx - q * step) {
@@ -767,7 +772,8 @@ template <int ZC>
 __global__ __launch_bounds__(512) void spec_gemm_fwd(GemmArgs A) {
   if (A.gate && *A.gate) return;  // a device stop test has ended the solve
   const int f = (int)blockIdx.x;
-  if (A.clear) {  // (frequencies x threads outnumber the positions)
+  // (frequencies x threads, NX NY / 2 x at least 8 a pulse, outnumber the positions of all planes)
+  if (A.clear) {
     const size_t i = (size_t)f * blockDim.x + threadIdx.x;
     if (i < A.n_clear) A.clear[i] = 0u;
   }
@@ -1079,15 +1085,16 @@ Geo geo_of(const psoam_plan* P) {
   return G;
 }
 
-// marks of H's operand (b; pulse volumes of their own have a plane each) and
-// of H^T's (r)
+// marks of H's operand (b) and of H^T's (r): pulse volumes of their own have a
+// plane each, species that every pulse mixes share one
+int mark_planes(const psoam_plan* P) { return P->sw.diag ? P->g.n_pulses : 1; }
 Marks marks_b(const psoam_plan* P) {
   const SpecPlan& Q = *P->spec;
-  return Marks{Q.d_at_b, Q.d_bad_b, Q.d_near_b, Q.call_b, P->sw.diag ? P->g.n_pulses : 1};
+  return Marks{Q.d_at_b, Q.d_bad_b, Q.d_near_b, Q.call_b, mark_planes(P)};
 }
 Marks marks_r(const psoam_plan* P) {
   const SpecPlan& Q = *P->spec;
-  return Marks{Q.d_at_r, Q.d_bad_r, Q.d_near_r, Q.call_r, 1};
+  return Marks{Q.d_at_r, Q.d_bad_r, Q.d_near_r, Q.call_r, mark_planes(P)};
 }
 
 FftDim dim_of(const SpecPlan& Q, int axis) {
@@ -1229,7 +1236,7 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
     GemmArgs A = gemm_args(P, false);
     if (mode != 0) {
       A.clear = Q.d_at_r;  // d_bad_r follows it
-      A.n_clear = 2 * (size_t)G.ny * G.nx;
+      A.n_clear = 2 * (size_t)MB.planes * G.ny * G.nx;
     }
     const int zc = Q.lz / 16;
     if (zc <= 4) SPEC_HIP(go(spec_gemm_fwd<4>, (size_t)Q.nf, waves * 64, 0, s, A));
@@ -1438,16 +1445,16 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   alloc(&Q.d_mask, sizeof(unsigned) * ntt);
   alloc(&Q.d_twx, sizeof(float2) * X.n);
   alloc(&Q.d_twy, sizeof(float2) * Y.n);
-  // marks of b (planes), of r (one plane): two words and a byte per position
-  const size_t planes = P->sw.diag ? g.n_pulses : 1;
-  const size_t mb = (planes + 1) * grid * (2 * sizeof(unsigned) + 1);
+  // marks of b and of r: two words and a byte per position and plane
+  const size_t planes = mark_planes(P);
+  const size_t mb = 2 * planes * grid * (2 * sizeof(unsigned) + 1);
   alloc(&Q.d_marks, mb);
   if (ok) {
     Q.d_at_b = (unsigned*)Q.d_marks;
     Q.d_bad_b = Q.d_at_b + planes * grid;
     Q.d_at_r = Q.d_bad_b + planes * grid;
-    Q.d_bad_r = Q.d_at_r + grid;
-    Q.d_near_b = (unsigned char*)(Q.d_bad_r + grid);
+    Q.d_bad_r = Q.d_at_r + planes * grid;
+    Q.d_near_b = (unsigned char*)(Q.d_bad_r + planes * grid);
     Q.d_near_r = Q.d_near_b + planes * grid;
   }
   alloc(&d_p, pb);

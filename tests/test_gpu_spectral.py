@@ -217,6 +217,41 @@ def test_bad_values_stay_in_their_footprint(bad, voxel, monkeypatch):
     plan.close()
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("k", [4, 5])
+def test_pulse_volumes_stay_apart(k, bad, monkeypatch):
+    """Pulse volumes of their own: a non-finite sample of one pulse and the
+    zeros of its neighbours stay in their volumes, in A, A^T and a solve."""
+    torch = torch_cuda()
+    import paper_2510_23739_amd as pk
+    shape = (21, 18, 19, k, 40, 9, 3, False)
+    rng, t0, taps, _, _ = _inputs(shape)
+    monkeypatch.setenv("PSOAM_SPECTRAL", "1")
+    say(f"[spectral] pulse volumes apart, {k} pulses, {bad}")
+    plan = pk.Plan.acoustic(21, 18, 19, k, 40, 9, t0, taps, prec="fp32")
+    c, y = torch.zeros(plan.c_shape, device="cuda"), torch.zeros(plan.y_shape, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    for v in (c, y):
+        v[1] = torch.randn(v[1].shape, device="cuda", generator=g)
+    ref = plan.apply_A(c), plan.apply_AT(y)
+    # every other pulse is zero; a bad value then goes into pulse 2
+    c[2, 5, 6, 7] = bad
+    y[2, 5, 6, 7] = bad
+    far = torch.ones(18, 21, dtype=torch.bool, device="cuda")
+    far[1:10, 2:11] = False
+    for out, clean in zip((plan.apply_A(c), plan.apply_AT(y)), ref):
+        assert torch.equal(out[1], clean[1]) and (out[1] != 0).any()
+        assert not torch.isfinite(out[2, 5, 6]).all() and (out[2][far] == 0).all()
+        for i in (i for i in range(k) if i not in (1, 2)):
+            assert (out[i] == 0).all(), i
+    y[2, 5, 6, 7] = 0.0
+    x, _ = plan.solve(y, k1=3, k2=0, alpha1=1e-3)
+    assert (x[1] != 0).any()
+    for i in (i for i in range(k) if i != 1):
+        assert (x[i] == 0).all(), i
+    plan.close()
+
+
 @pytest.mark.parametrize("voxel", [False, True])
 @pytest.mark.parametrize("form", ["0", "1"])
 def test_band_only_repeats_the_apply(form, voxel, monkeypatch):
