@@ -70,8 +70,14 @@ enum {
  * product per lateral frequency, all in float32.  Operands and table are
  * rounded to the precision's format exactly as above and then carried in
  * float32 (the _SPLIT forms carry them whole), so a precision keeps its
- * meaning and its results up to FP32 summation.  Results stay inside the
- * footprint: an output is zero where every operand value within its footprint
+ * meaning.  Its FP32 rounding is that of transforms: an output of the direct
+ * form errs in proportion to the values in its own footprint, one of the
+ * spectral form in proportion to the largest of its lateral plane (the same
+ * pulse and the same pair of neighbouring samples or depths), by at most about
+ * 1e-6 of it.  Over whole planes that is no more than the direct form's error;
+ * a region that is weaker than the rest of its plane by a factor w errs by up
+ * to 1e-6 w of its own values.  Pulses do not touch each other.  Results stay
+ * inside the footprint: an output is zero where every operand value within its footprint
  * is, and non-finite operand values make the outputs of their footprint
  * non-finite.  The spectra and the table per frequency take device memory (23
  * GB at 320 x 320 x 128 with 40 pulses and 512 samples, 1.6 GB at 128 x 128 x

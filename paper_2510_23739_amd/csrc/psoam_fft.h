@@ -258,16 +258,16 @@ __device__ __forceinline__ int rev_index(const FftDim& D, int nb, int b) {
 
 // Byte offsets of points i0 + q step (q < R) on a line of n points `pitch`
 // bytes apart; those past the end are its last point's.  lane: this lane's
-// offset at a point, top: that of the last lane.
+// offset at a point.
 template <int R>
-__device__ __forceinline__ void offsets(unsigned pitch, unsigned lane, unsigned top, int i0, int step,
-                                        int n, unsigned (&off)[R]) {
-  const unsigned o = (unsigned)i0 * pitch + lane;
+__device__ __forceinline__ void offsets(unsigned pitch, unsigned lane, int i0, int step, int n,
+                                        unsigned (&off)[R]) {
+  const unsigned o = (unsigned)i0 * pitch;
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const int c = q * step < n ? q * step : n - 1;
-    const unsigned last = (unsigned)(n - 1 - c) * pitch + top;
-    off[q] = (unsigned)c * pitch + (o < last ? o : last);
+    const unsigned last = (unsigned)(n - 1 - c) * pitch;
+    off[q] = (o < last ? o : last) + (unsigned)c * pitch + lane;
   }
 }
 template <class T>
@@ -305,26 +305,24 @@ __device__ __forceinline__ void first_stage(const FftDim& D, const Lds& L, Load&
   __syncthreads();
 }
 
-// points of a strided line in HBM (base: its first column; those from index n
-// on are zero); FULL: n is the line's length
+// points of a strided line in HBM (base: its first column, lane: this lane's
+// byte offset; those from index n on are zero); FULL: n is the line's length
 template <bool FULL>
-__device__ __forceinline__ auto strided(const float2* base, unsigned pitch, int n) {
-  const unsigned lane = (threadIdx.x & 15) * 8;
+__device__ __forceinline__ auto strided(const float2* base, unsigned pitch, int n, unsigned lane) {
   return [=](auto rc, int i0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
+    const unsigned o = (unsigned)i0 * pitch;
     if constexpr (FULL) {
-      const unsigned o = (unsigned)i0 * pitch + lane;
 #pragma unroll
-      for (int q = 0; q < R; ++q) v[q] = at(base + (size_t)(q * step) * (pitch / 8), o);
+      for (int q = 0; q < R; ++q) v[q] = at(base + (size_t)(q * step) * (pitch / 8), o + lane);
     } else {
-      const unsigned o = (unsigned)i0 * pitch + lane;
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const int c = q * step < n ? q * step : n - 1;
         // (a plane may pass 4 GiB, a butterfly's first point does not)
-        const size_t end = (size_t)(n - 1 - c) * pitch + 120;
-        const unsigned last = end < 0xffffffffu ? (unsigned)end : 0xffffffffu;
-        v[q] = at(base + (size_t)c * (pitch / 8), o < last ? o : last);
+        const size_t end = (size_t)(n - 1 - c) * pitch;
+        const unsigned last = end < 0xffffff00u ? (unsigned)end : 0xffffff00u;
+        v[q] = at(base + (size_t)c * (pitch / 8), (o < last ? o : last) + lane);
       }
 #pragma unroll
       for (int q = 0; q < R; ++q)
@@ -392,13 +390,15 @@ __device__ __forceinline__ void last_stage(const FftDim& D, const Lds& L, Store&
   });
 }
 
-// results of a strided line in HBM, those before index n
+// results of a strided line in HBM, those before index n; ok: the lane has a
+// column
 template <bool FULL>
-__device__ __forceinline__ auto strided_out(float2* base, unsigned pitch, int n) {
+__device__ __forceinline__ auto strided_out(float2* base, unsigned pitch, int n, bool ok) {
   const unsigned lane = (threadIdx.x & 15) * 8;
   return [=](auto rc, int i0, int step, const float2* v) {
     constexpr int R = decltype(rc)::value;
     const unsigned o = (unsigned)i0 * pitch + lane;
+    if (!ok) return;
 #pragma unroll
     for (int q = 0; q < R; ++q)
       if (FULL || i0 < n - q * step) at(base + (size_t)(q * step) * (pitch / 8), o) = v[q];

@@ -110,16 +110,16 @@ struct SpecPlan {
   int radx[4] = {}, rady[4] = {};
   int lz = 0;             // Nz rounded up to 16
   int tlo = 0, lt = 0;    // samples transformed: first, count (multiples of 16)
-  int np = 0;             // pairs of pulses
   size_t nf = 0;          // frequencies of the half plane
   int nblk = 0;           // 16 x 16 blocks of (t, z) per frequency
-  void* d_x = nullptr;    // [np][ny][nx][lz] complex: spectrum of S c
-  void* d_y = nullptr;    // [np][ny][nx][lt] complex: spectrum of y or r
-  void* d_r = nullptr;    // [np][Ny][nx][lt] complex: r transformed along x (H^T's operand)
-  void* d_g = nullptr;    // spectrum of H^T r (pairs of species after S^T, else of pulses)
+  void* d_x = nullptr;    // [K][ny][nx][lz / 2] complex: spectrum of S c
+  void* d_y = nullptr;    // [K][ny][nx][lt / 2] complex: spectrum of y or r
+  void* d_r = nullptr;    // [K][Ny][nx][lt / 2] complex: r transformed along x (H^T's operand)
+  void* d_g = nullptr;    // spectrum of H^T r (species after S^T, else pulses)
   float* d_tf = nullptr;  // [nf][nblk][2][64][4]: table of H (real, imaginary)
   float* d_ta = nullptr;  // the same blocks in H^T's lane order
   unsigned* d_mask = nullptr;  // [lt / 16] 16-depth blocks of each t tile
+  float* d_rate = nullptr;     // phi^gamma per voxel where gamma is neither 0 nor 1
   void* d_twx = nullptr;
   void* d_twy = nullptr;
   // marks of H's operand and H^T's: positions with a nonzero value, with a

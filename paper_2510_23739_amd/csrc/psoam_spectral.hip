@@ -19,11 +19,15 @@
 // operands and table are rounded exactly as the direct form rounds them and
 // then carried in float32, so every precision keeps its meaning.
 //
-// Two pulses share one complex image (real and imaginary part): H is real, so
-// the pair goes through the transforms unseparated; the product takes kappa
-// and -kappa together and separates them in registers.
+// Two neighbouring depths (samples) of a pulse share one complex image (real
+// and imaginary part): H is real, so the pair goes through the transforms
+// unseparated; the product takes kappa and -kappa together and separates them
+// in registers.  A transform rounds in proportion to the largest values of its
+// image, so what shares one has to be of one scale: neighbouring depths and
+// samples meet the same band entries, where pulses (paired once) may differ by
+// any factor.
 //
-//   spec_x_switch   S c (or phi c), rounded, pairs packed, transform along x
+//   spec_x_switch   S c (or phi c), rounded, transform along x
 //   spec_y          transform along y (forward, or inverse onto the grid)
 //   spec_gemm_fwd   T B per frequency
 //   spec_x_out      inverse along x, y written
@@ -51,6 +55,7 @@
 namespace psoam {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));  // two floats of a line
 
 namespace {
 
@@ -64,10 +69,17 @@ __device__ __forceinline__ float rnd(float v, float sc, float inv) {
 }
 __device__ __forceinline__ bool finite_(float v) { return fabsf(v) <= 3.402823466e38f; }
 
-__device__ __forceinline__ float spec_coef(const SwitchParams& sw, float phi, int k, int s) {
-  if (sw.diag) return k == s ? phi : 0.0f;
-  const float pg = (sw.gamma == 0.0f) ? 1.0f : powf(phi, sw.gamma);
+// Per-voxel switching: phi^gamma is 1 (gamma 0, phig null), phi (gamma 1, phig
+// the fluence itself) or an array that the plan holds: powf beside the
+// exponentials, though it ran for other gammas alone, took their kernel from 27
+// to 69 us at 77 x 61 x 50 with 19 pulses.
+__device__ __forceinline__ float switch_coef(const SwitchParams& sw, float phi, float pg, int k, int s) {
   return phi * __builtin_fmaf(sw.b[s], expf(-(float)k * pg * sw.inv_tau[s]), sw.a[s]);
+}
+__global__ __launch_bounds__(256) void spec_rate(const float* __restrict__ phi, float* __restrict__ out,
+                                                 float gamma, size_t n) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) out[i] = powf(phi[i], gamma);
 }
 
 // Where the operand is not zero, and where it is not finite.  A transform
@@ -89,25 +101,25 @@ struct Marks {
   int planes;           // 1, or one per pulse (pulse volumes of their own)
 };
 enum Near { kNearSome = 1, kNearBad = 2 };
-// The marks of a workgroup's row collect in LDS (a byte per column x and plane,
-// after the line and its twiddles) and go out once, and the reach of a row's
+// The marks of a workgroup's row collect in LDS (a byte per column x, after
+// the line and its twiddles) and go out once, and the reach of a row's
 // columns comes in once: a mark or a look at one never waits for HBM.
 struct RowMarks {
-  unsigned char* hit;  // [2][n]
-  signed char* near;   // [2][n]
+  unsigned char* hit;  // [n]
+  signed char* near;   // [n]
 };
 __device__ __forceinline__ RowMarks row_marks(unsigned char* raw, int n) {
   unsigned char* a = raw + (size_t)n * (kFftLanes + 1) * sizeof(float2);
-  return RowMarks{a, (signed char*)a + 2 * n};
+  return RowMarks{a, (signed char*)a + n};
 }
 __host__ __device__ constexpr size_t row_lds(int n) {
-  return (size_t)n * ((kFftLanes + 1) * sizeof(float2) + 4);
+  return (size_t)n * ((kFftLanes + 1) * sizeof(float2) + 2);
 }
 // One butterfly's operand values v (R positions x0, x0 + step, ..): the 16
 // lanes of a position (a DPP row) join their nonzero bits and lane q writes
 // position q's byte (every position belongs to one butterfly); non-finite
-// values, which are rare, are marked in HBM and become zero.  two: the planes
-// differ.
+// values, which are rare, are marked in HBM (row: the plane's row) and become
+// zero.
 __device__ __forceinline__ unsigned row_or(unsigned h) {
   h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x128, 0xf, 0xf, true);  // row_ror:8
   h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x124, 0xf, 0xf, true);
@@ -116,43 +128,26 @@ __device__ __forceinline__ unsigned row_or(unsigned h) {
   return h;
 }
 template <int R>
-__device__ __forceinline__ void mark_points(const RowMarks& W, int n, const Marks& M, size_t row0,
-                                            size_t row1, bool two, int x0, int step, float2* v) {
+__device__ __forceinline__ void mark_points(const RowMarks& W, const Marks& M, size_t row, int x0,
+                                            int step, float2* v) {
   const int lane = threadIdx.x & 15;
-  const int at = x0 + fft::mul24(lane, step);
   bool bad = false;
-  unsigned h0 = 0;
+  unsigned h = 0;
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     // zero where both are, not finite where either is not (or the sum overflows)
     const float s = fabsf(v[q].x) + fabsf(v[q].y);
     bad |= !finite_(s);
-    h0 |= s != 0.0f ? 1u << q : 0u;
+    h |= s != 0.0f ? 1u << q : 0u;
   }
-  if (two) {
-    unsigned h1 = 0;
-    h0 = 0;
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      h0 |= v[q].x != 0.0f ? 1u << q : 0u;
-      h1 |= v[q].y != 0.0f ? 1u << q : 0u;
-    }
-    h1 = row_or(h1);
-    if (lane < R) W.hit[n + at] = (unsigned char)(h1 >> lane & 1u);
-  }
-  h0 = row_or(h0);
-  if (lane < R) W.hit[at] = (unsigned char)(h0 >> lane & 1u);
+  h = row_or(h);
+  if (lane < R) W.hit[x0 + fft::mul24(lane, step)] = (unsigned char)(h >> lane & 1u);
   if (bad) {
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      if (!finite_(v[q].x)) {
-        M.bad[row0 + x0 + q * step] = M.now;
-        v[q].x = 0.0f;
-      }
-      if (!finite_(v[q].y)) {
-        M.bad[row1 + x0 + q * step] = M.now;
-        v[q].y = 0.0f;
-      }
+      if (!(finite_(v[q].x) && finite_(v[q].y))) M.bad[row + x0 + q * step] = M.now;
+      if (!finite_(v[q].x)) v[q].x = 0.0f;
+      if (!finite_(v[q].y)) v[q].y = 0.0f;
     }
   }
 }
@@ -163,116 +158,167 @@ constexpr signed char kReachBad = 127;
 __device__ __forceinline__ signed char reach_of(unsigned char near) {
   return near & kNearBad ? kReachBad : near & kNearSome ? (signed char)-1 : (signed char)0;
 }
-__device__ __forceinline__ void load_near(const RowMarks& W, int n, const Marks& M, size_t row,
-                                          size_t p0, size_t p1, int nx) {
-  for (int x = (int)threadIdx.x; x < n; x += kFftThreads) {
-    W.near[x] = x < nx ? reach_of(M.near[p0 + row + x]) : (signed char)0;
-    if (p1 != p0) W.near[n + x] = x < nx ? reach_of(M.near[p1 + row + x]) : (signed char)0;
-  }
+__device__ __forceinline__ void load_near(const RowMarks& W, int n, const Marks& M, size_t row, int nx) {
+  for (int x = (int)threadIdx.x; x < n; x += kFftThreads)
+    W.near[x] = x < nx ? reach_of(M.near[row + x]) : (signed char)0;
 }
 // a butterfly's results, zero or NaN where the reach says so
 template <int R>
-__device__ __forceinline__ void reach_points(const RowMarks& W, int n, bool two, int x0, int step,
-                                             float2* v) {
-  int r0[R], r1[R], most = 0;
+__device__ __forceinline__ void reach_points(const RowMarks& W, int x0, int step, float2* v) {
+  int r[R], most = 0;
 #pragma unroll
-  for (int q = 0; q < R; ++q) r0[q] = r1[q] = W.near[x0 + q * step];
-  if (two) {
-#pragma unroll
-    for (int q = 0; q < R; ++q) r1[q] = W.near[n + x0 + q * step];
-  }
+  for (int q = 0; q < R; ++q) r[q] = W.near[x0 + q * step];
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    most = max(most, max(r0[q], r1[q]));
-    v[q].x = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].x) & r0[q]);
-    v[q].y = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].y) & r1[q]);
+    most = max(most, r[q]);
+    v[q].x = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].x) & r[q]);
+    v[q].y = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].y) & r[q]);
   }
   if (most > 0) {
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      if (r0[q] > 0) v[q].x = __builtin_nanf("");
-      if (r1[q] > 0) v[q].y = __builtin_nanf("");
-    }
+    for (int q = 0; q < R; ++q)
+      if (r[q] > 0) v[q].x = v[q].y = __builtin_nanf("");
   }
 }
-// (after a barrier) marks of the row into planes p0 and, where it differs, p1
-__device__ __forceinline__ void store_hits(const RowMarks& W, int n, const Marks& M, size_t row,
-                                           size_t p0, size_t p1, int nx) {
-  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads) {
-    if (W.hit[x] && M.at[p0 + row + x] != M.now) M.at[p0 + row + x] = M.now;
-    if (p1 != p0 && W.hit[n + x] && M.at[p1 + row + x] != M.now) M.at[p1 + row + x] = M.now;
-  }
+// (after a barrier) marks into their plane's row
+__device__ __forceinline__ void store_hits(const RowMarks& W, const Marks& M, size_t row, int nx) {
+  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads)
+    if (W.hit[x] && M.at[row + x] != M.now) M.at[row + x] = M.now;
 }
 // a workgroup's row of marks, once per row and plane
-__device__ __forceinline__ void clear_row(const Marks& M, size_t row, size_t p0, size_t p1, int nx) {
-  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads) {
-    M.at[p0 + row + x] = M.bad[p0 + row + x] = 0u;
-    if (p1 != p0) M.at[p1 + row + x] = M.bad[p1 + row + x] = 0u;
-  }
+__device__ __forceinline__ void clear_row(const Marks& M, size_t row, int nx) {
+  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads) M.at[row + x] = M.bad[row + x] = 0u;
 }
 
 struct Geo {
   int ny, nx, nyp, nxp;  // grid and transform lengths
-  int nz, nt, lz, lt;    // depths, samples; transformed depths and samples (multiples of 16)
+  int nz, nt, hz, ht;    // depths, samples; columns (pairs of them) of the transformed ones
   int tlo;               // first transformed sample
-  int nk, np;            // pulses, pairs
-  int r, f;
+  int nk;                // pulses
+  int r;
 };
 
 // ------------------------------------------------------------ x transforms
-// Block: 16 columns (depths or samples l0 .. l0 + 15) of row iy of pair p.  On
-// the grid's side 16 columns are half of a 128-byte line, so neighbouring tiles
-// go to one XCD at about the same time: blocks are dealt to the 8 XCDs
-// round-robin, so of 8 kNear successive ones kNear neighbours are 8 apart.
+// Block: 16 columns (pairs of depths or samples 2 c0 .. 2 c0 + 31) of row iy of
+// pulse (or volume) k.  Neighbouring tiles share lines of the grid's side, so
+// they go to one XCD at about the same time: blocks are dealt to the 8 XCDs
+// round-robin, so of 8 kTilesNear successive ones kTilesNear neighbours are 8
+// apart.
 struct RowAt {
-  int p, iy, l0;
+  int k, iy, c0;
   int b;  // its number in that order
 };
+__host__ __device__ constexpr int col_tiles(int h) { return (h + kFftLanes - 1) / kFftLanes; }
 constexpr int kTilesNear = 4;
-__device__ __forceinline__ RowAt row_at(int ny, int l) {
-  int b = (int)blockIdx.x;
-  const int g = 8 * kTilesNear, first = b / g * g;
-  if (first + g <= (int)gridDim.x) b = first + (b & 7) * kTilesNear + ((b - first) >> 3);
+__device__ __forceinline__ int near_order(int near) {
+  const int b = (int)blockIdx.x, g = 8 * near, first = b / g * g;
+  return first + g <= (int)gridDim.x ? first + (b & 7) * near + ((b - first) >> 3) : b;
+}
+__device__ __forceinline__ RowAt row_at(int ny, int h) {
+  int b = near_order(kTilesNear);
   RowAt a;
   a.b = b;
-  const int tiles = l >> 4;
-  a.l0 = (b % tiles) * 16;
+  const int tiles = col_tiles(h);
+  a.c0 = (b % tiles) * kFftLanes;
   b /= tiles;
   a.iy = b % ny;
-  a.p = b / ny;
+  a.k = b / ny;
   return a;
+}
+// The same with kPulsesNear pulses of a tile next to each other, which read the
+// same c (blocks: of a multiple of so many pulses).  us of spec_x_switch for 1,
+// 2, 4 and 8 of them: 539, 367, 366 and 497 at 256 x 256 x 96 with 32 pulses,
+// 1237, 1319, 1470 and 1433 at 320 x 320 x 128 with 40, 87, 83, 90 and 90 at 128
+// x 128 x 64 with 32.
+constexpr int kPulsesNear = 2;
+__host__ __device__ constexpr int pulses_near(int nk) { return (nk + kPulsesNear - 1) / kPulsesNear * kPulsesNear; }
+__device__ __forceinline__ RowAt row_at_pulses(int ny, int h) {
+  int b = near_order(kPulsesNear);
+  RowAt a;
+  a.b = b;
+  a.k = b % kPulsesNear;
+  b /= kPulsesNear;
+  const int tiles = col_tiles(h);
+  a.c0 = (b % tiles) * kFftLanes;
+  b /= tiles;
+  a.iy = b % ny;
+  a.k += b / ny * kPulsesNear;
+  return a;
+}
+// A lane's column: its pair of depths (samples) l and l + 1 of n >= 2, the first
+// one `lo`, of which it holds two, one or (past the last column) none.  On a line
+// of the grid two floats at byte offset `lane` from the tile's `base` hold them:
+// a lane of one reads the value before it too (where the tile has just that one,
+// base is the value before), a lane of none the tile's first two (dropped).
+struct Pair {
+  bool first, both;
+  unsigned lane;
+  int base;
+  // the two floats, and the pair they hold: apart, so that a branch around loads
+  // holds nothing that waits for one
+  __device__ __forceinline__ float2 load(const float* base, unsigned byte) const {
+    const float2u v = *(const float2u*)((const char*)base + byte);
+    return {v.x, v.y};
+  }
+  __device__ __forceinline__ float2 pick(float2 v) const { return {first && !both ? v.y : v.x, v.y}; }
+  __device__ __forceinline__ float2 get(const float* base, unsigned byte) const {
+    return pick(load(base, byte));
+  }
+  __device__ __forceinline__ void put(float* base, unsigned byte, float2 v) const {
+    if (both) *(float2u*)((char*)base + byte) = float2u{v.x, v.y};
+    else if (first) *(float*)((char*)base + byte + 4) = v.x;
+  }
+};
+__device__ __forceinline__ Pair pair_at(int c0, int h, int lo, int n) {
+  const int c = threadIdx.x & 15, l = lo + 2 * (c0 + c);
+  Pair p;
+  p.first = c0 + c < h && l < n;
+  p.both = c0 + c < h && l + 1 < n;
+  const int start = lo + 2 * c0, one = start + 1 == n ? 1 : 0;
+  p.base = start - one;
+  p.lane = p.both ? 8u * (unsigned)c : p.first ? 8u * (unsigned)c - (one ? 0u : 4u) : 0u;
+  return p;
+}
+// the lane's column of a spectrum's line (past the last column: the last)
+struct Column {
+  unsigned lane;
+  bool ok;
+};
+__device__ __forceinline__ Column column_at(size_t c0, size_t h) {
+  const unsigned c = threadIdx.x & 15, last = (unsigned)min((size_t)15, h - 1 - c0);
+  return Column{8u * min(c, last), c <= last};
 }
 
 // where S comes from: the per-depth table, the fluence of each voxel, or
 // diagonal switching (pulse volumes)
 enum Src { kSrcDepth = 0, kSrcVoxel = 1, kSrcDiag = 2 };
 template <int RND, int SRC>
-__global__ __launch_bounds__(kFftThreads) void spec_x_switch(
-    const float* __restrict__ c, const float* __restrict__ phi, const float* __restrict__ stab_t,
-    const float* __restrict__ f16, SwitchParams sw, float2* __restrict__ out, Geo G, FftDim D,
+__global__ __launch_bounds__(kFftThreads, 4) void spec_x_switch(
+    const float* __restrict__ c, const float* __restrict__ phi, const float* phig,
+    const float* __restrict__ stab_t, const float* __restrict__ f16, SwitchParams sw, float2* __restrict__ out, Geo G, FftDim D,
     Marks M, const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
-  const RowAt at = row_at(G.ny, G.lz);
+  const RowAt at = row_at_pulses(G.ny, G.hz);
+  if (at.k >= G.nk) return;
   const RowMarks W = row_marks(raw, D.n);
-  const int z = at.l0 + (threadIdx.x & 15);
-  const bool zok = z < G.nz;
-  const int k0 = 2 * at.p, k1 = k0 + 1;
+  const Pair pr = pair_at(at.c0, G.hz, 0, G.nz);
+  const int k = at.k, z = pr.first ? 2 * (at.c0 + (int)(threadIdx.x & 15)) : 0, z1 = pr.both ? z + 1 : z;
   // the pulses' mark planes
-  const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
-  const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
-  const size_t vol = (size_t)G.ny * G.nx * G.nz;
-  const size_t row = (size_t)at.iy * G.nx * G.nz + at.l0;
-  const unsigned pitch = 4u * (unsigned)G.nz, lane = zok ? (threadIdx.x & 15) * 4 : 0,
-                 top = 4u * (unsigned)min(15, G.nz - 1 - at.l0);
+  const size_t grid = (size_t)G.ny * G.nx;
+  const size_t mrow = (M.planes == 1 ? 0 : k * grid) + (size_t)at.iy * G.nx;
+  const size_t vol = grid * G.nz;
+  const size_t row = (size_t)at.iy * G.nx * G.nz + pr.base;
+  const unsigned pitch = 4u * (unsigned)G.nz;
   const float sc = RND == kRndF16 ? f16[0] : 1.0f, inv = RND == kRndF16 ? f16[1] : 1.0f;
   float w[2][kMaxSpecies];
   if constexpr (SRC == kSrcDepth) {
 #pragma unroll
     for (int s = 0; s < kMaxSpecies; ++s) {
-      w[0][s] = (zok && s < sw.ns) ? stab_t[((size_t)k0 * sw.ns + s) * G.nz + z] : 0.0f;
-      w[1][s] = (zok && s < sw.ns && k1 < G.nk) ? stab_t[((size_t)k1 * sw.ns + s) * G.nz + z] : 0.0f;
+      const float* st = stab_t + ((size_t)k * sw.ns + s) * G.nz;
+      w[0][s] = s < sw.ns ? st[z] : 0.0f;
+      w[1][s] = s < sw.ns ? st[z1] : 0.0f;
     }
   }
   auto load = [&](auto rc, int x0, int step, float2* v) {
@@ -280,67 +326,68 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_switch(
     // points of a volume's row; past the grid they are its last column (their
     // values are dropped)
     unsigned off[R];
-    fft::offsets(pitch, lane, top, x0, step, G.nx, off);
-    auto get = [&](const float* volume, float (&to)[R]) {
+    fft::offsets(pitch, pr.lane, x0, step, G.nx, off);
+    auto get = [&](const float* volume, float2 (&to)[R]) {
 #pragma unroll
-      for (int q = 0; q < R; ++q) to[q] = fft::at(volume + row, off[q]);
+      for (int q = 0; q < R; ++q)
+        to[q] = pr.get(volume + row, off[q]);
     };
 #pragma unroll
     for (int q = 0; q < R; ++q) v[q] = {0.0f, 0.0f};
     if constexpr (SRC == kSrcDiag) {
-      const size_t o0 = k0 < sw.ns ? (size_t)k0 * vol : 0, o1 = k1 < sw.ns ? (size_t)k1 * vol : 0;
-      float c0[R], c1[R], ph[R];
-      get(c + o0, c0);
-      get(c + o1, c1);
+      float2 cv[R], ph[R];
+      get(c + (size_t)k * vol, cv);
       if (sw.per_voxel) {
         get(phi, ph);
       } else {
-        const float pz = phi[zok ? z : 0];
+        const float2 pz = {phi[z], phi[z1]};
 #pragma unroll
         for (int q = 0; q < R; ++q) ph[q] = pz;
       }
 #pragma unroll
-      for (int q = 0; q < R; ++q)
-        v[q] = {k0 < sw.ns ? ph[q] * c0[q] : 0.0f, k1 < sw.ns ? ph[q] * c1[q] : 0.0f};
+      for (int q = 0; q < R; ++q) v[q] = {ph[q].x * cv[q].x, ph[q].y * cv[q].y};
     } else if constexpr (SRC == kSrcDepth) {
 #pragma unroll
       for (int s = 0; s < kMaxSpecies; ++s)
         if (s < sw.ns) {
-          float cv[R];
+          float2 cv[R];
           get(c + (size_t)s * vol, cv);
 #pragma unroll
           for (int q = 0; q < R; ++q) {
-            v[q].x = __builtin_fmaf(w[0][s], cv[q], v[q].x);
-            v[q].y = __builtin_fmaf(w[1][s], cv[q], v[q].y);
+            v[q].x = __builtin_fmaf(w[0][s], cv[q].x, v[q].x);
+            v[q].y = __builtin_fmaf(w[1][s], cv[q].y, v[q].y);
           }
         }
     } else {
-      float ph[R];
+      float2 ph[R], pg[R];
       get(phi, ph);
+#pragma unroll
+      for (int q = 0; q < R; ++q) pg[q] = phig ? ph[q] : float2{1.0f, 1.0f};
+      if (phig && phig != phi) get(phig, pg);
       for (int s = 0; s < sw.ns; ++s) {
-        float cv[R];
+        float2 cv[R];
         get(c + (size_t)s * vol, cv);
 #pragma unroll
         for (int q = 0; q < R; ++q) {
-          v[q].x = __builtin_fmaf(spec_coef(sw, ph[q], k0, s), cv[q], v[q].x);
-          v[q].y = __builtin_fmaf(spec_coef(sw, ph[q], k1, s), cv[q], v[q].y);
+          v[q].x = __builtin_fmaf(switch_coef(sw, ph[q].x, pg[q].x, k, s), cv[q].x, v[q].x);
+          v[q].y = __builtin_fmaf(switch_coef(sw, ph[q].y, pg[q].y, k, s), cv[q].y, v[q].y);
+          if (q & 1) __builtin_amdgcn_sched_barrier(0);  // (few exponentials at a time: registers)
         }
       }
     }
-    // (no pulse k1: its zero weights may have met an infinity)
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const bool ok = zok && x0 + q * step < G.nx;
-      v[q].x = ok ? rnd<RND>(v[q].x, sc, inv) : 0.0f;
-      v[q].y = ok && k1 < G.nk ? rnd<RND>(v[q].y, sc, inv) : 0.0f;
+      const bool in = x0 + q * step < G.nx;
+      v[q].x = in && pr.first ? rnd<RND>(v[q].x, sc, inv) : 0.0f;
+      v[q].y = in && pr.both ? rnd<RND>(v[q].y, sc, inv) : 0.0f;
     }
-    mark_points<R>(W, D.n, M, p0 + mrow, p1 + mrow, p1 != p0, x0, step, v);
+    mark_points<R>(W, M, mrow, x0, step, v);
   };
   fft::first_stage<-1>(D, L, load);
-  store_hits(W, D.n, M, mrow, p0, p1, G.nx);
+  store_hits(W, M, mrow, G.nx);
   fft::middle_stages<-1>(D, L);
-  float2* o = out + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lz + at.l0;
-  fft::last_stage<-1>(D, L, fft::strided_out<true>(o, 8u * G.lz, G.nxp));
+  float2* o = out + ((size_t)k * G.nyp + at.iy) * G.nxp * G.hz + at.c0;
+  fft::last_stage<-1>(D, L, fft::strided_out<true>(o, 8u * G.hz, G.nxp, column_at(at.c0, G.hz).ok));
 }
 
 template <int RND>
@@ -352,76 +399,63 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
-  const RowAt at = row_at(G.ny, G.lt);
+  const RowAt at = row_at(G.ny, G.ht);
   const RowMarks W = row_marks(raw, D.n);
-  const int tl = at.l0 + (threadIdx.x & 15), t = G.tlo + tl;
-  const bool tok = t < G.nt;
-  const int k0 = 2 * at.p, k1 = k0 + 1;
-  const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
-  const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
+  const Pair pr = pair_at(at.c0, G.ht, G.tlo, G.nt);
+  const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
+  const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
-  const size_t plane = (size_t)G.ny * G.nx * G.nt;
-  const int t0 = G.tlo + at.l0;  // (inside the row: the tiles end with its last sample's)
-  const float* y0 = y + (size_t)k0 * plane + (size_t)at.iy * G.nx * G.nt + t0;
-  const float* y1 = k1 < G.nk ? y0 + plane : y0;
-  const unsigned pitch = 4u * (unsigned)G.nt, lane = tok ? (threadIdx.x & 15) * 4 : 0,
-                 top = 4u * (unsigned)min(15, G.nt - 1 - t0);
+  // (inside the row: the tiles end with its last sample's)
+  const float* yk = y + (at.k * grid + yrow) * G.nt + pr.base;
+  const unsigned pitch = 4u * (unsigned)G.nt;
   // loads past the grid read its last position (their values are dropped)
   auto load = [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
     unsigned off[R];
-    fft::offsets(pitch, lane, top, x0, step, G.nx, off);
+    fft::offsets(pitch, pr.lane, x0, step, G.nx, off);
 #pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = {fft::at(y0, off[q]), fft::at(y1, off[q])};
+    for (int q = 0; q < R; ++q) v[q] = pr.get(yk, off[q]);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const bool ok = tok && x0 + q * step < G.nx;
-      v[q].x = ok ? rnd<RND>(v[q].x, sc, inv) : 0.0f;
-      v[q].y = ok && k1 < G.nk ? rnd<RND>(v[q].y, sc, inv) : 0.0f;
+      const bool in = x0 + q * step < G.nx;
+      v[q].x = in && pr.first ? rnd<RND>(v[q].x, sc, inv) : 0.0f;
+      v[q].y = in && pr.both ? rnd<RND>(v[q].y, sc, inv) : 0.0f;
     }
-    mark_points<R>(W, D.n, M, p0 + mrow, p1 + mrow, p1 != p0, x0, step, v);
+    mark_points<R>(W, M, mrow, x0, step, v);
   };
   fft::first_stage<-1>(D, L, load);
-  store_hits(W, D.n, M, mrow, p0, p1, G.nx);
+  store_hits(W, M, mrow, G.nx);
   fft::middle_stages<-1>(D, L);
-  float2* o = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + at.l0;
-  fft::last_stage<-1>(D, L, fft::strided_out<true>(o, 8u * G.lt, G.nxp));
+  float2* o = out + ((size_t)at.k * G.ny + at.iy) * G.nxp * G.ht + at.c0;
+  fft::last_stage<-1>(D, L, fft::strided_out<true>(o, 8u * G.ht, G.nxp, column_at(at.c0, G.ht).ok));
 }
 
-// y = H b of the pair's two pulses
+// y = H b of a pulse
 __global__ __launch_bounds__(kFftThreads) void spec_x_out(const float2* __restrict__ in,
                                                           float* __restrict__ y, Geo G, FftDim D,
                                                           Marks M, const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
-  const RowAt at = row_at(G.ny, G.lt);
-  const int tl = at.l0 + (threadIdx.x & 15), t = G.tlo + tl;
-  const int k0 = 2 * at.p, k1 = k0 + 1;
+  const RowAt at = row_at(G.ny, G.ht);
+  const Pair pr = pair_at(at.c0, G.ht, G.tlo, G.nt);
   const RowMarks W = row_marks(raw, D.n);
-  const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
-  const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
-  load_near(W, D.n, M, mrow, p0, p1, G.nx);
-  if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + at.l0;
-  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.lt, G.nxp));
+  const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
+  const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
+  load_near(W, D.n, M, mrow, G.nx);
+  if (at.c0 == 0 && (M.planes > 1 || at.k == 0)) clear_row(M, mrow, G.nx);
+  const float2* i = in + ((size_t)at.k * G.nyp + at.iy) * G.nxp * G.ht + at.c0;
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.ht, G.nxp, column_at(at.c0, G.ht).lane));
   fft::middle_stages<1>(D, L);
-  float* y0 = y + ((size_t)k0 * grid + (size_t)at.iy * G.nx) * G.nt + G.tlo + at.l0;
-  float* y1 = y0 + grid * G.nt;
-  const unsigned pitch = 4u * (unsigned)G.nt, lane = (threadIdx.x & 15) * 4;
-  const bool two = k1 < G.nk;
+  float* yk = y + (at.k * grid + yrow) * G.nt + pr.base;
+  const unsigned pitch = 4u * (unsigned)G.nt;
   fft::last_stage<1>(D, L, [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
-    reach_points<R>(W, D.n, p1 != p0, x0, step, v);
-    const unsigned o = (unsigned)x0 * pitch + lane;
-    if (t >= G.nt) return;
+    reach_points<R>(W, x0, step, v);
+    const unsigned o = (unsigned)x0 * pitch + pr.lane;
 #pragma unroll
     for (int q = 0; q < R; ++q)
-      if (x0 < G.nx - q * step) {
-        const unsigned oq = o + (unsigned)(q * step) * pitch;
-        fft::at(y0, oq) = v[q].x;
-        if (two) fft::at(y1, oq) = v[q].y;
-      }
+      if (x0 < G.nx - q * step) pr.put(yk, o + (unsigned)(q * step) * pitch, v[q]);
   });
 }
 
@@ -441,81 +475,72 @@ __global__ __launch_bounds__(kFftThreads, 4) void spec_x_resid(
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   __shared__ double sh[kFftThreads / 64];
   const fft::Lds L = fft::carve(raw, D);
-  const RowAt at = row_at(G.ny, G.lt);
-  const int tl = at.l0 + (threadIdx.x & 15), t = G.tlo + tl;
-  const int k0 = 2 * at.p, k1 = k0 + 1;
-  const bool two = k1 < G.nk;
+  const RowAt at = row_at(G.ny, G.ht);
+  const Pair pr = pair_at(at.c0, G.ht, G.tlo, G.nt);
   const RowMarks W = row_marks(raw, D.n);
-  const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
-  const size_t p0 = M.planes == 1 ? 0 : k0 * grid, p1 = M.planes > k1 ? k1 * grid : p0;
-  const size_t r0 = MR.planes == 1 ? 0 : k0 * grid, r1 = MR.planes > k1 ? k1 * grid : r0;
-  load_near(W, D.n, M, mrow, p0, p1, G.nx);
-  if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
+  const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
+  const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
+  const size_t rrow = (MR.planes == 1 ? 0 : at.k * grid) + yrow;
+  load_near(W, D.n, M, mrow, G.nx);
+  if (at.c0 == 0 && (M.planes > 1 || at.k == 0)) clear_row(M, mrow, G.nx);
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lt + at.l0;
-  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.lt, G.nxp));
+  const Column col = column_at(at.c0, G.ht);
+  const float2* i = in + ((size_t)at.k * G.nyp + at.iy) * G.nxp * G.ht + at.c0;
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.ht, G.nxp, col.lane));
   fft::middle_stages<1>(D, L);
-  const size_t plane = grid * G.nt;
-  // the row's samples t0 .. of both pulses (of k0 alone: its own again); loads
-  // past the grid read inside it (values dropped)
-  const int t0 = G.tlo + at.l0;
-  const size_t row0 = ((size_t)k0 * grid + (size_t)at.iy * G.nx) * G.nt + t0,
-               row1 = row0 + (two ? plane : 0);
-  const bool tok = t < G.nt;
-  const unsigned pitch = 4u * (unsigned)G.nt, lane = tok ? (threadIdx.x & 15) * 4 : 0,
-                 top = 4u * (unsigned)min(15, G.nt - 1 - t0);
+  // the row's samples of the tile; loads past the grid read inside it (values
+  // dropped)
+  const size_t row = (at.k * grid + yrow) * G.nt + pr.base;
+  const unsigned pitch = 4u * (unsigned)G.nt;
   double ss = 0.0;
   fft::turn_stage(D, L, [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
     unsigned off[R];
-    fft::offsets(pitch, lane, top, x0, step, G.nx, off);
+    fft::offsets(pitch, pr.lane, x0, step, G.nx, off);
     float2 pv[R];
     float2 yo[REC ? R : 1];
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      auto get = [&](const float* a) {
-        return float2{fft::at(a + row0, off[q]), fft::at(a + row1, off[q])};
-      };
       pv[q] = {0.0f, 0.0f};
-      if (pm) pv[q] = get(pm);
+      if (pm) pv[q] = pr.load(pm + row, off[q]);
       if constexpr (REC) {
         yo[q] = {0.0f, 0.0f};
-        if (!yc_first) yo[q] = get(yc);
+        if (!yc_first) yo[q] = pr.load(yc + row, off[q]);
       }
     }
-    reach_points<R>(W, D.n, p1 != p0, x0, step, v);
+    reach_points<R>(W, x0, step, v);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const bool in = tok && x0 < G.nx - q * step;
-      const float2 w = {v[q].x, two ? v[q].y : 0.0f};
-      if (!two) pv[q].y = 0.0f;
+      pv[q] = pr.pick(pv[q]);
+      if constexpr (REC) yo[q] = pr.pick(yo[q]);
+      const bool in = x0 < G.nx - q * step, in0 = in && pr.first, in1 = in && pr.both;
+      const float2 w = v[q];
       float2 d = {w.x - pv[q].x, w.y - pv[q].y};
       if constexpr (REC) {
-        if (in) {
+        if (in0) {
           float2 n = w;
           if (!yc_first)
             n = {__builtin_fmaf(yc_beta, yo[q].x, w.x) * yc_inv,
                  __builtin_fmaf(yc_beta, yo[q].y, w.y) * yc_inv};
-          fft::at(yc + row0, off[q]) = n.x;
-          if (two) fft::at(yc + row1, off[q]) = n.y;
+          pr.put(yc + row, off[q], n);
           const double e0 = (double)n.x - (double)pv[q].x,
-                       e1 = two ? (double)n.y - (double)pv[q].y : 0.0;
+                       e1 = in1 ? (double)n.y - (double)pv[q].y : 0.0;
           ss += e0 * e0 + e1 * e1;
         }
       } else {
         // (a product of floats is exact in FP64, so its sum rounds once)
-        const double e0 = in ? (double)d.x : 0.0, e1 = in ? (double)d.y : 0.0;
+        const double e0 = in0 ? (double)d.x : 0.0, e1 = in1 ? (double)d.y : 0.0;
         ss += __builtin_fma(e0, e0, e1 * e1);
       }
-      d.x = in ? rnd<RND>(d.x, sc, inv) : 0.0f;
-      d.y = in ? rnd<RND>(d.y, sc, inv) : 0.0f;
+      d.x = in0 ? rnd<RND>(d.x, sc, inv) : 0.0f;
+      d.y = in1 ? rnd<RND>(d.y, sc, inv) : 0.0f;
       v[q] = d;
     }
-    mark_points<R>(W, D.n, MR, r0 + mrow, r1 + mrow, r1 != r0, x0, step, v);
+    mark_points<R>(W, MR, rrow, x0, step, v);
   });
-  store_hits(W, D.n, MR, mrow, r0, r1, G.nx);
-  float2* ov = out + ((size_t)at.p * G.ny + at.iy) * G.nxp * G.lt + at.l0;
-  fft::dit_stages(D, L, fft::strided_out<true>(ov, 8u * G.lt, G.nxp));
+  store_hits(W, MR, rrow, G.nx);
+  float2* ov = out + ((size_t)at.k * G.ny + at.iy) * G.nxp * G.ht + at.c0;
+  fft::dit_stages(D, L, fft::strided_out<true>(ov, 8u * G.ht, G.nxp, col.ok));
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
@@ -578,62 +603,59 @@ __global__ __launch_bounds__(256) void spec_idle_sums(const float* __restrict__ 
   if (threadIdx.x == 0) partial[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
-// c-side output of H^T: the pair's two volumes (species after S^T, or pulses)
-// times the fluence (diagonal switching) or one
+// c-side output of H^T: a volume (species after S^T, or pulse) times the fluence
+// (diagonal switching) or one
 __global__ __launch_bounds__(kFftThreads) void spec_x_vox(const float2* __restrict__ in,
                                                           float* __restrict__ c,
                                                           const float* __restrict__ phi,
-                                                          int phi_mode, int nvol, Geo G, FftDim D,
-                                                          Marks M, const int* __restrict__ gate) {
+                                                          int phi_mode, Geo G, FftDim D, Marks M,
+                                                          const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
-  const RowAt at = row_at(G.ny, G.lz);
-  const int z = at.l0 + (threadIdx.x & 15);
-  const int v0 = 2 * at.p, v1 = v0 + 1;
+  const RowAt at = row_at(G.ny, G.hz);
+  const Pair pr = pair_at(at.c0, G.hz, 0, G.nz);
   const RowMarks W = row_marks(raw, D.n);
   // (planes of their own: volumes are pulses)
-  const size_t grid = (size_t)G.ny * G.nx, mrow = (size_t)at.iy * G.nx;
-  const size_t p0 = M.planes == 1 ? 0 : v0 * grid, p1 = M.planes > v1 ? v1 * grid : p0;
-  load_near(W, D.n, M, mrow, p0, p1, G.nx);
-  if (at.l0 == 0 && (M.planes > 1 || at.p == 0)) clear_row(M, mrow, p0, p1, G.nx);
-  const float2* i = in + ((size_t)at.p * G.nyp + at.iy) * G.nxp * G.lz + at.l0;
-  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.lz, G.nxp));
+  const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
+  const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
+  load_near(W, D.n, M, mrow, G.nx);
+  if (at.c0 == 0 && (M.planes > 1 || at.k == 0)) clear_row(M, mrow, G.nx);
+  const float2* i = in + ((size_t)at.k * G.nyp + at.iy) * G.nxp * G.hz + at.c0;
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.hz, G.nxp, column_at(at.c0, G.hz).lane));
   fft::middle_stages<1>(D, L);
-  const size_t vol = (size_t)G.ny * G.nx * G.nz;
-  const size_t row = (size_t)at.iy * G.nx * G.nz + at.l0;
-  const unsigned pitch = 4u * (unsigned)G.nz, lane = (threadIdx.x & 15) * 4;
+  const size_t row = yrow * G.nz + pr.base;
+  float* ck = c + at.k * grid * G.nz + row;
+  const unsigned pitch = 4u * (unsigned)G.nz;
   fft::last_stage<1>(D, L, [&](auto rc, int x0, int step, float2* v) {
     constexpr int R = decltype(rc)::value;
-    if (z >= G.nz) return;
-    const unsigned o = (unsigned)x0 * pitch + lane;
-    const float pz = phi_mode == 1 ? phi[z] : 1.0f;
+    if (!pr.first) return;
+    const unsigned o = (unsigned)x0 * pitch + pr.lane;
+    float2 pz = {1.0f, 1.0f};
+    if (phi_mode == 1) pz = pr.get(phi + pr.base, pr.lane);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const bool in = x0 < G.nx - q * step;
-      const float ph = phi_mode == 2 && in ? fft::at(phi + row, o + (unsigned)(q * step) * pitch) : pz;
-      v[q] = {ph * v[q].x, ph * v[q].y};
+      const unsigned oq = o + (unsigned)(q * step) * pitch;
+      float2 ph = pz;
+      if (phi_mode == 2 && x0 < G.nx - q * step) ph = pr.get(phi + row, oq);
+      v[q] = {ph.x * v[q].x, ph.y * v[q].y};
     }
-    reach_points<R>(W, D.n, p1 != p0, x0, step, v);
+    reach_points<R>(W, x0, step, v);
 #pragma unroll
     for (int q = 0; q < R; ++q)
-      if (x0 < G.nx - q * step) {
-        const unsigned oq = o + (unsigned)(q * step) * pitch;
-        fft::at(c + (size_t)v0 * vol + row, oq) = v[q].x;
-        if (v1 < nvol) fft::at(c + (size_t)v1 * vol + row, oq) = v[q].y;
-      }
+      if (x0 < G.nx - q * step) pr.put(ck, o + (unsigned)(q * step) * pitch, v[q]);
   });
 }
 
 // c[s][v] = sum_k S_v[k][s] b[k][v], per-voxel fluence
 __global__ __launch_bounds__(256) void spec_st(const float* __restrict__ b, float* __restrict__ c,
-                                               const float* __restrict__ phi, SwitchParams sw,
-                                               size_t vol, const int* __restrict__ gate) {
+                                               const float* __restrict__ phi, const float* phig,
+                                               SwitchParams sw, size_t vol, const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   const size_t v = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (v >= vol) return;
   const float ph = phi[v];
-  const float pg = sw.gamma == 0.0f ? 1.0f : powf(ph, sw.gamma);
+  const float pg = !phig ? 1.0f : phig == phi ? ph : phig[v];
   float acc[kMaxSpecies];
 #pragma unroll
   for (int s = 0; s < kMaxSpecies; ++s) acc[s] = 0.0f;
@@ -641,9 +663,7 @@ __global__ __launch_bounds__(256) void spec_st(const float* __restrict__ b, floa
     const float bv = b[(size_t)k * vol + v];
 #pragma unroll
     for (int s = 0; s < kMaxSpecies; ++s)
-      if (s < sw.ns)
-        acc[s] = __builtin_fmaf(
-            ph * __builtin_fmaf(sw.b[s], expf(-(float)k * pg * sw.inv_tau[s]), sw.a[s]), bv, acc[s]);
+      if (s < sw.ns) acc[s] = __builtin_fmaf(switch_coef(sw, ph, pg, k, s), bv, acc[s]);
   }
 #pragma unroll
   for (int s = 0; s < kMaxSpecies; ++s)
@@ -651,31 +671,28 @@ __global__ __launch_bounds__(256) void spec_st(const float* __restrict__ b, floa
 }
 
 // ------------------------------------------------------------- y transform
-// Block: 16 columns of kappa_x of pair p; points of rows 0 .. n_in - 1 (the
-// others are zero), outputs of rows 0 .. n_out - 1.  in and out may be one
-// buffer: every point is read before the first barrier.
+// Block: 16 columns of image k (of all kappa_x: a row's columns lie in one line);
+// points of rows 0 .. n_in - 1 (the others are zero), outputs of rows 0 ..
+// n_out - 1.  in and out may be one buffer: every point is read before the first
+// barrier.
 template <int SIGN>
-__global__ __launch_bounds__(kFftThreads) void spec_y(const float2* in, float2* out, int nxp,
-                                                      int l, int rows_in, int rows_out, int n_in,
+__global__ __launch_bounds__(kFftThreads) void spec_y(const float2* in, float2* out, unsigned cols,
+                                                      int rows_in, int rows_out, int n_in,
                                                       int n_out, FftDim D,
                                                       const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
-  int b = (int)blockIdx.x;
-  const int tiles = l >> 4;
-  const int l0 = (b % tiles) * 16;
-  b /= tiles;
-  const int kx = b % nxp, p = b / nxp;
-  const size_t step = (size_t)nxp * l;
-  const unsigned pitch = 8u * (unsigned)step;
-  const size_t col = (size_t)kx * l + l0;
-  const float2* i = in + (size_t)p * rows_in * step + col;
+  const unsigned tiles = (cols + kFftLanes - 1) / kFftLanes;
+  const unsigned k = blockIdx.x / tiles, c0 = (blockIdx.x - k * tiles) * kFftLanes;
+  const unsigned pitch = 8u * cols;
+  const Column col = column_at(c0, cols);
+  const float2* i = in + (size_t)k * rows_in * cols + c0;
   // (the grid's side is the shorter one)
-  fft::first_stage<SIGN>(D, L, fft::strided<(SIGN > 0)>(i, pitch, n_in));
+  fft::first_stage<SIGN>(D, L, fft::strided<(SIGN > 0)>(i, pitch, n_in, col.lane));
   fft::middle_stages<SIGN>(D, L);
-  float2* o = out + (size_t)p * rows_out * step + col;
-  fft::last_stage<SIGN>(D, L, fft::strided_out<(SIGN < 0)>(o, pitch, n_out));
+  float2* o = out + (size_t)k * rows_out * cols + c0;
+  fft::last_stage<SIGN>(D, L, fft::strided_out<(SIGN < 0)>(o, pitch, n_out, col.ok));
 }
 
 // ------------------------------------------------- products per frequency
@@ -700,60 +717,72 @@ __device__ __forceinline__ Freq freq_at(int f, int nyp, int nxp) {
   return Freq{(size_t)ky * nxp + kx, (size_t)my * nxp + mx, ky == my && kx == mx};
 }
 
-// Values of one column at four consecutive contracted indices, separated from
-// the pair's image: pulse 2p is (Z(kappa) + conj Z(-kappa)) / 2 and pulse 2p +
-// 1 is (Z(kappa) - conj Z(-kappa)) / 2i; the halves are in the table's scale.
-// self: the lane's own part (real for even columns, imaginary for odd ones);
-// the part that meets the imaginary table is the neighbouring lane's.
-__device__ __forceinline__ void unpair(const float4* zp, const float4* zm, int h, int c,
-                                       float (&self)[4]) {
-  const float4 a0 = zp[0], a1 = zp[1], b0 = zm[0], b1 = zm[1];
-  const float zr[4] = {a0.x, a0.z, a1.x, a1.z}, zi[4] = {a0.y, a0.w, a1.y, a1.w};
-  const float wr[4] = {b0.x, b0.z, b1.x, b1.z}, wi[4] = {b0.y, b0.w, b1.y, b1.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float re = h ? zi[i] + wi[i] : zr[i] + wr[i];
-    const float im = h ? wr[i] - zr[i] : zi[i] - wi[i];
-    self[i] = c ? im : re;
-  }
-}
-
-__device__ __forceinline__ float quad_mirror(float v) {  // lane 4i + j <- 4i + 3 - j
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x1B, 0xf, 0xf, true));
-}
 __device__ __forceinline__ float quad_swap(float v) {    // lane j <- j ^ 1
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
 }
 
-// Packs the products of a quad of lanes (pulse 2p: re, im, pulse 2p + 1: re,
-// im; four consecutive rows each) into the pair's image and stores it at
-// kappa (lanes 0, 1) and -kappa (lanes 2, 3): Z(kappa) = Y0 + i Y1, Z(-kappa)
-// = conj Y0 + i conj Y1.  Each lane stores two rows, 16 bytes.
-__device__ __forceinline__ void pair_store(f32x4 v, float2* zp, float2* zm, int c, int h, bool ok,
-                                           bool self) {
-  // lane 0: re - other.im (re of kappa); 1: im + other.re (im of kappa);
-  // lane 2: re1 - im0 (im of -kappa); 3: im1 + re0 (re of -kappa)
-  float own[4], oth[4];
+// Values of one pulse at four consecutive contracted indices of two 16-wide
+// tiles A and B, separated from the images of their pairs: index 2j is
+// (Z(kappa) + conj Z(-kappa)) / 2 and index 2j + 1 is (Z(kappa) - conj
+// Z(-kappa)) / 2i; the halves are in the table's scale.  A lane's result is its
+// own part (real for even lanes, imaginary for odd ones); the part that meets
+// the imaginary table is the neighbouring lane's.  The even lane reads tile A,
+// the odd one tile B (zp, zm: its own), and each hands the other its part: a
+// load covers a whole line of both tiles, and no value is read twice.
+__device__ __forceinline__ void unpair(const float2* zp, const float2* zm, int c, float (&A)[4],
+                                       float (&B)[4]) {
+  const float4 a = *(const float4*)zp, b = *(const float4*)zm;
+  const float re[4] = {a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w};
+  const float im[4] = {a.y - b.y, b.x - a.x, a.w - b.w, b.z - a.z};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float m = quad_mirror(v[i]);
-    own[i] = c ? v[i] + m : v[i] - m;
-    oth[i] = quad_swap(own[i]);
+    const float other = quad_swap(c ? re[i] : im[i]);
+    A[i] = c ? other : re[i];
+    B[i] = c ? im[i] : other;
   }
-  // kappa: lane 0 has re, lane 1 im; -kappa: lane 3 has re, lane 2 im
-  const bool re = (c ^ h) == 0;
-  float4 o;
-  if (re) o = {own[0], oth[0], own[1], oth[1]};
-  else o = {oth[2], own[2], oth[3], own[3]};
-  float2* z = h ? zm : zp;
-  if (ok && !(h && self)) *(float4*)(z + (re ? 0 : 2)) = o;
 }
 
+// The first of the pairs of sample tiles that a product takes: pairs are lines,
+// and a position of an odd number of tiles starts inside one every other time
+// (256 x 256 x 96 with 13 tiles: H's product 1390 us without this, 1220 with it).
+__device__ __forceinline__ int first_tile(int ht, size_t at) { return (ht & 8) && (at & 1) ? -1 : 0; }
+
+// Packs a pulse's products (an even lane's real, an odd one's imaginary parts;
+// four consecutive rows Y0 .. Y3) into its pairs' images: Z(kappa) = Y0 + i Y1 on
+// even lanes, Z(-kappa) = conj Y0 + i conj Y1 on odd ones.
+__device__ __forceinline__ f32x4 pair_pack(f32x4 v, int c) {
+  float m[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m[i] = quad_swap(v[i]);
+  const float s0 = v[1] + m[0], s1 = v[3] + m[2];
+  const float d0 = v[0] - m[1], d1 = v[2] - m[3];
+  return f32x4{c ? s0 : d0, c ? -d0 : s0, c ? s1 : d1, c ? -d1 : s1};
+}
+// and stores tiles A and B: the even lane tile A's and the odd one tile B's
+// values at kappa and -kappa (op: its own tile's at kappa, neg further at
+// ok: the lane has a pulse and its tile is there
+__device__ __forceinline__ void pair_store(f32x4 va, f32x4 vb, float2* op, ptrdiff_t neg, int c, bool ok,
+                                           bool self) {
+  const f32x4 a = pair_pack(va, c), b = pair_pack(vb, c);
+  f32x4 p, m;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float r = quad_swap(c ? a[i] : b[i]);
+    p[i] = c ? r : a[i];
+    m[i] = c ? b[i] : r;
+  }
+  if (ok) {
+    *(f32x4*)op = p;
+    if (!self) *(f32x4*)(op + neg) = m;
+  }
+}
+
+// (mask, [t tiles], the tile's 16-depth blocks, is an argument of its own: known
+// not to alias, it comes by scalar loads, which wait for no store)
 struct GemmArgs {
   const float* tab;       // [nf][nblk][real, imaginary][64][4]
-  const unsigned* mask;   // [t tiles] the tile's 16-depth blocks
   int nblk, ntt;          // blocks of a frequency, t tiles
-  int nyp, nxp, lz, lt, np, nk;
+  int nyp, nxp, lz, lt, nk;
   const float2* in;
   float2* out;
   // H before a residual: r's marks (at, bad), cleared
@@ -769,7 +798,8 @@ struct GemmArgs {
 // depths sits in registers, the table's 16 x 16 blocks stream past it (the
 // block's waves share them through the caches).
 template <int ZC>
-__global__ __launch_bounds__(512) void spec_gemm_fwd(GemmArgs A) {
+__global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_fwd(GemmArgs A,
+                                                                          const unsigned* __restrict__ mask) {
   if (A.gate && *A.gate) return;  // a device stop test has ended the solve
   const int f = (int)blockIdx.x;
   // (frequencies x threads, NX NY / 2 x at least 8 a pulse, outnumber the positions of all planes)
@@ -779,128 +809,142 @@ __global__ __launch_bounds__(512) void spec_gemm_fwd(GemmArgs A) {
   }
   const Freq F = freq_at(f, A.nyp, A.nxp);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int g = lane >> 4, n = lane & 15, c = n & 1, h = (n >> 1) & 1;
-  const int p = wave * 4 + (n >> 2);
-  const bool ok = p < A.np;
-  const size_t img = (size_t)A.nyp * A.nxp;
-  const float2* zp = A.in + ((size_t)(ok ? p : 0) * img + F.at) * A.lz;
-  const float2* zm = A.in + ((size_t)(ok ? p : 0) * img + F.neg) * A.lz;
+  const int g = lane >> 4, n = lane & 15, c = n & 1;
+  const int k = wave * 8 + (n >> 1);
+  const bool ok = k < A.nk;
+  const size_t img = (size_t)(ok ? k : 0) * A.nyp * A.nxp;
+  const int hz = A.lz / 2, ht = A.lt / 2;
+  const float2* zp = A.in + (img + F.at) * hz + 2 * g;
+  const float2* zm = A.in + (img + F.neg) * hz + 2 * g;
   float bs[ZC][4];
   const float sg = c ? 1.0f : -1.0f;
 #pragma unroll
-  for (int zc = 0; zc < ZC; ++zc) {
+  for (int zc = 0; zc < ZC; zc += 2) {
     if (zc * 16 < A.lz) {
-      const int z = zc * 16 + 4 * g;
-      unpair((const float4*)(zp + z), (const float4*)(zm + z), h, c, bs[zc]);
+      // (no second tile: the first one's again, which no block meets)
+      const int own = zc * 8 + ((zc + 1) * 16 < A.lz ? 8 * c : 0);
+      unpair(zp + own, zm + own, c, bs[zc], bs[zc + 1]);
     } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bs[zc][i] = 0.0f;
+      for (int i = 0; i < 4; ++i) bs[zc][i] = bs[zc + 1][i] = 0.0f;
     }
   }
-  float2* op = A.out + ((size_t)(ok ? p : 0) * img + F.at) * A.lt + 4 * g;
-  float2* om = A.out + ((size_t)(ok ? p : 0) * img + F.neg) * A.lt + 4 * g;
-  const float4* tab = (const float4*)A.tab + (size_t)f * A.nblk * 128 + lane;
-  float4 ar = tab[0], ai = tab[64];  // (the table ends with a spare block)
-  for (int tt = 0; tt < A.ntt; ++tt) {
-    const unsigned m = A.mask[tt];
-    f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = a0;
+  // (a uniform base and a lane's offset, and the way from kappa to -kappa: registers)
+  float2* op = A.out + (img + F.at) * ht + 2 * g + 8 * c;
+  const ptrdiff_t neg = ((ptrdiff_t)F.neg - (ptrdiff_t)F.at) * ht;
+  const float4* tab = (const float4*)A.tab + (size_t)f * A.nblk * 128;
+  float4 ar = tab[lane], ai = tab[64 + lane];  // (the table ends with a spare block)
+  for (int tt = first_tile(ht, F.at); tt < A.ntt; tt += 2) {
+    f32x4 y[2];
 #pragma unroll
-    for (int zc = 0; zc < ZC; ++zc)
-      if (m >> zc & 1u) {
-        const float r[4] = {ar.x, ar.y, ar.z, ar.w}, q[4] = {ai.x, ai.y, ai.z, ai.w};
-        tab += 128;
-        ar = tab[0];
-        ai = tab[64];
+    for (int u = 0; u < 2; ++u) {
+      const unsigned m = tt + u >= 0 && tt + u < A.ntt ? mask[tt + u] : 0u;
+      f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = a0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(r[i], bs[zc][i], a0, 0, 0, 0);
-          a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(q[i], sg * quad_swap(bs[zc][i]), a1, 0, 0, 0);
+      for (int zc = 0; zc < ZC; ++zc)
+        if (m >> zc & 1u) {
+          const float r[4] = {ar.x, ar.y, ar.z, ar.w}, q[4] = {ai.x, ai.y, ai.z, ai.w};
+          tab += 128;
+          ar = tab[lane];
+          ai = tab[64 + lane];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(r[i], bs[zc][i], a0, 0, 0, 0);
+            a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(q[i], sg * quad_swap(bs[zc][i]), a1, 0, 0, 0);
+          }
         }
-      }
-    a0 += a1;
-    pair_store(a0, op + tt * 16, om + tt * 16, c, h, ok, F.self);
+      y[u] = a0 + a1;
+    }
+    pair_store(y[0], y[1], op + tt * 8, neg, c, ok && tt + c >= 0 && tt + c < A.ntt, F.self);
   }
 }
 
 // G = conj(T)^T R, the accumulators of all depths in registers; ST: S^T over
-// the pulses in LDS, pairs of species written instead of pairs of pulses.
+// the pulses in LDS, species written instead of pulses.
 template <int ZC, bool ST>
-__global__ __launch_bounds__(512) void spec_gemm_adj(GemmArgs A) {
+__global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_adj(GemmArgs A,
+                                                                                        const unsigned* __restrict__ mask) {
   if (A.gate && *A.gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const int f = (int)blockIdx.x;
   const Freq F = freq_at(f, A.nyp, A.nxp);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int g = lane >> 4, n = lane & 15, c = n & 1, h = (n >> 1) & 1;
-  const int p = wave * 4 + (n >> 2);
-  const bool ok = p < A.np;
-  const size_t img = (size_t)A.nyp * A.nxp;
-  const float2* zp = A.in + ((size_t)(ok ? p : 0) * img + F.at) * A.lt + 4 * g;
-  const float2* zm = A.in + ((size_t)(ok ? p : 0) * img + F.neg) * A.lt + 4 * g;
+  const int g = lane >> 4, n = lane & 15, c = n & 1;
+  const int k = wave * 8 + (n >> 1);
+  const bool ok = k < A.nk;
+  const size_t img = (size_t)(ok ? k : 0) * A.nyp * A.nxp;
+  const int hz = A.lz / 2, ht = A.lt / 2;
+  const float2* zp = A.in + (img + F.at) * ht + 2 * g;
+  const ptrdiff_t away = ((ptrdiff_t)F.neg - (ptrdiff_t)F.at) * ht;
   const float sg = c ? -1.0f : 1.0f;
   f32x4 acc[ZC];
 #pragma unroll
   for (int zc = 0; zc < ZC; ++zc) acc[zc] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  const float4* tab = (const float4*)A.tab + (size_t)f * A.nblk * 128 + lane;
-  float4 ar = tab[0], ai = tab[64];
-  for (int tt = 0; tt < A.ntt; ++tt) {
-    const unsigned m = A.mask[tt];
-    if (m == 0) continue;
-    float rs[4], ro[4];
-    unpair((const float4*)(zp + tt * 16), (const float4*)(zm + tt * 16), h, c, rs);
-    // conj(T): real columns meet +imaginary parts, imaginary ones -real parts
+  const float4* tab = (const float4*)A.tab + (size_t)f * A.nblk * 128;
+  float4 ar = tab[lane], ai = tab[64 + lane];
+  for (int tt = first_tile(ht, F.at); tt < A.ntt; tt += 2) {
+    const unsigned ms[2] = {tt >= 0 ? mask[tt] : 0u, tt + 1 < A.ntt ? mask[tt + 1] : 0u};
+    if ((ms[0] | ms[1]) == 0) continue;
+    float rs[2][4];
+    // (one tile alone is read twice)
+    const int own = 8 * min(max(tt + c, 0), A.ntt - 1);
+    unpair(zp + own, zp + own + away, c, rs[0], rs[1]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ro[i] = sg * quad_swap(rs[i]);
+    for (int u = 0; u < 2; ++u) {
+      // conj(T): real columns meet +imaginary parts, imaginary ones -real parts
+      float ro[4];
 #pragma unroll
-    for (int zc = 0; zc < ZC; ++zc)
-      if (m >> zc & 1u) {
-        const float r[4] = {ar.x, ar.y, ar.z, ar.w}, q[4] = {ai.x, ai.y, ai.z, ai.w};
-        tab += 128;
-        ar = tab[0];
-        ai = tab[64];
+      for (int i = 0; i < 4; ++i) ro[i] = sg * quad_swap(rs[u][i]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[zc] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[i], rs[i], acc[zc], 0, 0, 0);
-          acc[zc] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[i], ro[i], acc[zc], 0, 0, 0);
+      for (int zc = 0; zc < ZC; ++zc)
+        if (ms[u] >> zc & 1u) {
+          const float r[4] = {ar.x, ar.y, ar.z, ar.w}, q[4] = {ai.x, ai.y, ai.z, ai.w};
+          tab += 128;
+          ar = tab[lane];
+          ai = tab[64 + lane];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            acc[zc] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[i], rs[u][i], acc[zc], 0, 0, 0);
+            acc[zc] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[i], ro[i], acc[zc], 0, 0, 0);
+          }
         }
-      }
+    }
   }
   if constexpr (!ST) {
-    float2* op = A.out + ((size_t)(ok ? p : 0) * img + F.at) * A.lz + 4 * g;
-    float2* om = A.out + ((size_t)(ok ? p : 0) * img + F.neg) * A.lz + 4 * g;
+    float2* op = A.out + (img + F.at) * hz + 2 * g + 8 * c;
+    const ptrdiff_t neg = ((ptrdiff_t)F.neg - (ptrdiff_t)F.at) * hz;
 #pragma unroll
-    for (int zc = 0; zc < ZC; ++zc)
-      if (zc * 16 < A.lz) pair_store(acc[zc], op + zc * 16, om + zc * 16, c, h, ok, F.self);
+    for (int zc = 0; zc < ZC; zc += 2)
+      if (zc * 16 < A.lz)
+        pair_store(acc[zc], acc[zc + 1], op + zc * 8, neg, c, ok && (zc + c) * 16 < A.lz, F.self);
   } else {
-    float* gb = (float*)raw;  // [2 pairs][lz][2]
-    const int q = 2 * p + h;
+    float* gb = (float*)raw;  // [nk][lz][2]
     if (ok) {
 #pragma unroll
       for (int zc = 0; zc < ZC; ++zc)
         if (zc * 16 < A.lz) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) gb[((size_t)q * A.lz + zc * 16 + 4 * g + j) * 2 + c] = acc[zc][j];
+          for (int j = 0; j < 4; ++j) gb[((size_t)k * A.lz + zc * 16 + 4 * g + j) * 2 + c] = acc[zc][j];
         }
     }
     __syncthreads();
-    const float2* gv = (const float2*)raw;
-    const int nps = (A.ns + 1) / 2;
-    for (int i = (int)threadIdx.x; i < nps * A.lz; i += (int)blockDim.x) {
-      const int ps = i / A.lz, z = i - ps * A.lz;
+    const float4* gv = (const float4*)raw;
+    for (int i = (int)threadIdx.x; i < A.ns * hz; i += (int)blockDim.x) {
+      const int s = i / hz, j = i - s * hz;
       float2 s0 = {0.0f, 0.0f}, s1 = {0.0f, 0.0f};
-      if (z < A.nz) {
-        const bool two = 2 * ps + 1 < A.ns;
-        const float* w = A.stab_t + (size_t)(2 * ps) * A.nz + z;
-        for (int k = 0; k < A.nk; ++k, w += (size_t)A.ns * A.nz) {
-          const float2 v = gv[(size_t)k * A.lz + z];
-          const float w0 = w[0], w1 = two ? w[A.nz] : 0.0f;
-          s0 = fft::cfma(w0, v, s0);
-          s1 = fft::cfma(w1, v, s1);
+      if (2 * j < A.nz) {
+        const int next = 2 * j + 1 < A.nz ? 1 : 0;
+        const float* w = A.stab_t + (size_t)s * A.nz + 2 * j;
+        for (int q = 0; q < A.nk; ++q, w += (size_t)A.ns * A.nz) {
+          const float4 v = gv[(size_t)q * hz + j];
+          s0 = fft::cfma(w[0], float2{v.x, v.y}, s0);
+          s1 = fft::cfma(w[next], float2{v.z, v.w}, s1);
         }
+        if (!next) s1 = {0.0f, 0.0f};
       }
-      float2* o = A.out + (size_t)ps * img * A.lz + z;
-      o[F.at * A.lz] = float2{s0.x - s1.y, s0.y + s1.x};
-      if (!F.self) o[F.neg * A.lz] = float2{s0.x + s1.y, s1.x - s0.y};
+      float2* o = A.out + (size_t)s * A.nyp * A.nxp * hz + j;
+      o[F.at * hz] = float2{s0.x - s1.y, s0.y + s1.x};
+      if (!F.self) o[F.neg * hz] = float2{s0.x + s1.y, s1.x - s0.y};
     }
   }
 }
@@ -1075,13 +1119,11 @@ Geo geo_of(const psoam_plan* P) {
   G.nxp = Q.nx;
   G.nz = P->g.nz;
   G.nt = P->g.nt;
-  G.lz = Q.lz;
-  G.lt = Q.lt;
+  G.hz = Q.lz / 2;
+  G.ht = Q.lt / 2;
   G.tlo = Q.tlo;
   G.nk = P->g.n_pulses;
-  G.np = Q.np;
   G.r = P->R;
-  G.f = P->F;
   return G;
 }
 
@@ -1129,14 +1171,12 @@ GemmArgs gemm_args(const psoam_plan* P, bool adj) {
   const SpecPlan& Q = *P->spec;
   GemmArgs A;
   A.tab = adj ? Q.d_ta : Q.d_tf;
-  A.mask = Q.d_mask;
   A.nblk = Q.nblk;
   A.ntt = Q.lt / 16;
   A.nyp = Q.ny;
   A.nxp = Q.nx;
   A.lz = Q.lz;
   A.lt = Q.lt;
-  A.np = Q.np;
   A.nk = P->g.n_pulses;
   A.in = (const float2*)(adj ? Q.d_y : Q.d_x);
   A.out = (float2*)(adj ? Q.d_g : Q.d_y);
@@ -1152,10 +1192,13 @@ GemmArgs gemm_args(const psoam_plan* P, bool adj) {
 // S^T inside the product: per-depth fluence, species mixed
 bool st_in_gemm(const psoam_plan* P) { return P->d_stab_t && !P->sw.diag; }
 
-// c-side planes (pairs) of H^T
-int adj_pairs(const psoam_plan* P) {
-  return st_in_gemm(P) ? (P->sw.ns + 1) / 2 : (P->g.n_pulses + 1) / 2;
+// phi^gamma of each voxel (see switch_coef)
+const float* rates(const psoam_plan* P) {
+  return P->sw.gamma == 0.0f ? nullptr : P->sw.gamma == 1.0f ? P->d_phi : P->spec->d_rate;
 }
+
+// c-side images of H^T
+int adj_images(const psoam_plan* P) { return st_in_gemm(P) ? P->sw.ns : P->g.n_pulses; }
 
 #define SPEC_HIP(call)                 \
   do {                                 \
@@ -1163,11 +1206,20 @@ int adj_pairs(const psoam_plan* P) {
     if (_e != hipSuccess) return _e;   \
   } while (0)
 
+// a transform along y of `images` images of h columns a position
+template <class K>
+hipError_t y_pass(K kern, int images, int h, const void* in, void* out, const Geo& G, int rows_in,
+                  int rows_out, int n_in, int n_out, const FftDim& Y, hipStream_t s) {
+  const unsigned cols = (unsigned)G.nxp * (unsigned)h;
+  return go(kern, (size_t)images * ((cols + kFftLanes - 1) / kFftLanes), kFftThreads, fft_lds(G.nyp), s,
+            (const float2*)in, (float2*)out, cols, rows_in, rows_out, n_in, n_out, Y, gate_now());
+}
+
 }  // namespace
 
 size_t spec_partials(const psoam_plan* P) {
   const SpecPlan& Q = *P->spec;
-  return (size_t)Q.np * P->g.ny * (Q.lt / 16) + kIdleSums;
+  return (size_t)P->g.n_pulses * P->g.ny * col_tiles(Q.lt / 2) + kIdleSums;
 }
 
 hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s) {
@@ -1176,9 +1228,9 @@ hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s) {
   const FftDim X = dim_of(Q, 1), Y = dim_of(Q, 0);
   ++Q.call_b;
   const Marks M = marks_b(P);
-  const size_t nb = (size_t)Q.np * G.ny * (G.lz / 16);
+  const size_t nb = (size_t)pulses_near(G.nk) * G.ny * col_tiles(G.hz);
   auto x = [&](auto kern) {
-    return go(kern, nb, kFftThreads, row_lds(G.nxp), s, c, P->d_phi, P->d_stab_t, P->d_f16, P->sw,
+    return go(kern, nb, kFftThreads, row_lds(G.nxp), s, c, P->d_phi, rates(P), P->d_stab_t, P->d_f16, P->sw,
               (float2*)Q.d_x, G, X, M, gate_now());
   };
   const int src = P->sw.diag ? kSrcDiag : P->d_stab_t ? kSrcDepth : kSrcVoxel;
@@ -1193,8 +1245,7 @@ hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s) {
   }
 #undef SPEC_SW
   SPEC_HIP(go(spec_reach, (size_t)M.planes * G.ny, 256, (size_t)G.nx, s, M, G.ny, G.nx, G.r, gate_now()));
-  return go(spec_y<-1>, (size_t)Q.np * G.nxp * (G.lz / 16), kFftThreads, fft_lds(G.nyp), s,
-            (const float2*)Q.d_x, (float2*)Q.d_x, G.nxp, G.lz, G.nyp, G.nyp, G.ny, G.nyp, Y, gate_now());
+  return y_pass(spec_y<-1>, G.nk, G.hz, Q.d_x, Q.d_x, G, G.nyp, G.nyp, G.ny, G.nyp, Y, s);
 }
 
 // The reach of r's marks, beside the pass that made r: what follows only reads
@@ -1211,7 +1262,7 @@ hipError_t spec_pack(const psoam_plan* P, const float* y, hipStream_t s) {
   const FftDim X = dim_of(Q, 1);
   ++Q.call_r;
   const Marks M = marks_r(P);
-  const size_t nb = (size_t)Q.np * G.ny * (G.lt / 16);
+  const size_t nb = (size_t)G.nk * G.ny * col_tiles(G.ht);
   auto x = [&](auto kern) {
     return go(kern, nb, kFftThreads, row_lds(G.nxp), s, y, P->d_f16, (float2*)Q.d_r, G, X, M,
               gate_now());
@@ -1230,7 +1281,7 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
   SpecPlan& Q = *P->spec;
   const Geo G = geo_of(P);
   const FftDim X = dim_of(Q, 1), Y = dim_of(Q, 0);
-  const int waves = (Q.np + 3) / 4;
+  const int waves = (G.nk + 7) / 8;  // eight pulses a wave
   const Marks MB = marks_b(P);
   if (mode != 2) {
     GemmArgs A = gemm_args(P, false);
@@ -1239,15 +1290,13 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
       A.n_clear = 2 * (size_t)MB.planes * G.ny * G.nx;
     }
     const int zc = Q.lz / 16;
-    if (zc <= 4) SPEC_HIP(go(spec_gemm_fwd<4>, (size_t)Q.nf, waves * 64, 0, s, A));
-    else if (zc <= 8) SPEC_HIP(go(spec_gemm_fwd<8>, (size_t)Q.nf, waves * 64, 0, s, A));
-    else SPEC_HIP(go(spec_gemm_fwd<16>, (size_t)Q.nf, waves * 64, 0, s, A));
-    SPEC_HIP(go(spec_y<1>, (size_t)Q.np * G.nxp * (G.lt / 16), kFftThreads, fft_lds(G.nyp), s,
-                (const float2*)Q.d_y, (float2*)Q.d_y, G.nxp, G.lt, G.nyp, G.nyp, G.nyp, G.ny, Y,
-                gate_now()));
-    const size_t nb = (size_t)Q.np * G.ny * (G.lt / 16);
+    if (zc <= 4) SPEC_HIP(go(spec_gemm_fwd<4>, (size_t)Q.nf, waves * 64, 0, s, A, Q.d_mask));
+    else if (zc <= 8) SPEC_HIP(go(spec_gemm_fwd<8>, (size_t)Q.nf, waves * 64, 0, s, A, Q.d_mask));
+    else SPEC_HIP(go(spec_gemm_fwd<16>, (size_t)Q.nf, waves * 64, 0, s, A, Q.d_mask));
+    SPEC_HIP(y_pass(spec_y<1>, G.nk, G.ht, Q.d_y, Q.d_y, G, G.nyp, G.nyp, G.nyp, G.ny, Y, s));
+    const size_t nb = (size_t)G.nk * G.ny * col_tiles(G.ht);
     // samples [tlo, thi) are transformed
-    const int thi = std::min(G.nt, G.tlo + G.lt);
+    const int thi = std::min(G.nt, G.tlo + Q.lt);
     const size_t rows = (size_t)G.nk * G.ny * G.nx;
     if (mode == 0 && thi - G.tlo < G.nt) {
       if (G.nt % 4 == 0 && thi % 4 == 0)  // (y is 16-byte aligned)
@@ -1279,36 +1328,31 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
     return reach_r(P, s);
   }
   const Marks MR = marks_r(P);
-  SPEC_HIP(go(spec_y<-1>, (size_t)Q.np * G.nxp * (G.lt / 16), kFftThreads, fft_lds(G.nyp), s,
-              (const float2*)Q.d_r, (float2*)Q.d_y, G.nxp, G.lt, G.ny, G.nyp, G.ny, G.nyp, Y,
-              gate_now()));
+  SPEC_HIP(y_pass(spec_y<-1>, G.nk, G.ht, Q.d_r, Q.d_y, G, G.ny, G.nyp, G.ny, G.nyp, Y, s));
   const GemmArgs A = gemm_args(P, true);
   const int zc = Q.lz / 16;
   const bool st = st_in_gemm(P);
-  const size_t lds = st ? (size_t)2 * Q.np * Q.lz * sizeof(float2) : 0;
+  const size_t lds = st ? (size_t)G.nk * Q.lz * sizeof(float2) : 0;
   if (st) {
-    if (zc <= 4) SPEC_HIP(go(spec_gemm_adj<4, true>, (size_t)Q.nf, waves * 64, lds, s, A));
-    else if (zc <= 8) SPEC_HIP(go(spec_gemm_adj<8, true>, (size_t)Q.nf, waves * 64, lds, s, A));
-    else SPEC_HIP(go(spec_gemm_adj<16, true>, (size_t)Q.nf, waves * 64, lds, s, A));
+    if (zc <= 4) SPEC_HIP(go(spec_gemm_adj<4, true>, (size_t)Q.nf, waves * 64, lds, s, A, Q.d_mask));
+    else if (zc <= 8) SPEC_HIP(go(spec_gemm_adj<8, true>, (size_t)Q.nf, waves * 64, lds, s, A, Q.d_mask));
+    else SPEC_HIP(go(spec_gemm_adj<16, true>, (size_t)Q.nf, waves * 64, lds, s, A, Q.d_mask));
   } else {
-    if (zc <= 4) SPEC_HIP(go(spec_gemm_adj<4, false>, (size_t)Q.nf, waves * 64, lds, s, A));
-    else if (zc <= 8) SPEC_HIP(go(spec_gemm_adj<8, false>, (size_t)Q.nf, waves * 64, lds, s, A));
-    else SPEC_HIP(go(spec_gemm_adj<16, false>, (size_t)Q.nf, waves * 64, lds, s, A));
+    if (zc <= 4) SPEC_HIP(go(spec_gemm_adj<4, false>, (size_t)Q.nf, waves * 64, lds, s, A, Q.d_mask));
+    else if (zc <= 8) SPEC_HIP(go(spec_gemm_adj<8, false>, (size_t)Q.nf, waves * 64, lds, s, A, Q.d_mask));
+    else SPEC_HIP(go(spec_gemm_adj<16, false>, (size_t)Q.nf, waves * 64, lds, s, A, Q.d_mask));
   }
-  const int na = adj_pairs(P);
-  SPEC_HIP(go(spec_y<1>, (size_t)na * G.nxp * (G.lz / 16), kFftThreads, fft_lds(G.nyp), s,
-              (const float2*)Q.d_g, (float2*)Q.d_g, G.nxp, G.lz, G.nyp, G.nyp, G.nyp, G.ny, Y,
-              gate_now()));
-  const size_t nb = (size_t)na * G.ny * (G.lz / 16);
+  const int na = adj_images(P);
+  SPEC_HIP(y_pass(spec_y<1>, na, G.hz, Q.d_g, Q.d_g, G, G.nyp, G.nyp, G.nyp, G.ny, Y, s));
+  const size_t nb = (size_t)na * G.ny * col_tiles(G.hz);
   const bool mix = !st && !P->sw.diag;  // per-voxel fluence: S^T after the pulses are back
   float* dst = mix ? (float*)Q.d_y : out;
-  const int nvol = st ? P->sw.ns : G.nk;
   const int phi_mode = P->sw.diag ? (P->sw.per_voxel ? 2 : 1) : 0;
   SPEC_HIP(go(spec_x_vox, nb, kFftThreads, row_lds(G.nxp), s, (const float2*)Q.d_g, dst, P->d_phi,
-              phi_mode, nvol, G, X, MR, gate_now()));
+              phi_mode, G, X, MR, gate_now()));
   if (mix) {
     const size_t vol = P->v_elems();
-    SPEC_HIP(go(spec_st, (vol + 255) / 256, 256, 0, s, (const float*)Q.d_y, out, P->d_phi, P->sw, vol,
+    SPEC_HIP(go(spec_st, (vol + 255) / 256, 256, 0, s, (const float*)Q.d_y, out, P->d_phi, rates(P), P->sw, vol,
                 gate_now()));
   }
   return hipSuccess;
@@ -1317,7 +1361,7 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
 void spec_free(psoam_plan* P) {
   if (!P->spec) return;
   SpecPlan& Q = *P->spec;
-  for (void* b : {Q.d_x, Q.d_y, Q.d_r, Q.d_g, (void*)Q.d_tf, (void*)Q.d_ta, (void*)Q.d_mask, Q.d_twx,
+  for (void* b : {Q.d_x, Q.d_y, Q.d_r, Q.d_g, (void*)Q.d_tf, (void*)Q.d_ta, (void*)Q.d_mask, (void*)Q.d_rate, Q.d_twx,
                   Q.d_twy, (void*)Q.d_marks})
     if (b) (void)hipFree(b);
   delete P->spec;
@@ -1331,6 +1375,7 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   if (!choose_length(g.nx + P->R, X) || !choose_length(g.ny + P->R, Y)) return false;
   const int lz = (g.nz + 15) / 16 * 16;
   if (lz > 256) return false;  // the product holds every depth in registers
+  if (g.nz < 2 || g.nt < 2) return false;  // columns are pairs
   const int F = P->F, W = P->W;
   // the 16 x 16 blocks of (t, z) with a nonzero entry at any offset
   std::vector<unsigned> mask((g.nt + 15) / 16, 0);
@@ -1351,30 +1396,30 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   const int ntt = (int)mask.size(), lt = 16 * ntt;
   int nblk = 0;
   for (unsigned m : mask) nblk += __builtin_popcount(m);
-  const int np = (g.n_pulses + 1) / 2;
   const int ni = (X.n - 1) / 2, edges = X.n % 2 ? 1 : 2;
   const size_t nf = (size_t)ni * Y.n + (size_t)edges * (Y.n / 2 + 1);
   const bool st = !g.phi_per_voxel && !P->sw.diag;
   const size_t img = (size_t)Y.n * X.n;
-  const size_t xb = (size_t)np * img * lz * 8;
+  // a complex value holds two depths or samples
+  const size_t xb = (size_t)g.n_pulses * img * lz * 4;
   // per-voxel fluence: y's spectrum also holds the pulse volumes S^T reads,
   // which are the larger where the depths outnumber the samples
-  const size_t yb = std::max((size_t)np * img * lt * 8, (size_t)g.n_pulses * P->v_elems() * sizeof(float));
-  const size_t rb = (size_t)np * g.ny * X.n * lt * 8;
-  const size_t gb = (size_t)(st ? (P->sw.ns + 1) / 2 : np) * img * lz * 8;
+  const size_t yb = std::max((size_t)g.n_pulses * img * lt * 4, (size_t)g.n_pulses * P->v_elems() * sizeof(float));
+  const size_t rb = (size_t)g.n_pulses * g.ny * X.n * lt * 4;
+  const size_t gb = (size_t)(st ? P->sw.ns : g.n_pulses) * img * lz * 4;
   const size_t tb = (nf * nblk + 2) * 512 * sizeof(float);
   const size_t pb = (size_t)(X.n / 2 + 1) * F * 256 * sizeof(double2);
   const size_t grid = (size_t)g.ny * g.nx;
   // the transforms' offsets within a line are 32 bits, its positions 20
   X.derive();
   Y.derive();
-  const size_t most = (size_t)std::max(lz, lt) * 8;
+  const size_t most = (size_t)std::max(lz, lt) * 4;
   if (std::max({X.n * std::max<size_t>(most, 4 * (size_t)std::max(g.nt, g.nz)),
                 Y.reach(most * X.n)}) >= (1ull << 32) ||
       std::max(X.n, Y.n) >= (1 << 20))
     return false;
   // launch grids are 32-bit counts of blocks
-  if (nf >= (1u << 31) || (size_t)np * X.n * (lt / 16) >= (1u << 31)) return false;
+  if (nf >= (1u << 31) || (size_t)g.n_pulses * ((size_t)X.n * (std::max(lz, lt) / 2) / 16 + 1) >= (1u << 31)) return false;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return false;
   const size_t need = xb + yb + rb + gb + 2 * tb + pb;
@@ -1388,7 +1433,7 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
     // pulses and a footprint of 31 the pair takes 1.4 ms against the direct
     // form's 41 ms in FP32 and 3.2 ms in BF16; at 97 x 95 x 16 with a
     // footprint of 7 and 64 samples it takes 0.8 ms against 0.28 ms in BF16.
-    const double a = 2.0 * np * g.ny * X.n * lz * 8 + 2.0 * xb + tb + 2.0 * yb + 2.0 * rb;
+    const double a = 2.0 * g.n_pulses * g.ny * X.n * lz * 4 + 2.0 * xb + tb + 2.0 * yb + 2.0 * rb;
     const double at = 2.0 * rb + 2.0 * yb + tb + 4.0 * gb;
     const double y = 4.0 * g.n_pulses * grid;  // a sample of every A-scan
     const double us = 62.0 + 0.248e-6 * (a + at + y * (g.nt + lt) + (fact ? 2.0 : 0.0) * y * g.nt);
@@ -1417,7 +1462,6 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   Q.lz = lz;
   Q.lt = lt;
   Q.tlo = 16 * tb0;
-  Q.np = np;
   Q.nf = nf;
   Q.nblk = nblk;
   double2* d_p = nullptr;
@@ -1443,6 +1487,8 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   alloc(&Q.d_tf, tb);
   alloc(&Q.d_ta, tb);
   alloc(&Q.d_mask, sizeof(unsigned) * ntt);
+  const bool rate = P->sw.per_voxel && !P->sw.diag && P->sw.gamma != 0.0f && P->sw.gamma != 1.0f;
+  if (rate) alloc(&Q.d_rate, sizeof(float) * P->v_elems());
   alloc(&Q.d_twx, sizeof(float2) * X.n);
   alloc(&Q.d_twy, sizeof(float2) * Y.n);
   // marks of b and of r: two words and a byte per position and plane
@@ -1478,6 +1524,9 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
     check(hipMemsetAsync(Q.d_marks, 0, mb, stream));
     check(hipMemsetAsync(Q.d_tf + (nf * nblk) * 512, 0, 1024 * sizeof(float), stream));
     check(hipMemsetAsync(Q.d_ta + (nf * nblk) * 512, 0, 1024 * sizeof(float), stream));
+    if (rate)
+      check(go(spec_rate, (P->v_elems() + 255) / 256, 256, 0, stream, P->d_phi, Q.d_rate, P->sw.gamma,
+               P->v_elems()));
     // 1/2 from the pairs' separation, 1 / (NX NY) from the inverse transform
     const double scale = 0.5 / ((double)X.n * (double)Y.n);
     const int kxn = X.n / 2 + 1;

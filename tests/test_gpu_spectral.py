@@ -93,6 +93,26 @@ def test_matches_direct_form(name, prec, monkeypatch):
         assert ea <= TOL_OP["fp32"] and et <= TOL_OP["fp32"]
 
 
+@pytest.mark.parametrize("gamma", [0.0, 0.5, 1.0])
+def test_switching_rates(gamma, monkeypatch):
+    """Per-voxel fluence with a rate that does not depend on it, and with
+    exponents whose power is and is not the fluence itself."""
+    torch = torch_cuda()
+    shape = (21, 18, 33, 5, 40, 9, 3, True)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    sp = synth.Species(sp.a, sp.b, sp.tau, gamma)
+    c = torch.from_numpy(rng.standard_normal((3, 18, 21, 33)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.standard_normal((5, 18, 21, 40)).astype(np.float32)).cuda()
+    out = []
+    for form in "01":
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "fp32")
+        out.append((plan.apply_A(c), plan.apply_AT(y)))
+        plan.close()
+    e = [_rel(s, d) for s, d in zip(out[1], out[0])]
+    say(f"[spectral] gamma {gamma}: {e}")
+    assert max(e) <= 2 * TOL_OP["fp32"]
+
+
 @pytest.mark.parametrize("n", [*range(8, 33), 45, 50, 54, 64, 80, 81, 90, 100, 125, 144, 243, 343, 500])
 def test_transform_lengths(n, monkeypatch):
     """Grids one row wide whose transforms take every radix and stage count."""
@@ -217,6 +237,53 @@ def test_bad_values_stay_in_their_footprint(bad, voxel, monkeypatch):
     plan.close()
 
 
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16_split"])
+def test_weak_pulses_beside_strong_ones(prec, monkeypatch):
+    """Pulse volumes whose amplitudes fall by a factor of 1000 from one to the
+    next: each pulse's A and A^T err as they would alone."""
+    torch = torch_cuda()
+    import paper_2510_23739_amd as pk
+    rng, t0, taps, _, _ = _inputs((40, 38, 20, 5, 40, 15, 5, False))
+    scale = torch.tensor([1.0, 1e-3, 1e-6, 1e-9, 1.0], device="cuda")[:, None, None, None]
+    g = torch.Generator(device="cuda").manual_seed(3)
+    out = []
+    for form in "01":
+        monkeypatch.setenv("PSOAM_SPECTRAL", form)
+        plan = pk.Plan.acoustic(40, 38, 20, 5, 40, 15, t0, taps, prec=prec)
+        g.manual_seed(3)
+        c, y = (torch.randn(s, device="cuda", generator=g) * scale for s in (plan.c_shape, plan.y_shape))
+        out.append((plan.apply_A(c), plan.apply_AT(y)))
+        plan.close()
+    tol = TOL_OP[prec] if prec.endswith("split") else 2 * TOL_OP["fp32"]
+    for a, b in zip(*out):
+        for k in range(5):
+            e = _rel(b[k], a[k])
+            say(f"[spectral] weak pulses {prec} pulse {k}: {e:.2e}")
+            assert e <= tol
+
+
+@pytest.mark.parametrize("amp", [1e-3, 1e-6])
+def test_weak_region_far_from_a_strong_one(amp, monkeypatch):
+    """A transform rounds in proportion to its plane: beside a point of 1 a
+    weak region out of its reach errs by at most 1e-6 of the plane's largest
+    output (16 units of FP32 rounding, about one a stage of two transforms),
+    not of its own."""
+    torch = torch_cuda()
+    shape = (90, 80, 12, 2, 60, 15, 1, False)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    c = torch.zeros((1, 80, 90, 12), device="cuda")
+    c[0, 20, 20] = torch.from_numpy(rng.standard_normal(12).astype(np.float32)).cuda()
+    c[0, 55:65, 60:70] = amp * torch.from_numpy(rng.standard_normal((10, 10, 12)).astype(np.float32)).cuda()
+    out = []
+    for form in "01":
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "fp32")
+        out.append(plan.apply_A(c))
+        plan.close()
+    far = (out[0] - out[1])[:, 40:, 40:].abs()
+    say(f"[spectral] weak region {amp}: {float(far.max()):.2e} of {float(out[0].abs().max()):.2e}")
+    assert float(far.max()) <= 1e-6 * float(out[0].abs().max())
+
+
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("k", [4, 5])
 def test_pulse_volumes_stay_apart(k, bad, monkeypatch):
@@ -339,6 +406,32 @@ def test_planes_beyond_four_gibibytes(monkeypatch):
             if free - torch.cuda.mem_get_info()[0] < 10e9:
                 plan.close()
                 pytest.skip("no memory for the spectra")
+        out.append((plan.apply_A(c), plan.apply_AT(y)))
+        plan.close()
+    for a, b in zip(*out):
+        assert float((a - b).norm() / a.norm()) <= 2 * TOL_OP["fp32"]
+
+
+def test_pulse_planes_beyond_four_gibibytes(monkeypatch):
+    """The same with 1024 samples: one pulse's spectrum of 5.2 GB."""
+    torch = torch_cuda()
+    shape = (1100, 1100, 4, 1, 1024, 3, 1, False)
+    rng, _, _, phi, sp = _inputs(shape)
+    t0 = np.zeros((4, 3, 3), np.int32)
+    t0[3] = 1012
+    taps = np.zeros((4, 3, 3, 4), np.float32)
+    taps[[0, 3]] = rng.standard_normal((2, 3, 3, 4)).astype(np.float32)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    c = torch.randn((1, 1100, 1100, 4), device="cuda", generator=g)
+    y = torch.randn((1, 1100, 1100, 1024), device="cuda", generator=g)
+    out = []
+    for form in "01":
+        say(f"[spectral] a pulse's plane beyond 4 GiB, form {form}")
+        free = torch.cuda.mem_get_info()[0]
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "bf16")
+        if form == "1" and free - torch.cuda.mem_get_info()[0] < 14e9:
+            plan.close()
+            pytest.skip("no memory for the spectra")
         out.append((plan.apply_A(c), plan.apply_AT(y)))
         plan.close()
     for a, b in zip(*out):
