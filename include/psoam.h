@@ -76,7 +76,9 @@ enum {
  * pulse and the same pair of neighbouring samples or depths), by at most about
  * 1e-6 of it.  Over whole planes that is no more than the direct form's error;
  * a region that is weaker than the rest of its plane by a factor w errs by up
- * to 1e-6 w of its own values.  Pulses do not touch each other.  Results stay
+ * to 1e-6 w of its own values.  Pulses do not touch each other.  Operands as
+ * large as the direct form takes do not overflow; below about 1e-30 they lose
+ * precision to the transforms' subnormal values.  Results stay
  * inside the footprint: an output is zero where every operand value within its footprint
  * is, and non-finite operand values make the outputs of their footprint
  * non-finite.  The spectra and the table per frequency take device memory (23

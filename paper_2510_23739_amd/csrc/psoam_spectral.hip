@@ -190,12 +190,23 @@ __device__ __forceinline__ void clear_row(const Marks& M, size_t row, int nx) {
   for (int x = (int)threadIdx.x; x < nx; x += kFftThreads) M.at[row + x] = M.bad[row + x] = 0u;
 }
 
+// Operand values enter the transforms times 1 / 2^e >= 1 / (NX NY) (exact; the
+// table has the rest of the inverse transform's 1 / (NX NY)): every value on the
+// way is then at most about as large as the largest operand or result, where
+// sums over a plane would overflow for operands beyond 3e38 / (NX NY).
+template <int R>
+__device__ __forceinline__ void scale_points(float in_scale, float2* v) {
+#pragma unroll
+  for (int q = 0; q < R; ++q) v[q] = {v[q].x * in_scale, v[q].y * in_scale};
+}
+
 struct Geo {
   int ny, nx, nyp, nxp;  // grid and transform lengths
   int nz, nt, hz, ht;    // depths, samples; columns (pairs of them) of the transformed ones
   int tlo;               // first transformed sample
   int nk;                // pulses
   int r;
+  float in_scale;        // 1 / 2^e (see scale_points)
 };
 
 // ------------------------------------------------------------ x transforms
@@ -382,6 +393,7 @@ __global__ __launch_bounds__(kFftThreads, 4) void spec_x_switch(
       v[q].y = in && pr.both ? rnd<RND>(v[q].y, sc, inv) : 0.0f;
     }
     mark_points<R>(W, M, mrow, x0, step, v);
+    scale_points<R>(G.in_scale, v);
   };
   fft::first_stage<-1>(D, L, load);
   store_hits(W, M, mrow, G.nx);
@@ -422,6 +434,7 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
       v[q].y = in && pr.both ? rnd<RND>(v[q].y, sc, inv) : 0.0f;
     }
     mark_points<R>(W, M, mrow, x0, step, v);
+    scale_points<R>(G.in_scale, v);
   };
   fft::first_stage<-1>(D, L, load);
   store_hits(W, M, mrow, G.nx);
@@ -537,6 +550,7 @@ __global__ __launch_bounds__(kFftThreads, 4) void spec_x_resid(
       v[q] = d;
     }
     mark_points<R>(W, MR, rrow, x0, step, v);
+    scale_points<R>(G.in_scale, v);
   });
   store_hits(W, MR, rrow, G.nx);
   float2* ov = out + ((size_t)at.k * G.ny + at.iy) * G.nxp * G.ht + at.c0;
@@ -1110,6 +1124,9 @@ bool choose_length(int need, FftDim& D) {
   return found;
 }
 
+// the power of two at or above NX NY
+double plane_scale(int nx, int ny) { return std::exp2(std::ceil(std::log2((double)nx * (double)ny))); }
+
 Geo geo_of(const psoam_plan* P) {
   const SpecPlan& Q = *P->spec;
   Geo G;
@@ -1124,6 +1141,7 @@ Geo geo_of(const psoam_plan* P) {
   G.tlo = Q.tlo;
   G.nk = P->g.n_pulses;
   G.r = P->R;
+  G.in_scale = (float)(1.0 / plane_scale(Q.nx, Q.ny));
   return G;
 }
 
@@ -1528,7 +1546,8 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
       check(go(spec_rate, (P->v_elems() + 255) / 256, 256, 0, stream, P->d_phi, Q.d_rate, P->sw.gamma,
                P->v_elems()));
     // 1/2 from the pairs' separation, 1 / (NX NY) from the inverse transform
-    const double scale = 0.5 / ((double)X.n * (double)Y.n);
+    // with the operands' scale taken out
+    const double scale = 0.5 * plane_scale(X.n, Y.n) / ((double)X.n * (double)Y.n);
     const int kxn = X.n / 2 + 1;
     for (int pass = 0; pass < (twice ? 2 : 1) && ok; ++pass) {
       check(hipMemcpyAsync(d_taps, pass ? taps_a : taps_f, sizeof(float) * ntab * W,

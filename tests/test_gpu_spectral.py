@@ -237,6 +237,26 @@ def test_bad_values_stay_in_their_footprint(bad, voxel, monkeypatch):
     plan.close()
 
 
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("power", [116, -80])
+def test_operands_of_any_scale(power, prec, monkeypatch):
+    """Operands times a power of two, up to where outputs are near the largest
+    float: the transforms' sums over a plane do not overflow first, so outputs
+    scale by the same power, bit for bit (below: but for subnormal remainders)."""
+    torch = torch_cuda()
+    shape = (90, 80, 12, 3, 40, 7, 2, False)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    c = torch.from_numpy(rng.uniform(0.5, 1.0, (2, 80, 90, 12)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.uniform(0.5, 1.0, (3, 80, 90, 40)).astype(np.float32)).cuda()
+    for form in "01":
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, prec)
+        for f, v in ((plan.apply_A, c), (plan.apply_AT, y)):
+            small, big = f(v).double(), f(v * 2.0 ** power).double() * 2.0 ** -power
+            say(f"[spectral] scale 2^{power} {prec} form {form}: {float((big - small).norm() / small.norm()):.1e}")
+            assert torch.equal(small, big) if power > 0 else _rel(big, small) <= 1e-7
+        plan.close()
+
+
 @pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16_split"])
 def test_weak_pulses_beside_strong_ones(prec, monkeypatch):
     """Pulse volumes whose amplitudes fall by a factor of 1000 from one to the
