@@ -78,10 +78,10 @@ enum {
  * a region that is weaker than the rest of its plane by a factor w errs by up
  * to 1e-6 w of its own values.  Pulses do not touch each other.  Operands as
  * large as the direct form takes do not overflow; below about 1e-30 they lose
- * precision to the transforms' subnormal values.  Results stay
- * inside the footprint: an output is zero where every operand value within its footprint
- * is, and non-finite operand values make the outputs of their footprint
- * non-finite.  The spectra and the table per frequency take device memory (23
+ * precision to the transforms' subnormal values.  Results stay inside the
+ * footprint, and of it in the 16-wide tiles of depths and samples that band
+ * entries join: an output is zero where every operand value that can reach it so
+ * is, and NaN where a non-finite one can.  The spectra and the table per frequency take device memory (23
  * GB at 320 x 320 x 128 with 40 pulses and 512 samples, 1.6 GB at 128 x 128 x
  * 64 with 32 and 256); a plan for which they exceed a third of the free
  * memory, or cannot be allocated, keeps the direct form.  The environment

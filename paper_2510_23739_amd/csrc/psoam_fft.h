@@ -282,9 +282,14 @@ __device__ __forceinline__ const T& at(const T* base, unsigned byte) {
 // stage 0 of the natural-order side: load(radix, first index, step, points)
 // fills a butterfly's points, so that it can issue all their loads before it
 // looks at any (a branch between two loads makes each wait for the one
-// before); barriers: one before (the twiddles are in LDS) and one after
-template <int SIGN, class Load>
-__device__ __forceinline__ void first_stage(const FftDim& D, const Lds& L, Load&& load) {
+// before); barriers: one before (the twiddles are in LDS) and one after, which
+// late() precedes
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <int SIGN, class Load, class Late = Nothing>
+__device__ __forceinline__ void first_stage(const FftDim& D, const Lds& L, Load&& load,
+                                            Late&& late = Nothing{}) {
   const int lane = threadIdx.x & 15, row = threadIdx.x >> 4;
   __syncthreads();
   with_radix(D.rad[0], [&](auto rc) {
@@ -302,6 +307,7 @@ __device__ __forceinline__ void first_stage(const FftDim& D, const Lds& L, Load&
         lds_at(a, q * mb) = q ? twmul<SIGN>(v[q], lds_at(L.tw, t)) : v[q];
     }
   });
+  late();
   __syncthreads();
 }
 

@@ -122,16 +122,15 @@ struct SpecPlan {
   float* d_rate = nullptr;     // phi^gamma per voxel where gamma is neither 0 nor 1
   void* d_twx = nullptr;
   void* d_twy = nullptr;
-  // marks of H's operand and H^T's: positions with a nonzero value, with a
-  // non-finite one, and what either reaches (one allocation)
+  // marks of H's operand and H^T's: the depth tiles of each position with a
+  // nonzero and a non-finite value, what these reach, and rows read by the
+  // kernel that finds that (one allocation)
   void* d_marks = nullptr;
   unsigned* d_at_b = nullptr;
-  unsigned* d_bad_b = nullptr;
-  unsigned char* d_near_b = nullptr;
   unsigned* d_at_r = nullptr;
-  unsigned* d_bad_r = nullptr;
-  unsigned char* d_near_r = nullptr;
-  unsigned call_b = 0, call_r = 0;
+  unsigned* d_near_b = nullptr;
+  unsigned* d_near_r = nullptr;
+  int* d_seen = nullptr;
 };
 
 // Launch shape of the marching TV kernel (psoam_tvmarch.hip): positions per

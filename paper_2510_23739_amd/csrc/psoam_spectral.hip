@@ -84,48 +84,53 @@ __global__ __launch_bounds__(256) void spec_rate(const float* __restrict__ phi, 
 
 // Where the operand is not zero, and where it is not finite.  A transform
 // spreads its rounding over the whole image, and a value that is not finite
-// over all of it; the direct form reaches a footprint.  So every pass that
-// makes an operand marks its positions, spec_reach widens the marks by the
-// footprint, and the pass that writes the result writes zero where no nonzero
-// value reaches and NaN where a non-finite one does (such a value enters the
-// transforms as zero).  A mark is the number of the call that set it, so that
-// no call sees an older one's; and since a captured call repeats its number,
-// the pass that reads the reach last clears the marks it came from (and the
-// product before the residual's pass those of r, which an objective leaves
-// behind).
+// over all of it; the direct form reaches the footprint, and of it the tiles of
+// depths or samples that band entries meet.  So every pass that makes an operand
+// marks its positions, spec_reach widens the marks by the footprint, and the
+// pass that writes the result writes zero where no nonzero value reaches and NaN
+// where a non-finite one does (such a value enters the transforms as zero).  A
+// mark is a bit per 16 depths: those of an operand of H, those that the sample
+// tile meets (the product's mask) of one of H^T, looked at the other way round
+// by the results.  spec_reach leaves the marks cleared: the next operand finds
+// them so, whatever ran before it, eagerly or replayed.
 struct Marks {
-  unsigned* at;         // [planes][Ny][Nx]: a nonzero value
-  unsigned* bad;        // the same: a non-finite one
-  unsigned char* near;  // the same: bit 0 a nonzero value in reach, bit 1 a non-finite one
-  unsigned now;
-  int planes;           // 1, or one per pulse (pulse volumes of their own)
+  unsigned* at;    // [planes][Ny][Nx]: bits 0 .. 15 nonzero, 16 .. 31 not finite
+  unsigned* near;  // the same, of all positions in reach
+  int* seen;       // [planes][Ny]: how many rows have looked at this one
+  int planes;      // 1, or one per pulse (pulse volumes of their own)
 };
-enum Near { kNearSome = 1, kNearBad = 2 };
+constexpr int kBadBit = 16;
 // The marks of a workgroup's row collect in LDS (a byte per column x, after
 // the line and its twiddles) and go out once, and the reach of a row's
-// columns comes in once: a mark or a look at one never waits for HBM.
+// columns comes in once: a mark or a look at one never waits for HBM.  The
+// workgroup's two tiles have a bit each, lanes 0 .. 7 the first, 8 .. 15 the
+// second.
 struct RowMarks {
-  unsigned char* hit;  // [n]
-  signed char* near;   // [n]
+  unsigned char* hit;   // [n]: bits 0, 1 a nonzero value of the tile
+  unsigned char* near;  // [n]: bits 0, 1 one in the tile's reach, bits 2, 3 a non-finite one
+  unsigned tile[2];     // the tiles' bits of a mark
 };
-__device__ __forceinline__ RowMarks row_marks(unsigned char* raw, int n) {
+// mask: the depths that each sample tile meets (null: the tiles are depths)
+__device__ __forceinline__ RowMarks row_marks(unsigned char* raw, int n, const unsigned* __restrict__ mask,
+                                              int c0, int h) {
   unsigned char* a = raw + (size_t)n * (kFftLanes + 1) * sizeof(float2);
-  return RowMarks{a, (signed char*)a + n};
+  const int t = c0 >> 3;
+  const bool two = c0 + 8 < h;
+  return RowMarks{a, a + n, {mask ? mask[t] : 1u << t, two ? mask ? mask[t + 1] : 1u << (t + 1) : 0u}};
 }
 __host__ __device__ constexpr size_t row_lds(int n) {
   return (size_t)n * ((kFftLanes + 1) * sizeof(float2) + 2);
 }
-// One butterfly's operand values v (R positions x0, x0 + step, ..): the 16
-// lanes of a position (a DPP row) join their nonzero bits and lane q writes
-// position q's byte (every position belongs to one butterfly); non-finite
-// values, which are rare, are marked in HBM (row: the plane's row) and become
-// zero.
-__device__ __forceinline__ unsigned row_or(unsigned h) {
-  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x128, 0xf, 0xf, true);  // row_ror:8
-  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x124, 0xf, 0xf, true);
-  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x122, 0xf, 0xf, true);
-  h |= (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x121, 0xf, 0xf, true);
-  return h;
+__device__ __forceinline__ void set_mark(const Marks& M, size_t i, unsigned bits) {
+  if ((M.at[i] & bits) != bits) atomicOr(&M.at[i], bits);
+}
+// One butterfly's operand values v (R positions x0, x0 + step, ..): the eight
+// lanes of a tile join their nonzero bits and lane q writes position q's byte
+// (every position belongs to one butterfly); non-finite values, which are rare,
+// are marked in HBM (row: the plane's row) and become zero.
+template <int CTRL>
+__device__ __forceinline__ unsigned or_dpp(unsigned h) {
+  return h | (unsigned)__builtin_amdgcn_mov_dpp((int)h, CTRL, 0xf, 0xf, true);
 }
 template <int R>
 __device__ __forceinline__ void mark_points(const RowMarks& W, const Marks& M, size_t row, int x0,
@@ -140,54 +145,72 @@ __device__ __forceinline__ void mark_points(const RowMarks& W, const Marks& M, s
     bad |= !finite_(s);
     h |= s != 0.0f ? 1u << q : 0u;
   }
-  h = row_or(h);
-  if (lane < R) W.hit[x0 + fft::mul24(lane, step)] = (unsigned char)(h >> lane & 1u);
+  h = or_dpp<0x141>(or_dpp<0x4E>(or_dpp<0xB1>(h)));  // lanes j ^ 1, j ^ 2, 7 - j of eight
+  const unsigned other = (unsigned)__builtin_amdgcn_mov_dpp((int)h, 0x128, 0xf, 0xf, true);  // row_ror:8
+  const unsigned a = lane < 8 ? h : other, b = lane < 8 ? other : h;
+  if (lane < R)
+    W.hit[x0 + fft::mul24(lane, step)] = (unsigned char)((a >> lane & 1u) | (b >> lane & 1u) << 1);
   if (bad) {
+    const unsigned bits = (lane < 8 ? W.tile[0] : W.tile[1]) << kBadBit;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      if (!(finite_(v[q].x) && finite_(v[q].y))) M.bad[row + x0 + q * step] = M.now;
+      if (!(finite_(v[q].x) && finite_(v[q].y))) set_mark(M, row + x0 + q * step, bits);
       if (!finite_(v[q].x)) v[q].x = 0.0f;
       if (!finite_(v[q].y)) v[q].y = 0.0f;
     }
   }
 }
-// The reach of the row's columns as bytes to and a value with: all ones where a
-// nonzero value reaches, 0 where none does (and past the grid), kReachBad where
-// a non-finite one does.
-constexpr signed char kReachBad = 127;
-__device__ __forceinline__ signed char reach_of(unsigned char near) {
-  return near & kNearBad ? kReachBad : near & kNearSome ? (signed char)-1 : (signed char)0;
+// The reach of the row's columns (past the grid: none): on its way while the
+// first stage loads and computes, then into LDS.
+constexpr int kNearWords = 5;  // of 256 columns: more than a line in LDS has
+struct NearWords {
+  unsigned w[kNearWords];
+};
+__device__ __forceinline__ NearWords load_near(const Marks& M, size_t row, int nx) {
+  NearWords N;
+#pragma unroll
+  for (int i = 0; i < kNearWords; ++i) {
+    const int x = (int)threadIdx.x + i * kFftThreads;
+    N.w[i] = x < nx ? M.near[row + x] : 0u;
+  }
+  return N;
 }
-__device__ __forceinline__ void load_near(const RowMarks& W, int n, const Marks& M, size_t row, int nx) {
-  for (int x = (int)threadIdx.x; x < n; x += kFftThreads)
-    W.near[x] = x < nx ? reach_of(M.near[row + x]) : (signed char)0;
+__device__ __forceinline__ void keep_near(const RowMarks& W, int n, const NearWords& N) {
+#pragma unroll
+  for (int i = 0; i < kNearWords; ++i) {
+    const int x = (int)threadIdx.x + i * kFftThreads;
+    const unsigned w = N.w[i], b = w >> kBadBit;
+    if (x < n)
+      W.near[x] = (unsigned char)((w & W.tile[0] ? 1 : 0) | (w & W.tile[1] ? 2 : 0) |
+                                  (b & W.tile[0] ? 4 : 0) | (b & W.tile[1] ? 8 : 0));
+  }
 }
 // a butterfly's results, zero or NaN where the reach says so
 template <int R>
 __device__ __forceinline__ void reach_points(const RowMarks& W, int x0, int step, float2* v) {
-  int r[R], most = 0;
+  const int tile = threadIdx.x >> 3 & 1;
+  int r[R], any = 0;
 #pragma unroll
   for (int q = 0; q < R; ++q) r[q] = W.near[x0 + q * step];
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    most = max(most, r[q]);
-    v[q].x = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].x) & r[q]);
-    v[q].y = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].y) & r[q]);
+    any |= r[q];
+    const int keep = __builtin_amdgcn_sbfe(r[q], tile, 1);  // all ones or zero
+    v[q].x = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].x) & keep);
+    v[q].y = __builtin_bit_cast(float, __builtin_bit_cast(int, v[q].y) & keep);
   }
-  if (most > 0) {
+  if (any >> 2) {
 #pragma unroll
     for (int q = 0; q < R; ++q)
-      if (r[q] > 0) v[q].x = v[q].y = __builtin_nanf("");
+      if (r[q] >> (2 + tile) & 1) v[q].x = v[q].y = __builtin_nanf("");
   }
 }
 // (after a barrier) marks into their plane's row
 __device__ __forceinline__ void store_hits(const RowMarks& W, const Marks& M, size_t row, int nx) {
-  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads)
-    if (W.hit[x] && M.at[row + x] != M.now) M.at[row + x] = M.now;
-}
-// a workgroup's row of marks, once per row and plane
-__device__ __forceinline__ void clear_row(const Marks& M, size_t row, int nx) {
-  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads) M.at[row + x] = M.bad[row + x] = 0u;
+  for (int x = (int)threadIdx.x; x < nx; x += kFftThreads) {
+    const unsigned char h = W.hit[x];
+    if (h) set_mark(M, row + x, (h & 1 ? W.tile[0] : 0u) | (h & 2 ? W.tile[1] : 0u));
+  }
 }
 
 // Operand values enter the transforms times 1 / 2^e >= 1 / (NX NY) (exact; the
@@ -205,7 +228,6 @@ struct Geo {
   int nz, nt, hz, ht;    // depths, samples; columns (pairs of them) of the transformed ones
   int tlo;               // first transformed sample
   int nk;                // pulses
-  int r;
   float in_scale;        // 1 / 2^e (see scale_points)
 };
 
@@ -313,7 +335,7 @@ __global__ __launch_bounds__(kFftThreads, 4) void spec_x_switch(
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at_pulses(G.ny, G.hz);
   if (at.k >= G.nk) return;
-  const RowMarks W = row_marks(raw, D.n);
+  const RowMarks W = row_marks(raw, D.n, nullptr, at.c0, G.hz);
   const Pair pr = pair_at(at.c0, G.hz, 0, G.nz);
   const int k = at.k, z = pr.first ? 2 * (at.c0 + (int)(threadIdx.x & 15)) : 0, z1 = pr.both ? z + 1 : z;
   // the pulses' mark planes
@@ -407,12 +429,13 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
                                                            const float* __restrict__ f16,
                                                            float2* __restrict__ out, Geo G,
                                                            FftDim D, Marks M,
+                                                           const unsigned* __restrict__ mask,
                                                            const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.ht);
-  const RowMarks W = row_marks(raw, D.n);
+  const RowMarks W = row_marks(raw, D.n, mask, at.c0, G.ht);
   const Pair pr = pair_at(at.c0, G.ht, G.tlo, G.nt);
   const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
   const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
@@ -446,19 +469,20 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_pack(const float* __restri
 // y = H b of a pulse
 __global__ __launch_bounds__(kFftThreads) void spec_x_out(const float2* __restrict__ in,
                                                           float* __restrict__ y, Geo G, FftDim D,
-                                                          Marks M, const int* __restrict__ gate) {
+                                                          Marks M, const unsigned* __restrict__ mask,
+                                                          const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.ht);
   const Pair pr = pair_at(at.c0, G.ht, G.tlo, G.nt);
-  const RowMarks W = row_marks(raw, D.n);
+  const RowMarks W = row_marks(raw, D.n, mask, at.c0, G.ht);
   const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
   const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
-  load_near(W, D.n, M, mrow, G.nx);
-  if (at.c0 == 0 && (M.planes > 1 || at.k == 0)) clear_row(M, mrow, G.nx);
+  const NearWords nw = load_near(M, mrow, G.nx);
   const float2* i = in + ((size_t)at.k * G.nyp + at.iy) * G.nxp * G.ht + at.c0;
-  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.ht, G.nxp, column_at(at.c0, G.ht).lane));
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.ht, G.nxp, column_at(at.c0, G.ht).lane),
+                      [&] { keep_near(W, D.n, nw); });
   fft::middle_stages<1>(D, L);
   float* yk = y + (at.k * grid + yrow) * G.nt + pr.base;
   const unsigned pitch = 4u * (unsigned)G.nt;
@@ -483,23 +507,23 @@ __global__ __launch_bounds__(kFftThreads, 4) void spec_x_resid(
     const float2* __restrict__ in, const float* __restrict__ pm, const float* __restrict__ f16,
     float2* __restrict__ out, float* __restrict__ yc, float yc_beta, float yc_inv, int yc_first,
     double* __restrict__ partial, Geo G, FftDim D, Marks M, Marks MR,
-    const int* __restrict__ gate) {
+    const unsigned* __restrict__ mask, const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   __shared__ double sh[kFftThreads / 64];
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.ht);
   const Pair pr = pair_at(at.c0, G.ht, G.tlo, G.nt);
-  const RowMarks W = row_marks(raw, D.n);
+  const RowMarks W = row_marks(raw, D.n, mask, at.c0, G.ht);
   const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
   const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
   const size_t rrow = (MR.planes == 1 ? 0 : at.k * grid) + yrow;
-  load_near(W, D.n, M, mrow, G.nx);
-  if (at.c0 == 0 && (M.planes > 1 || at.k == 0)) clear_row(M, mrow, G.nx);
+  const NearWords nw = load_near(M, mrow, G.nx);
   const float sc = RND == kRndF16 ? f16[2] : 1.0f, inv = RND == kRndF16 ? f16[3] : 1.0f;
   const Column col = column_at(at.c0, G.ht);
   const float2* i = in + ((size_t)at.k * G.nyp + at.iy) * G.nxp * G.ht + at.c0;
-  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.ht, G.nxp, col.lane));
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.ht, G.nxp, col.lane),
+                      [&] { keep_near(W, D.n, nw); });
   fft::middle_stages<1>(D, L);
   // the row's samples of the tile; loads past the grid read inside it (values
   // dropped)
@@ -629,14 +653,14 @@ __global__ __launch_bounds__(kFftThreads) void spec_x_vox(const float2* __restri
   const fft::Lds L = fft::carve(raw, D);
   const RowAt at = row_at(G.ny, G.hz);
   const Pair pr = pair_at(at.c0, G.hz, 0, G.nz);
-  const RowMarks W = row_marks(raw, D.n);
+  const RowMarks W = row_marks(raw, D.n, nullptr, at.c0, G.hz);
   // (planes of their own: volumes are pulses)
   const size_t grid = (size_t)G.ny * G.nx, yrow = (size_t)at.iy * G.nx;
   const size_t mrow = (M.planes == 1 ? 0 : at.k * grid) + yrow;
-  load_near(W, D.n, M, mrow, G.nx);
-  if (at.c0 == 0 && (M.planes > 1 || at.k == 0)) clear_row(M, mrow, G.nx);
+  const NearWords nw = load_near(M, mrow, G.nx);
   const float2* i = in + ((size_t)at.k * G.nyp + at.iy) * G.nxp * G.hz + at.c0;
-  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.hz, G.nxp, column_at(at.c0, G.hz).lane));
+  fft::first_stage<1>(D, L, fft::strided<true>(i, 8u * G.hz, G.nxp, column_at(at.c0, G.hz).lane),
+                      [&] { keep_near(W, D.n, nw); });
   fft::middle_stages<1>(D, L);
   const size_t row = yrow * G.nz + pr.base;
   float* ck = c + at.k * grid * G.nz + row;
@@ -799,9 +823,6 @@ struct GemmArgs {
   int nyp, nxp, lz, lt, nk;
   const float2* in;
   float2* out;
-  // H before a residual: r's marks (at, bad), cleared
-  unsigned* clear;
-  size_t n_clear;
   // H^T with S^T: the species' coefficients [K][S][Nz]
   const float* stab_t;
   int ns, nz;
@@ -816,11 +837,6 @@ __global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_
                                                                           const unsigned* __restrict__ mask) {
   if (A.gate && *A.gate) return;  // a device stop test has ended the solve
   const int f = (int)blockIdx.x;
-  // (frequencies x threads, NX NY / 2 x at least 8 a pulse, outnumber the positions of all planes)
-  if (A.clear) {
-    const size_t i = (size_t)f * blockDim.x + threadIdx.x;
-    if (i < A.n_clear) A.clear[i] = 0u;
-  }
   const Freq F = freq_at(f, A.nyp, A.nxp);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int g = lane >> 4, n = lane & 15, c = n & 1;
@@ -1048,27 +1064,38 @@ __global__ __launch_bounds__(256) void spec_table_y(const double2* __restrict__ 
 
 // ------------------------------------------------------ reach of the marks
 // Block: one row of one plane.  The marks of the 2 R + 1 rows around it are
-// joined per column, then the columns over 2 R + 1 neighbours.
+// joined per column, then the columns over 2 R + 1 neighbours.  The last block to
+// have read a row clears its marks.
 __global__ __launch_bounds__(256) void spec_reach(Marks M, int ny, int nx, int r,
                                                   const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
-  const int iy = (int)blockIdx.x % ny;
-  const size_t plane = (size_t)((int)blockIdx.x / ny) * ny * nx;
+  unsigned* row = (unsigned*)raw;           // [nx]
+  int* done = (int*)raw + nx;               // [1 + 2 R + 1]: how many rows to clear, and which
+  const int iy = (int)blockIdx.x % ny, p = (int)blockIdx.x / ny;
+  const size_t plane = (size_t)p * ny * nx;
   const int y0 = max(0, iy - r), y1 = min(ny - 1, iy + r);
+  if (threadIdx.x == 0) done[0] = 0;
   for (int x = (int)threadIdx.x; x < nx; x += 256) {
     unsigned f = 0;
-    for (int y = y0; y <= y1; ++y) {
-      const size_t i = plane + (size_t)y * nx + x;
-      f |= (M.at[i] == M.now ? kNearSome : 0) | (M.bad[i] == M.now ? kNearBad : 0);
-    }
-    raw[x] = (unsigned char)f;
+    for (int y = y0; y <= y1; ++y) f |= M.at[plane + (size_t)y * nx + x];
+    row[x] = f;
   }
   __syncthreads();
+  for (int y = y0 + (int)threadIdx.x; y <= y1; y += 256) {
+    const int readers = min(ny - 1, y + r) - max(0, y - r) + 1;
+    if (atomicAdd(&M.seen[p * ny + y], 1) == readers - 1) done[1 + atomicAdd(&done[0], 1)] = y;
+  }
   for (int x = (int)threadIdx.x; x < nx; x += 256) {
     unsigned f = 0;
-    for (int i = max(0, x - r); i <= min(nx - 1, x + r); ++i) f |= raw[i];
-    M.near[plane + (size_t)iy * nx + x] = (unsigned char)f;
+    for (int i = max(0, x - r); i <= min(nx - 1, x + r); ++i) f |= row[i];
+    M.near[plane + (size_t)iy * nx + x] = f;
+  }
+  __syncthreads();
+  for (int i = 0; i < done[0]; ++i) {
+    const int y = done[1 + i];
+    for (int x = (int)threadIdx.x; x < nx; x += 256) M.at[plane + (size_t)y * nx + x] = 0u;
+    if (threadIdx.x == 0) M.seen[p * ny + y] = 0;
   }
 }
 
@@ -1140,7 +1167,6 @@ Geo geo_of(const psoam_plan* P) {
   G.ht = Q.lt / 2;
   G.tlo = Q.tlo;
   G.nk = P->g.n_pulses;
-  G.r = P->R;
   G.in_scale = (float)(1.0 / plane_scale(Q.nx, Q.ny));
   return G;
 }
@@ -1150,13 +1176,12 @@ Geo geo_of(const psoam_plan* P) {
 int mark_planes(const psoam_plan* P) { return P->sw.diag ? P->g.n_pulses : 1; }
 Marks marks_b(const psoam_plan* P) {
   const SpecPlan& Q = *P->spec;
-  return Marks{Q.d_at_b, Q.d_bad_b, Q.d_near_b, Q.call_b, mark_planes(P)};
+  return Marks{Q.d_at_b, Q.d_near_b, Q.d_seen, mark_planes(P)};
 }
 Marks marks_r(const psoam_plan* P) {
   const SpecPlan& Q = *P->spec;
-  return Marks{Q.d_at_r, Q.d_bad_r, Q.d_near_r, Q.call_r, mark_planes(P)};
+  return Marks{Q.d_at_r, Q.d_near_r, Q.d_seen, mark_planes(P)};
 }
-
 FftDim dim_of(const SpecPlan& Q, int axis) {
   FftDim D;
   D.n = axis ? Q.nx : Q.ny;
@@ -1185,6 +1210,13 @@ hipError_t go(K kern, size_t blocks, int threads, size_t lds, hipStream_t s, Arg
   return hipGetLastError();
 }
 
+// widens the marks of the operand just made
+hipError_t reach(const psoam_plan* P, const Marks& M, hipStream_t s) {
+  const int ny = P->g.ny, nx = P->g.nx;
+  return go(spec_reach, (size_t)M.planes * ny, 256, sizeof(unsigned) * ((size_t)nx + 2 * P->R + 2), s, M,
+            ny, nx, P->R, gate_now());
+}
+
 GemmArgs gemm_args(const psoam_plan* P, bool adj) {
   const SpecPlan& Q = *P->spec;
   GemmArgs A;
@@ -1202,8 +1234,6 @@ GemmArgs gemm_args(const psoam_plan* P, bool adj) {
   A.ns = P->sw.ns;
   A.nz = P->g.nz;
   A.gate = gate_now();
-  A.clear = nullptr;
-  A.n_clear = 0;
   return A;
 }
 
@@ -1244,7 +1274,6 @@ hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s) {
   SpecPlan& Q = *P->spec;
   const Geo G = geo_of(P);
   const FftDim X = dim_of(Q, 1), Y = dim_of(Q, 0);
-  ++Q.call_b;
   const Marks M = marks_b(P);
   const size_t nb = (size_t)pulses_near(G.nk) * G.ny * col_tiles(G.hz);
   auto x = [&](auto kern) {
@@ -1262,35 +1291,28 @@ hipError_t spec_switch(const psoam_plan* P, const float* c, hipStream_t s) {
     default: SPEC_SW(kRndNone); break;
   }
 #undef SPEC_SW
-  SPEC_HIP(go(spec_reach, (size_t)M.planes * G.ny, 256, (size_t)G.nx, s, M, G.ny, G.nx, G.r, gate_now()));
+  SPEC_HIP(reach(P, M, s));
   return y_pass(spec_y<-1>, G.nk, G.hz, Q.d_x, Q.d_x, G, G.nyp, G.nyp, G.ny, G.nyp, Y, s);
 }
 
-// The reach of r's marks, beside the pass that made r: what follows only reads
-// it, so that H^T may run again on the same r.
-static hipError_t reach_r(const psoam_plan* P, hipStream_t s) {
-  const Geo G = geo_of(P);
-  const Marks M = marks_r(P);
-  return go(spec_reach, (size_t)M.planes * G.ny, 256, (size_t)G.nx, s, M, G.ny, G.nx, G.r, gate_now());
-}
-
+// (r's reach is found beside the pass that makes r: what follows only reads it,
+// so that H^T may run again on the same r)
 hipError_t spec_pack(const psoam_plan* P, const float* y, hipStream_t s) {
   SpecPlan& Q = *P->spec;
   const Geo G = geo_of(P);
   const FftDim X = dim_of(Q, 1);
-  ++Q.call_r;
   const Marks M = marks_r(P);
   const size_t nb = (size_t)G.nk * G.ny * col_tiles(G.ht);
   auto x = [&](auto kern) {
     return go(kern, nb, kFftThreads, row_lds(G.nxp), s, y, P->d_f16, (float2*)Q.d_r, G, X, M,
-              gate_now());
+              Q.d_mask, gate_now());
   };
   switch (rnd_of(P)) {
     case kRndBf16: SPEC_HIP(x(spec_x_pack<kRndBf16>)); break;
     case kRndF16: SPEC_HIP(x(spec_x_pack<kRndF16>)); break;
     default: SPEC_HIP(x(spec_x_pack<kRndNone>)); break;
   }
-  return reach_r(P, s);
+  return reach(P, M, s);
 }
 
 hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pmeas,
@@ -1302,11 +1324,7 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
   const int waves = (G.nk + 7) / 8;  // eight pulses a wave
   const Marks MB = marks_b(P);
   if (mode != 2) {
-    GemmArgs A = gemm_args(P, false);
-    if (mode != 0) {
-      A.clear = Q.d_at_r;  // d_bad_r follows it
-      A.n_clear = 2 * (size_t)MB.planes * G.ny * G.nx;
-    }
+    const GemmArgs A = gemm_args(P, false);
     const int zc = Q.lz / 16;
     if (zc <= 4) SPEC_HIP(go(spec_gemm_fwd<4>, (size_t)Q.nf, waves * 64, 0, s, A, Q.d_mask));
     else if (zc <= 8) SPEC_HIP(go(spec_gemm_fwd<8>, (size_t)Q.nf, waves * 64, 0, s, A, Q.d_mask));
@@ -1329,13 +1347,12 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
                   partial + nb, gate_now()));
     if (mode == 0)
       return go(spec_x_out, nb, kFftThreads, row_lds(G.nxp), s, (const float2*)Q.d_y, out, G, X, MB,
-                gate_now());
-    ++Q.call_r;
-    const Marks MR = marks_r(P);
+                Q.d_mask, gate_now());
+      const Marks MR = marks_r(P);
     const float beta = (float)yc_beta, inv = (float)(1.0 / (1.0 + yc_beta));
     auto r = [&](auto kern) {
       return go(kern, nb, kFftThreads, row_lds(G.nxp), s, (const float2*)Q.d_y, pmeas, P->d_f16,
-                (float2*)Q.d_r, yc, beta, inv, yc_first, partial, G, X, MB, MR, gate_now());
+                (float2*)Q.d_r, yc, beta, inv, yc_first, partial, G, X, MB, MR, Q.d_mask, gate_now());
     };
     const bool rec = yc != nullptr;
     switch (rnd_of(P)) {
@@ -1343,7 +1360,7 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
       case kRndF16: SPEC_HIP(rec ? r(spec_x_resid<kRndF16, true>) : r(spec_x_resid<kRndF16, false>)); break;
       default: SPEC_HIP(rec ? r(spec_x_resid<kRndNone, true>) : r(spec_x_resid<kRndNone, false>)); break;
     }
-    return reach_r(P, s);
+    return reach(P, MR, s);
   }
   const Marks MR = marks_r(P);
   SPEC_HIP(y_pass(spec_y<-1>, G.nk, G.ht, Q.d_r, Q.d_y, G, G.ny, G.nyp, G.ny, G.nyp, Y, s));
@@ -1509,17 +1526,16 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   if (rate) alloc(&Q.d_rate, sizeof(float) * P->v_elems());
   alloc(&Q.d_twx, sizeof(float2) * X.n);
   alloc(&Q.d_twy, sizeof(float2) * Y.n);
-  // marks of b and of r: two words and a byte per position and plane
+  // marks and reach of b and of r, a word each per position and plane
   const size_t planes = mark_planes(P);
-  const size_t mb = 2 * planes * grid * (2 * sizeof(unsigned) + 1);
+  const size_t mb = sizeof(unsigned) * planes * (4 * grid + (size_t)g.ny);
   alloc(&Q.d_marks, mb);
   if (ok) {
     Q.d_at_b = (unsigned*)Q.d_marks;
-    Q.d_bad_b = Q.d_at_b + planes * grid;
-    Q.d_at_r = Q.d_bad_b + planes * grid;
-    Q.d_bad_r = Q.d_at_r + planes * grid;
-    Q.d_near_b = (unsigned char*)(Q.d_bad_r + planes * grid);
+    Q.d_at_r = Q.d_at_b + planes * grid;
+    Q.d_near_b = Q.d_at_r + planes * grid;
     Q.d_near_r = Q.d_near_b + planes * grid;
+    Q.d_seen = (int*)(Q.d_near_r + planes * grid);
   }
   alloc(&d_p, pb);
   alloc(&d_t0, sizeof(int) * ntab);
@@ -1537,8 +1553,8 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
     upload(Q.d_twy, Y.n);
     check(hipMemcpy(Q.d_mask, mask.data(), sizeof(unsigned) * ntt, hipMemcpyHostToDevice));
     check(hipMemcpy(d_t0, t0, sizeof(int) * ntab, hipMemcpyHostToDevice));
-    // the marks start below every call's number; the table's spare blocks are
-    // read and not used
+    // nothing marked, nothing in reach; the table's spare blocks are read and
+    // not used
     check(hipMemsetAsync(Q.d_marks, 0, mb, stream));
     check(hipMemsetAsync(Q.d_tf + (nf * nblk) * 512, 0, 1024 * sizeof(float), stream));
     check(hipMemsetAsync(Q.d_ta + (nf * nblk) * 512, 0, 1024 * sizeof(float), stream));

@@ -304,6 +304,60 @@ def test_weak_region_far_from_a_strong_one(amp, monkeypatch):
     assert float(far.max()) <= 1e-6 * float(out[0].abs().max())
 
 
+@pytest.mark.parametrize("species", [True, False])
+@pytest.mark.parametrize("bad", [float("nan"), -float("inf")])
+@pytest.mark.parametrize("nz, nt, lag", [(50, 83, 9), (33, 61, 0), (256, 300, 20)])
+def test_bad_values_stay_in_their_tiles(nz, nt, lag, bad, species, monkeypatch):
+    """A band that meets each depth in a few samples: a non-finite value reaches
+    the 16-wide tiles of samples (depths) that entries join to its own tile, in
+    its footprint, and every other output is what it was; so do nonzero values
+    among zeros."""
+    torch = torch_cuda()
+    import paper_2510_23739_amd as pk
+    f, w, ny, nx, k = 5, 3, 11, 14, 3
+    rng = np.random.default_rng(nz)
+    t0 = np.broadcast_to((np.arange(nz) + lag)[:, None, None], (nz, f, f)).astype(np.int32)
+    taps = rng.uniform(0.5, 1.0, (nz, f, f, w)).astype(np.float32)
+    monkeypatch.setenv("PSOAM_SPECTRAL", "1")
+    if species:
+        plan = pk.Plan(nx, ny, nz, k, nt, f, synth.phi_depth(nz), synth.species(2), t0, taps, prec="fp32")
+    else:
+        plan = pk.Plan.acoustic(nx, ny, nz, k, nt, f, t0, taps, prec="fp32")
+    say(f"[spectral] tiles {nz} {nt} {bad} species {species}")
+    # tiles joined by an entry: joins[depth tile][sample tile]
+    joins = torch.zeros((nz + 15) // 16, (nt + 15) // 16, dtype=torch.bool)
+    for z in range(nz):
+        for t in range(z + lag, min(z + lag + w, nt)):
+            joins[z // 16, t // 16] = True
+    joins = joins.cuda()
+    for apply, n_in, n_out, j, shape in ((plan.apply_A, nz, nt, joins, plan.c_shape),
+                                         (plan.apply_AT, nt, nz, joins.t(), plan.y_shape)):
+        g = torch.Generator(device="cuda").manual_seed(3)
+        v = torch.randn(shape, device="cuda", generator=g)
+        for at in (0, 17, n_in - 1):
+            reach = j[at // 16].repeat_interleave(16)[:n_out]
+            # a bad concentration makes every pulse's S c bad, its other species' part too
+            clean, dirty = v.clone(), v.clone()
+            clean[slice(None) if species and apply == plan.apply_A else 1, 4, 6, at] = 0.0
+            dirty[1, 4, 6, at] = bad
+            ref, out = apply(clean), apply(dirty)
+            near = torch.zeros(out.shape[1:], dtype=torch.bool, device="cuda")
+            near[2:7, 4:9] = reach
+            assert torch.equal(out[:, ~near], ref[:, ~near])
+            if species:
+                assert not torch.isfinite(out[:, near]).any()
+            else:
+                assert not torch.isfinite(out[1, near]).any() and torch.isfinite(out[[0, 2]]).all()
+            zero = torch.zeros_like(v)
+            zero[1, 4, 6, at] = 1.0
+            out = apply(zero)
+            assert (out[:, ~near] == 0).all()
+            # (a sample before or past the band has no entry, its tile may)
+            met = at + lag < nt if n_in == nz else lag <= at < nz + lag + w - 1
+            assert met == bool((out != 0).any())
+    plan.close()
+
+
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("k", [4, 5])
 def test_pulse_volumes_stay_apart(k, bad, monkeypatch):
@@ -386,6 +440,33 @@ def test_replayed_calls_forget(monkeypatch):
         assert torch.equal(torch.nan_to_num(plan.apply_A(c, a), -1.0), torch.nan_to_num(ra, -1.0)), i
         assert torch.equal(torch.nan_to_num(plan.apply_AT(y, g), -1.0), torch.nan_to_num(rg, -1.0)), i
         assert torch.isfinite(ra).all() == torch.isfinite(c).all()
+    plan.close()
+
+
+def test_an_objective_leaves_no_marks(monkeypatch):
+    """A residual whose H^T never runs (an objective) leaves its marks to no
+    later A^T, replayed from a graph or not."""
+    torch = torch_cuda()
+    shape = (24, 22, 10, 5, 30, 7, 2, False)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    plan = _plan(monkeypatch, "1", shape, t0, taps, phi, sp, "fp32")
+    y, g = torch.zeros(plan.y_shape, device="cuda"), torch.zeros(plan.c_shape, device="cuda")
+    y[1, 17, 12, 9] = 1.0
+    s = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    plan.apply_AT(y, g)
+    with torch.cuda.graph(graph, stream=s):
+        plan.apply_AT(y, g, stream=s)
+    p = torch.from_numpy(rng.standard_normal(plan.y_shape).astype(np.float32)).cuda()
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        first = g.clone()
+        assert (first != 0).any() and (first[:, :, :9] == 0).all()
+        # the trace's last residual is the operand of no H^T
+        plan.solve(p, k1=2, k2=1, alpha1=1e-3, trace=True)
+        assert torch.equal(plan.apply_AT(y), first)
+        plan.solve(p, k1=2, k2=1, alpha1=1e-3, trace=True)
     plan.close()
 
 
