@@ -365,7 +365,8 @@ def scale_runs(torch, pk):
         t_H = time_events(torch, lambda: plan.band_only(0, y), reps)
         rows[prec] = {"apply_A_ms": t_A, "apply_AT_ms": t_AT,
                       "isolated_applies_per_s": 1e3 / (t_A + t_AT), "H_kernel_ms": t_H,
-                      "H_alg_frac_of_peak": flops / (t_H * 1e-3) / 1e12 / PEAK_TFLOPS[prec],
+                      "H_alg_frac_of_peak": alg_frac(flops, t_H, prec, info),
+                      "form": "spectral" if info["spectral"] else "direct",
                       "staged_rows": info["lds_rows"]}
         plan.close()
         torch.cuda.empty_cache()
@@ -507,6 +508,12 @@ def sampled_A_errors(cfg, t0, taps, phi, sp, c_true, samples, scans):
     return {q: oracle.rel_err(y_g, y_s) for q, y_g in samples.items()}, S
 
 
+def alg_frac(flops, ms, prec, info):
+    """The band contraction's algorithmic rate over the matrix cores' peak; a
+    spectral plan does not run that contraction (None)."""
+    return None if info["spectral"] else flops / (ms * 1e-3) / 1e12 / PEAK_TFLOPS[prec]
+
+
 def per_prec_rows(runs, flops, cfg):
     """The JSON rows of the precisions timed on one workload."""
     fp32 = runs.get("fp32")
@@ -518,8 +525,9 @@ def per_prec_rows(runs, flops, cfg):
             "apply_A_ms": r["t_A"], "apply_AT_ms": r["t_AT"],
             "isolated_applies_per_s": 1e3 / (r["t_A"] + r["t_AT"]),
             "H_kernel_ms": r["t_H"], "HT_kernel_ms": r["t_HT"],
-            "H_alg_frac_of_peak": flops / (r["t_H"] * 1e-3) / 1e12 / PEAK_TFLOPS[q],
-            "HT_alg_frac_of_peak": flops / (r["t_HT"] * 1e-3) / 1e12 / PEAK_TFLOPS[q],
+            "H_alg_frac_of_peak": alg_frac(flops, r["t_H"], q, r["info"]),
+            "HT_alg_frac_of_peak": alg_frac(flops, r["t_HT"], q, r["info"]),
+            "form": "spectral" if r["info"]["spectral"] else "direct",
             "fista_iterations": cfg.k1,
         }
         if "solve_s" in r:
@@ -722,16 +730,15 @@ def main(argv=None):
     traffic, traffic_src = profiled_traffic(f"{'band16_lds_adj' if dom == 'HT' else 'band16_lds_H'}"
                                             f"_{cfg.name}_{args.prec}_hbm.md")
     info = res["info"]
-    # a rate of executed tile products above the peak: the plan does not run the
-    # band tiles but transforms and one product per frequency, which HBM bounds;
-    # the rate is then that of the bytes H (H^T) cannot do without: the operand
-    # of one side in float32 and the result of the other
-    executed = 2.0 * info["executed_macs"][dom == "HT"] * cfg.n_pulses * cfg.nx * cfg.ny
+    # a spectral plan does not run the band tiles but transforms and one product
+    # per frequency, which HBM bounds; the rate is then that of the bytes H (H^T)
+    # cannot do without: the operand of one side in float32 and the result of the
+    # other
     roof = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
             "frac": achieved / peak, "traffic": traffic,
             "kernel": f"{kname}, {args.prec}: algorithmic flops 2*K*sum over offsets of "
                       f"band nonzeros x in-grid scans = {flops / 1e9:.1f} GFLOP per launch"}
-    if executed / (t_dom * 1e-3) / 1e12 > peak:
+    if info["spectral"]:
         nbytes = 4.0 * cfg.n_pulses * cfg.nx * cfg.ny * (cfg.nz + cfg.nt)
         if dom == "HT":
             nbytes = 4.0 * cfg.nx * cfg.ny * (cfg.n_species * cfg.nz + cfg.n_pulses * cfg.nt)

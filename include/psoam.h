@@ -404,12 +404,19 @@ typedef struct {
   int64_t useful_macs[2];
   int64_t chunks[2];
   int64_t executed_macs[2];
-  int64_t operand_bytes[2];  /* padded operand buffer of H (0) and H^T (1) */
+  int64_t operand_bytes[2];  /* operand buffer of H (0) and H^T (1): padded volumes,
+                                or the operands' spectra of a spectral plan */
   int64_t lds_bytes[2];      /* LDS per workgroup of the staged kernel, 0 if not used */
   int32_t lds_rows[2];       /* output rows per workgroup of the staged kernel */
 } psoam_plan_info;
 
 int psoam_plan_stats(const psoam_plan* plan, psoam_plan_info* info);
+
+/* The form in which the plan applies H and H^T (it depends on the memory that was
+ * free at plan creation): *spectral 1 or 0, and *bytes the device memory of the
+ * spectral form's spectra and tables (0 in the direct form).  Separable plans:
+ * of their contraction.  EINVAL: null pointer. */
+int psoam_plan_form(const psoam_plan* plan, int32_t* spectral, int64_t* bytes);
 
 /* Launch only the band-contraction kernel of H (dir 0: writes y) or of
  * S^T H^T (dir 1: writes c) on the padded operand the plan holds from its

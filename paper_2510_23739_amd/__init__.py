@@ -174,9 +174,12 @@ class Plan:
     def stats(self) -> dict:
         info = _lib.PlanInfo()
         check(load().psoam_plan_stats(self.handle, C.byref(info)))
-        return {k: [int(getattr(info, k)[0]), int(getattr(info, k)[1])]
-                for k in ("useful_macs", "chunks", "executed_macs", "operand_bytes", "lds_bytes",
-                          "lds_rows")}
+        out = {k: [int(getattr(info, k)[0]), int(getattr(info, k)[1])]
+               for k in ("useful_macs", "chunks", "executed_macs", "operand_bytes", "lds_bytes",
+                         "lds_rows")}
+        spectral, nbytes = C.c_int32(), C.c_int64()
+        check(load().psoam_plan_form(self.handle, C.byref(spectral), C.byref(nbytes)))
+        return dict(out, spectral=spectral.value, spectral_bytes=nbytes.value)
 
     def band_only(self, direction: int, out, stream=None):
         """Launch only the band kernel (0: H -> y, 1: S^T H^T -> c) on the

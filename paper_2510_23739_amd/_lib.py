@@ -92,6 +92,7 @@ EXPORTS = {
                                     C.POINTER(C.c_void_p), C.POINTER(SolveOpts),
                                     C.POINTER(SolveStats), C.c_void_p]),
     "psoam_plan_stats": (C.c_int, [C.c_void_p, C.POINTER(PlanInfo)]),
+    "psoam_plan_form": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int64)]),
     "psoam_band_only": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
     "psoam_last_error": (C.c_char_p, []),
 }

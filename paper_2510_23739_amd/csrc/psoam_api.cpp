@@ -1425,8 +1425,16 @@ int psoam_plan_stats(const psoam_plan* plan, psoam_plan_info* info) {
     info->lds_bytes[d] = staged ? (int64_t)T[d]->lds_bytes : 0;
     info->lds_rows[d] = staged ? T[d]->rows : 0;
   }
-  info->operand_bytes[0] = (int64_t)plan->bq_bytes;
-  info->operand_bytes[1] = (int64_t)plan->rq_bytes;
+  info->operand_bytes[0] = (int64_t)(plan->spec ? plan->spec->xb : plan->bq_bytes);
+  info->operand_bytes[1] = (int64_t)(plan->spec ? plan->spec->rb : plan->rq_bytes);
+  return PSOAM_OK;
+}
+
+int psoam_plan_form(const psoam_plan* plan, int32_t* spectral, int64_t* bytes) {
+  if (!plan || !spectral || !bytes) return fail(PSOAM_EINVAL, "plan_form: NULL argument");
+  if (plan->inner) plan = plan->inner;
+  *spectral = plan->spec ? 1 : 0;
+  *bytes = plan->spec ? (int64_t)plan->spec->bytes : 0;
   return PSOAM_OK;
 }
 

@@ -112,6 +112,8 @@ struct SpecPlan {
   int tlo = 0, lt = 0;    // samples transformed: first, count (multiples of 16)
   size_t nf = 0;          // frequencies of the half plane
   int nblk = 0;           // 16 x 16 blocks of (t, z) per frequency
+  size_t xb = 0, rb = 0;  // bytes of d_x, d_r
+  size_t bytes = 0;       // of all that follows
   void* d_x = nullptr;    // [K][ny][nx][lz / 2] complex: spectrum of S c
   void* d_y = nullptr;    // [K][ny][nx][lt / 2] complex: spectrum of y or r
   void* d_r = nullptr;    // [K][Ny][nx][lt / 2] complex: r transformed along x (H^T's operand)

@@ -1499,6 +1499,8 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   Q.tlo = 16 * tb0;
   Q.nf = nf;
   Q.nblk = nblk;
+  Q.xb = xb;
+  Q.rb = rb;
   double2* d_p = nullptr;
   int* d_t0 = nullptr;
   float* d_taps = nullptr;
@@ -1530,6 +1532,8 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   const size_t planes = mark_planes(P);
   const size_t mb = sizeof(unsigned) * planes * (4 * grid + (size_t)g.ny);
   alloc(&Q.d_marks, mb);
+  Q.bytes = xb + yb + rb + gb + 2 * tb + mb + sizeof(float2) * ((size_t)X.n + Y.n) +
+            sizeof(unsigned) * ntt + (rate ? sizeof(float) * P->v_elems() : 0);
   if (ok) {
     Q.d_at_b = (unsigned*)Q.d_marks;
     Q.d_at_r = Q.d_at_b + planes * grid;

@@ -537,3 +537,27 @@ def test_pulse_planes_beyond_four_gibibytes(monkeypatch):
         plan.close()
     for a, b in zip(*out):
         assert float((a - b).norm() / a.norm()) <= 2 * TOL_OP["fp32"]
+
+
+@pytest.mark.parametrize("separable", [False, True])
+def test_plan_tells_its_form(separable, monkeypatch):
+    """stats() names the form a plan runs in and what it holds: the memory that
+    the card loses to a spectral plan over a direct one, within its smaller
+    buffers and the allocator's granules."""
+    torch = torch_cuda()
+    shape = (90, 80, 33, 9, 64, 11, 2, False)
+    rng, t0, taps, phi, sp = _inputs(shape)
+    took = []
+    for form in "01":
+        free = torch.cuda.mem_get_info()[0]
+        plan = _plan(monkeypatch, form, shape, t0, taps, phi, sp, "fp32", separable=separable)
+        took.append(free - torch.cuda.mem_get_info()[0])
+        st = plan.stats()
+        say(f"[spectral] form {form}: {st}, {took[-1]} bytes taken")
+        assert st["spectral"] == int(form) and min(st["operand_bytes"]) > 0
+        if form == "0":
+            assert st["spectral_bytes"] == 0
+        else:
+            assert sum(st["operand_bytes"]) < st["spectral_bytes"] <= took[1] + (16 << 20)
+            assert st["spectral_bytes"] >= took[1] - (64 << 20)
+        plan.close()
