@@ -451,20 +451,25 @@ typedef struct {
  * the report's rows are those its direct form would have), times each band
  * kernel's solver form on `stream` (HIP events, one warm-up and three timed
  * launches on the operands as allocated),
- * times the TV dual step on the plan's grid with each tile shape of the
+ * times the TV dual step as a launch of its own (what a plan that takes several
+ * steps a launch keeps for the step left over) with each tile shape of the
  * kernel's list (8x8x32 with 512 threads, 4x8x32/256, 4x16x32/512,
  * 4x8x64/512, 8x8x32/1024; one warm-up and ten steps), and returns the plan
  * with the fastest H, H^T and TV step.  Rows, loader waves and TV tiles do
  * not change results (the same products and sums in the same order);
  * another H^T operand shift or the other FP32 kernel can regroup the band's
- * entries and so the summation order (rounding-level differences).  The
+ * entries and so the summation order (rounding-level differences), and the
+ * other form rounds as described above.  The
  * choice is cached per process and on disk, keyed by the device
  * (architecture and compute units), the geometry, the precision and a hash
  * of the impulse-response table; the disk cache is the file named by the
  * environment variable PSOAM_TUNE_CACHE (empty: no disk cache), else
  * $HOME/.cache/psoam/tune.txt, one line per choice, appended after each
  * tuning (a file that cannot be read or written is skipped silently).  A
- * call served from a cache only builds the plan.  Separable plans have
+ * call served from a cache only builds the plan.  The form is part of the
+ * choice only where both were timed, and a choice made while the environment
+ * fixed the form is not cached, one made while memory was short for the
+ * spectral form not on disk.  Separable plans have
  * nothing to tune and are built directly.  For callers who create a plan
  * once and apply it many times: tuning builds up to seven plans (about
  * 0.25 s at 128 x 128 x 64).  `report` may be null.  Errors as

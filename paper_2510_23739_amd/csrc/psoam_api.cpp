@@ -851,12 +851,12 @@ namespace {
 // shift, H's loader waves, and the tile of the TV dual step.  Measured per
 // process and cached in memory and on disk by device, geometry, precision
 // and a hash of the impulse-response table.
-constexpr int kTuneVersion = 5;  // bump when the kernels or the choices change meaning
+constexpr int kTuneVersion = 6;  // bump when the kernels or the choices change meaning
 
 struct Shape {
   int h_rows = 0, ht_rows = 0, tsh = 0, h_loadw = 0, tv = 0;
   int runs_h = 0, runs_ht = 0;  // FP32: run-packed (1) or per-tile (0) kernel
-  int spec = 0;                 // spectral (1) or direct (0) form
+  int spec = 0;                 // spectral (1) or direct (0) form; -1: by the plan's rules
   bool operator==(const Shape& o) const {
     return h_rows == o.h_rows && ht_rows == o.ht_rows && tsh == o.tsh && h_loadw == o.h_loadw &&
            tv == o.tv && runs_h == o.runs_h && runs_ht == o.runs_ht && spec == o.spec;
@@ -1104,31 +1104,56 @@ int create_tuned(const psoam_geom* g, const psoam_species* sp, const float* phi,
   std::vector<std::pair<Shape, int>> alts;
   // the other form of the band operator, with its own rules' shapes (compared
   // with S's pass: the spectral form transforms its operand there)
-  double h_full = 0.0;
+  bool both = false;            // both forms were timed
+  bool little = P->spec_short;  // or one was refused for want of memory
   if (base.h_rows || fp32) {
-    rc = time_band(P, 0, s, &h_full, true);
-    if (rc != PSOAM_OK) {
-      free_plan(P);
-      return rc;
-    }
     Shape o = base;
     o.spec = base.spec ? 0 : 1;
     // FP32 keeps the form that errs less (see the plan's rule)
-    if (!(o.spec && fp32 && g->f < kSpecMinFp32F)) alts.push_back({o, 3});
+    if (!(o.spec && fp32 && g->f < kSpecMinFp32F)) {
+      double h_full = 0.0, ms = 0.0, ms2 = 0.0, full = 0.0;
+      psoam_plan* Q = nullptr;
+      rc = time_band(P, 0, s, &h_full, true);
+      if (rc == PSOAM_OK) rc = build_shaped(g, sp, phi, t0, taps, sir_w, prec, s, o, &Q);
+      if (rc == PSOAM_OK) {
+        both = shape_of(Q) == o;
+        little |= Q->spec_short;
+        if (both) {
+          rc = time_band(Q, 0, s, &ms);
+          if (rc == PSOAM_OK) rc = time_band(Q, 1, s, &ms2);
+          if (rc == PSOAM_OK) rc = time_band(Q, 0, s, &full, true);
+          ++r.candidates;
+        }
+        free_plan(Q);
+      }
+      if (rc != PSOAM_OK) {
+        free_plan(P);
+        return rc;
+      }
+      // (a tenth at least: 16-bit operands are rounded from sums that differ
+      // in their last bits between the forms)
+      if (both && ms <= h_best && ms2 <= ht_best && full + ms2 < 0.9 * (h_full + ht_best)) {
+        h_best = ms;
+        ht_best = ms2;
+        best.spec = o.spec;
+      }
+    }
   }
-  if (base.h_rows && !base.spec)
+  // (the spectral form has no launch shapes of its own to try)
+  if (base.h_rows && !best.spec)
     for (int rows : {4, 8, 12})
       for (int lw : {0, 1})
         if ((rows != base.h_rows || lw != base.h_loadw) && !(rows != 8 && lw == 1))
           alts.push_back({Shape{rows, base.ht_rows, base.tsh, lw, base.tv}, 0});
-  if (base.ht_rows && !base.spec)
+  if (base.ht_rows && !best.spec)
     for (int rows : {4, 8, 12})
       for (int tsh : {0, 4})
         if (rows != base.ht_rows || tsh != base.tsh)
           alts.push_back({Shape{base.h_rows, rows, tsh, base.h_loadw, base.tv}, 1});
-  if (fp32 && !base.spec && (base.runs_h || base.runs_ht)) {
+  if (fp32 && !best.spec && (base.runs_h || base.runs_ht)) {
     // the other FP32 kernel, for both directions at once (timed on each)
     Shape o = base;
+    o.spec = 0;
     o.runs_h = base.runs_h ? 0 : 1;
     o.runs_ht = base.runs_ht ? 0 : 1;
     alts.push_back({o, 2});
@@ -1137,29 +1162,15 @@ int create_tuned(const psoam_geom* g, const psoam_species* sp, const float* phi,
     psoam_plan* Q = nullptr;
     if ((rc = build_shaped(g, sp, phi, t0, taps, sir_w, prec, s, a.first, &Q))) break;
     const Shape got = shape_of(Q);
-    double ms = 0.0, ms2 = 0.0, full = 0.0;
+    double ms = 0.0, ms2 = 0.0;
     if (got == a.first) {  // it fitted
-      rc = time_band(Q, a.second >= 2 ? 0 : a.second, s, &ms);
-      if (rc == PSOAM_OK && a.second >= 2) rc = time_band(Q, 1, s, &ms2);
-      if (rc == PSOAM_OK && a.second == 3) rc = time_band(Q, 0, s, &full, true);
+      rc = time_band(Q, a.second == 2 ? 0 : a.second, s, &ms);
+      if (rc == PSOAM_OK && a.second == 2) rc = time_band(Q, 1, s, &ms2);
       ++r.candidates;
     }
     free_plan(Q);
     if (rc != PSOAM_OK) break;
     if (!(got == a.first)) continue;
-    if (a.second == 3) {
-      // it comes first: h_best and ht_best are still the base's
-      // (a tenth at least: 16-bit operands are rounded from sums that differ
-      // in their last bits between the forms)
-      if (ms <= h_best && ms2 <= ht_best && full + ms2 < 0.9 * (h_full + ht_best)) {
-        h_best = ms;
-        ht_best = ms2;
-        best.spec = a.first.spec;
-        // the spectral form has no launch shapes of its own to try
-        if (best.spec) break;
-      }
-      continue;
-    }
     if (a.second == 2) {
       if (ms < h_best) {
         h_best = ms;
@@ -1191,9 +1202,15 @@ int create_tuned(const psoam_geom* g, const psoam_species* sp, const float* phi,
   r.ht_ms = ht_best;
   r.tv_ms = tv_best;
   {
+    // a form that was not measured against the other is no choice to keep, and
+    // one that the environment or a full card decided is none of this table's
+    Shape keep = best;
+    if (!both) keep.spec = -1;
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune_cache[key] = best;
-    disk_store(key, best);
+    if (!form_forced()) {
+      g_tune_cache[key] = keep;
+      if (!little) disk_store(key, keep);
+    }
   }
   if (best.h_rows == base.h_rows && best.ht_rows == base.ht_rows && best.tsh == base.tsh &&
       best.h_loadw == base.h_loadw && best.runs_h == base.runs_h && best.runs_ht == base.runs_ht &&

@@ -176,6 +176,7 @@ struct psoam_plan {
   // set: H and H^T run in the spectral form, and fwd / adj hold only the
   // direct form's figures
   psoam::SpecPlan* spec = nullptr;
+  bool spec_short = false;  // the spectral form was refused for want of memory
   // solver scratch (allocated on first use, grown as needed)
   psoam::Workspace solve_ws;
   double* d_partial = nullptr;  // per-wave / per-block FP64 partial sums
@@ -232,6 +233,8 @@ namespace psoam {
 void set_tune_choice(int rows_fwd, int rows_adj, int tsh, int loadw_fwd, int runs_fwd = -1,
                      int runs_adj = -1, int spectral = -1);
 void clear_tune_choice();
+// the environment fixes the form of the band operator
+bool form_forced();
 
 // Device stop gate of the calling thread: while a solve with device-side
 // stopping tests enqueues its iterations, every kernel launched on this

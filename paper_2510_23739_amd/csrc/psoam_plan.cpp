@@ -653,19 +653,29 @@ static int adj_window_octets(const psoam_geom& g, const int32_t* t0, const float
   return best;
 }
 
-// 1 spectral, 0 direct, -1 the sizes decide.  PSOAM_SPECTRAL=1 or 0 forces one
-// (tests and timing compare both); the autotuner's choice comes next; any
-// switch of the direct form's kernels means that form.
-static int spectral_choice() {
-  if (const char* e = std::getenv("PSOAM_SPECTRAL")) {
-    if (e[0] == '0') return 0;
-    if (e[0] == '1') return 1;
-  }
-  if (g_tune.spectral >= 0) return g_tune.spectral;
+// The form that the environment asks for: 1 spectral, 0 direct, -1 neither.
+// PSOAM_SPECTRAL=1 or 0 forces one (tests and timing compare both).
+static int spectral_env() {
+  const char* e = std::getenv("PSOAM_SPECTRAL");
+  return e && (e[0] == '0' || e[0] == '1') ? e[0] - '0' : -1;
+}
+
+// any switch of the direct form's kernels means that form
+static bool direct_env() {
   for (const char* n : {"PSOAM_BAND_GLOBAL", "PSOAM_LDS_ROWS", "PSOAM_LDS_LOADW", "PSOAM_HALF_BLOCK",
                         "PSOAM_ADJ_SHIFT", "PSOAM_FP32_RUNS", "PSOAM_EIR_PACK"})
-    if (std::getenv(n)) return 0;
-  return -1;
+    if (std::getenv(n)) return true;
+  return false;
+}
+
+bool form_forced() { return spectral_env() >= 0 || direct_env(); }
+
+// 1 spectral, 0 direct, -1 the sizes decide: the environment, then the
+// autotuner's choice
+static int spectral_choice() {
+  if (const int e = spectral_env(); e >= 0) return e;
+  if (g_tune.spectral >= 0) return g_tune.spectral;
+  return direct_env() ? 0 : -1;
 }
 
 // The refined form's low-order parts, as its packing applies them: a group

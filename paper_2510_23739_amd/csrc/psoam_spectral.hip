@@ -1460,7 +1460,10 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   const size_t need = xb + yb + rb + gb + 2 * tb + pb;
   // the direct form needs about the operands alone; this one stays where a
   // user's own arrays still have most of the card
-  if (need > free_b / 3) return false;
+  if (need > free_b / 3) {
+    P->spec_short = true;
+    return false;
+  }
   if (!force) {
     // Predicted time of one A and one A^T: the launches, and the bytes of all
     // passes at 4.0 TB/s (a fit to 400 random geometries: half of the
@@ -1512,6 +1515,7 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
       (void)hipGetLastError();
       *p = nullptr;
       ok = false;
+      P->spec_short = true;
     }
   };
   auto check = [&](hipError_t e) {

@@ -66,3 +66,15 @@ def ragged_cfg(seed=0):
     phi = rng.uniform(0.2, 1.0, size=(cfg.ny, cfg.nx, cfg.nz)).astype(np.float32)
     sp = synth.species(3, gamma=1.0)
     return cfg, t0, taps, phi, sp
+
+
+def leave_free(torch, nbytes):
+    """Tensors that hold the card's memory but for about nbytes (64 MiB either
+    way); None where it has less."""
+    torch.cuda.empty_cache()
+    rest = []
+    while (more := torch.cuda.mem_get_info()[0] - nbytes) > 64 << 20:
+        if len(rest) == 8:
+            return None
+        rest.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
+    return rest if rest and more > -(64 << 20) else None
