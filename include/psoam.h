@@ -190,6 +190,13 @@ size_t psoam_prox_tv_ws_bytes(const psoam_plan* plan);
 int psoam_prox_tv(const psoam_plan* plan, float* x, const float* z, float theta,
                   int32_t n_inner, int32_t nonneg, void* ws, void* stream);
 
+/* psoam_prox_tv with the size of ws: one that holds three dual buffers and not
+ * four (3 sets of 3 S Ny Nx Nz floats, each on 256 bytes; psoam_prox_tv_ws_bytes
+ * before it grew) takes one dual step a launch, the same result bit for bit;
+ * EINVAL below that. */
+int psoam_prox_tv_sized(const psoam_plan* plan, float* x, const float* z, float theta,
+                        int32_t n_inner, int32_t nonneg, void* ws, size_t ws_bytes, void* stream);
+
 /* psoam_prox_tv for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same dual iteration and result, bit for bit, with its three or

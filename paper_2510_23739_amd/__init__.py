@@ -215,8 +215,10 @@ class Plan:
         nbytes = int(load().psoam_prox_tv_ws_bytes(self.handle))
         if ws is None:
             ws = torch.empty(nbytes // 4 + 64, dtype=torch.float32, device=z.device)
-        check(load().psoam_prox_tv(self.handle, _ptr(x), _ptr(z), float(theta), int(n_inner),
-                                   1 if nonneg else 0, _ptr(ws), _stream(stream)))
+        # what is behind ws's pointer
+        nbytes = ws.untyped_storage().nbytes() - ws.storage_offset() * ws.element_size()
+        check(load().psoam_prox_tv_sized(self.handle, _ptr(x), _ptr(z), float(theta), int(n_inner),
+                                         1 if nonneg else 0, _ptr(ws), nbytes, _stream(stream)))
         return x
 
     def prox_tv_noalloc(self, z, theta: float, n_inner: int, nonneg: bool = False, x=None,

@@ -84,6 +84,8 @@ EXPORTS = {
                                 C.c_float, C.c_int32, C.c_void_p, C.c_void_p]),
     "psoam_prox_tv": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_float, C.c_int32,
                                 C.c_int32, C.c_void_p, C.c_void_p]),
+    "psoam_prox_tv_sized": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_float, C.c_int32,
+                                      C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]),
     "psoam_prox_tv_noalloc": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_float, C.c_int32,
                                         C.c_int32, C.c_void_p]),
     "psoam_solve": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(SolveOpts),

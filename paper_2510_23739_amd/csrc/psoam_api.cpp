@@ -1315,6 +1315,11 @@ size_t psoam_prox_tv_ws_bytes(const psoam_plan* plan) {
 
 int psoam_prox_tv(const psoam_plan* plan, float* x, const float* z, float theta,
                   int32_t n_inner, int32_t nonneg, void* ws, void* stream) {
+  return psoam_prox_tv_sized(plan, x, z, theta, n_inner, nonneg, ws, psoam_prox_tv_ws_bytes(plan), stream);
+}
+
+int psoam_prox_tv_sized(const psoam_plan* plan, float* x, const float* z, float theta,
+                        int32_t n_inner, int32_t nonneg, void* ws, size_t ws_bytes, void* stream) {
   if (int rc = check_plan(plan)) return rc;
   if (!x || !z || !ws) return fail(PSOAM_EINVAL, "prox_tv: NULL argument");
   if (!(theta >= 0.0f) || !std::isfinite(theta))
@@ -1327,7 +1332,10 @@ int psoam_prox_tv(const psoam_plan* plan, float* x, const float* z, float theta,
   float* u1 = align(u0 + 3 * sv);
   float* u2 = align(u1 + 3 * sv);
   float* u3 = align(u2 + 3 * sv);
-  float* u[4] = {u0, u1, u2, u3};
+  auto holds = [&](float* end) { return (size_t)((char*)end - (char*)ws) <= ws_bytes; };
+  if (!holds(u2 + 3 * sv))
+    return fail(PSOAM_EINVAL, "prox_tv: ws is smaller than psoam_prox_tv_ws_bytes says");
+  float* u[4] = {u0, u1, u2, holds(u3 + 3 * sv) ? u3 : nullptr};
   // z and x may alias: keep z intact until the final map, which reads z[v] only at v
   return tv_prox_core(plan, x, z, theta, n_inner, nonneg ? 1 : 0, 0.0f, u, nullptr, false,
                       nullptr, S(stream));
