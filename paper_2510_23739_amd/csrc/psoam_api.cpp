@@ -67,13 +67,22 @@ struct SolveBufs {
 
 int ensure_solve_ws(psoam_plan* P, SolveBufs& B) {
   const size_t sv = P->c_elems();
-  const size_t need = sizeof(float) * sv * (5 + 12 + 1) + 256 * 16;
+  // the fourth dual buffer, for several dual steps a launch, where there is
+  // memory for it
+  const size_t need = sizeof(float) * sv * (5 + 9 + 1) + 256 * 16;
+  const size_t more = need + sizeof(float) * sv * 3;
   if (P->solve_ws.bytes < need) {
     if (P->solve_ws.base) PSOAM_HIP(hipFree(P->solve_ws.base));
     P->solve_ws.base = nullptr;
     P->solve_ws.bytes = 0;
-    PSOAM_HIP(hipMalloc(&P->solve_ws.base, need));
-    P->solve_ws.bytes = need;
+    if (hipMalloc(&P->solve_ws.base, more) == hipSuccess) {
+      P->solve_ws.bytes = more;
+    } else {
+      (void)hipGetLastError();
+      P->solve_ws.base = nullptr;
+      PSOAM_HIP(hipMalloc(&P->solve_ws.base, need));
+      P->solve_ws.bytes = need;
+    }
   }
   size_t np = std::max(band_partials(P->inner ? P->inner : P, 1), (size_t)2 * reduce_blocks((int64_t)sv));
   if (P->inner) np = std::max({np, sep_blocks(P), reduce_blocks((int64_t)P->y_elems())});
@@ -89,9 +98,10 @@ int ensure_solve_ws(psoam_plan* P, SolveBufs& B) {
   auto align = [](char* p) { return (float*)(((uintptr_t)p + 255) & ~(uintptr_t)255); };
   char* p = (char*)P->solve_ws.base;
   float** slots[] = {&B.cprev, &B.cnext, &B.xi, &B.g, &B.zb, &B.u[0], &B.u[1], &B.u[2],
-                     &B.u[3], &B.w};
-  const size_t lens[] = {sv, sv, sv, sv, sv, 3 * sv, 3 * sv, 3 * sv, 3 * sv, sv};
-  for (int i = 0; i < 10; ++i) {
+                     &B.w, &B.u[3]};
+  const size_t lens[] = {sv, sv, sv, sv, sv, 3 * sv, 3 * sv, 3 * sv, sv, 3 * sv};
+  B.u[3] = nullptr;
+  for (int i = 0; i < (P->solve_ws.bytes < more ? 9 : 10); ++i) {
     float* a = align(p);
     *slots[i] = a;
     p = (char*)(a + lens[i]);

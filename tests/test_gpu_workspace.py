@@ -1,10 +1,11 @@
 """Workspaces of the TV prox: one that holds three dual buffers and not four takes
-single steps inside its bounds, a smaller one is refused."""
+single steps inside its bounds, a smaller one is refused; and a solve whose
+scratch does not fit with the fourth buffer runs without it."""
 import numpy as np
 import pytest
 
 import synth
-from gpu_common import say, torch_cuda
+from gpu_common import leave_free, say, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +35,25 @@ def test_smaller_workspace_stays_in_bounds(shape):
     with pytest.raises(pk.PsoamError):
         p.prox_tv(z, 0.1, 7, ws=torch.empty(9 * n - 1, device="cuda"))
     p.close()
+
+
+def test_solve_without_room_for_the_fourth_buffer():
+    """400 x 400 x 400 voxels, 2 species: scratch of 9.2 GB with the fourth dual
+    buffer and of 7.7 GB without, on a card with 8.4 GB left."""
+    torch = torch_cuda()
+    shape, o = (400, 400, 400, 2), dict(lambda_tv=0.05, k1=2, k2=5, alpha1=0.3)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    p = _plan(*shape)
+    y = torch.randn(p.y_shape, device="cuda", generator=g)
+    want, _ = p.solve(y, **o)
+    p.close()
+    p, c = _plan(*shape), torch.zeros(p.c_shape, device="cuda")
+    rest = leave_free(torch, int(8.4e9))
+    if rest is None:
+        pytest.skip("the card is in use")
+    say(f"[workspace] {torch.cuda.mem_get_info()[0] / 1e9:.2f} GB left")
+    p.solve(y, c=c, **o)
+    del rest
+    assert torch.equal(c, want)
+    p.close()
+    torch.cuda.empty_cache()
