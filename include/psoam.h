@@ -86,7 +86,7 @@ enum {
  * 64 with 32 and 256); a plan for which they exceed a third of the free
  * memory, or cannot be allocated, keeps the direct form.  The environment
  * variable PSOAM_SPECTRAL=0 or 1 at plan creation forces the direct or (where
- * it can run: at most 256 depths) the spectral form. */
+ * it can run: 2 to 256 depths, at least 2 samples) the spectral form. */
 typedef enum {
   PSOAM_FP32 = 0,
   PSOAM_BF16 = 1,

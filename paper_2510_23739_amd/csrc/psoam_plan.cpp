@@ -815,7 +815,8 @@ static int create_plan_impl(const psoam_geom* gp, const psoam_species* sp, const
   }
   tv_march_plan(P);
   // PSOAM_TV_TILE=i takes tile shape i of the TV dual step, one step a launch
-  // (tests run each); PSOAM_TV_MARCH=1 to 4 bounds the steps of a launch
+  // (tests run each); PSOAM_TV_MARCH=1 to 4 sets the steps of a launch (the last
+  // ones may be one more or less)
   if (const char* e = std::getenv("PSOAM_TV_MARCH"))
     if (const int k = std::atoi(e); k >= 1 && k <= kTvMaxSteps && (k < 2 || P->tv_shape[k].p)) P->tv_march = k;
   if (const char* e = std::getenv("PSOAM_TV_TILE")) {

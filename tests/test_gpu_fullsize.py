@@ -299,13 +299,13 @@ def test_batched_family_instance_sampled(inst):
 # the direct form of the band operator at size, which a plan takes where memory
 # is short for the spectral form
 # ---------------------------------------------------------------------------
-@pytest.mark.parametrize("prec", ["bf16", "bf16_split", "fp32"])
+@pytest.mark.parametrize("prec", ["bf16_split"])
 def test_c3_direct_form_sampled(c3, prec, monkeypatch):
     monkeypatch.setenv("PSOAM_SPECTRAL", "0")
     test_c3_apply_A_and_AT_sampled(c3, prec)
 
 
-@pytest.mark.parametrize("prec", ["bf16", "fp16", "fp32"])
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
 def test_c5_direct_form_sampled(c5, prec, monkeypatch):
     monkeypatch.setenv("PSOAM_SPECTRAL", "0")
     test_c5_apply_A_sampled(c5, prec)
