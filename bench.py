@@ -313,7 +313,7 @@ def factorised_run(torch, pk, cfg, phi, sp, c_true, p_t, lam_tv, lam_l1, prec, s
     return out, sample
 
 
-def profiled_traffic(name):
+def profiled_traffic(name, sources=("psoam_kernels.hip", "psoam_plan.cpp", "psoam_internal.h")):
     """HBM bytes per launch of the dominant kernel from the committed counter
     summary profiles/<name>, valid only while the kernel and plan sources hash
     to what was profiled."""
@@ -327,7 +327,7 @@ def profiled_traffic(name):
             k, v = line[2:].split(":", 1)
             want[k.strip()] = v.strip().strip("`")
     h = hashlib.sha1()
-    for f in ("psoam_kernels.hip", "psoam_plan.cpp", "psoam_internal.h"):
+    for f in sources:
         h.update(open(os.path.join(ROOT, "paper_2510_23739_amd", "csrc", f), "rb").read())
     if want.get("source_sha1") != h.hexdigest():
         return None, "kernel sources changed since the counters were taken"
@@ -727,9 +727,14 @@ def main(argv=None):
     achieved = flops / (t_dom * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.prec]
     kname = {"H": "band16_lds (H, y = H b)", "HT": "band16_lds_adj (S^T H^T)"}[dom]
-    traffic, traffic_src = profiled_traffic(f"{'band16_lds_adj' if dom == 'HT' else 'band16_lds_H'}"
-                                            f"_{cfg.name}_{args.prec}_hbm.md")
     info = res["info"]
+    if info["spectral"]:
+        traffic, traffic_src = profiled_traffic(
+            f"spectral_{dom}_{cfg.name}_{args.prec}_hbm.md",
+            ("psoam_spectral.hip", "psoam_fft.h", "psoam_internal.h"))
+    else:
+        traffic, traffic_src = profiled_traffic(f"{'band16_lds_adj' if dom == 'HT' else 'band16_lds_H'}"
+                                                f"_{cfg.name}_{args.prec}_hbm.md")
     # a spectral plan does not run the band tiles but transforms and one product
     # per frequency, which HBM bounds; the rate is then that of the bytes H (H^T)
     # cannot do without: the operand of one side in float32 and the result of the
@@ -745,7 +750,7 @@ def main(argv=None):
         rate = nbytes / (t_dom * 1e-3) / 1e9
         name = "y = H b" if dom == "H" else "S^T H^T r"
         roof = {"bound": "hbm", "achieved": rate, "peak": PEAK_HBM_GBPS, "unit": "GB/s",
-                "frac": rate / PEAK_HBM_GBPS, "traffic": None,
+                "frac": rate / PEAK_HBM_GBPS, "traffic": traffic,
                 "kernel": f"{name}, spectral form (products per lateral frequency and transforms, "
                           f"float32), {args.prec}: {nbytes / 1e9:.2f} GB of operand and result per "
                           f"launch; {flops / 1e9:.1f} GFLOP as a band contraction"}

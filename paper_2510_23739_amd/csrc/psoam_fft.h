@@ -229,10 +229,12 @@ __device__ __forceinline__ Lds carve(unsigned char* raw, const FftDim& D) {
 // plus a 32-bit offset that a butterfly computes once.  That and the cheaper
 // marks took a third of the vector instructions out, and tiles that share lines
 // on one XCD a third of the reads; us before and after at 320 x 320 x 128 (256
-// samples, 40 pulses): residual 3660 -> 3150, y -> spectrum 2440 -> 2115,
-// spectrum -> y 2500 -> 1990, S c 1500 -> 1205; at 128 x 128 x 64 (160 samples,
-// 32 pulses) 330 -> 340, 196 -> 178, 214 -> 194 and 104 -> 73.  The larger size
-// is at 4.2 to 4.5 TB/s, a copy's 4.9.
+// samples, 40 pulses; two pulses an image then): residual 3660 -> 3150, y ->
+// spectrum 2440 -> 2115, spectrum -> y 2500 -> 1990, S c 1500 -> 1205; at 128 x
+// 128 x 64 (160 samples, 32 pulses) 330 -> 340, 196 -> 178, 214 -> 194 and 104 ->
+// 73.  With a pulse's own pairs: residual 3350 and S c 1325 at the larger size,
+// 298, 150, 196 and 82 at the smaller, at 4.1 and 4.1, 5.6, 3.8 and 2.2 TB/s
+// (a copy's 4.9; what the cache behind L2 holds comes faster).
 __device__ __forceinline__ int mul24(int a, int b) { return (int)__umul24((unsigned)a, (unsigned)b); }
 __device__ __forceinline__ float inv_of(int m) { return __builtin_amdgcn_rcpf((float)m); }
 __device__ __forceinline__ int div_by(int b, float inv) { return (int)(((float)b + 0.5f) * inv); }

@@ -233,10 +233,10 @@ struct Geo {
 
 // ------------------------------------------------------------ x transforms
 // Block: 16 columns (pairs of depths or samples 2 c0 .. 2 c0 + 31) of row iy of
-// pulse (or volume) k.  Neighbouring tiles share lines of the grid's side, so
-// they go to one XCD at about the same time: blocks are dealt to the 8 XCDs
-// round-robin, so of 8 kTilesNear successive ones kTilesNear neighbours are 8
-// apart.
+// pulse (or volume) k.  Where rows of the grid are not whole lines, neighbouring
+// tiles share some, so they go to one XCD at about the same time: blocks are
+// dealt to the 8 XCDs round-robin, so of 8 kTilesNear successive ones kTilesNear
+// neighbours are 8 apart.
 struct RowAt {
   int k, iy, c0;
   int b;  // its number in that order
@@ -264,7 +264,9 @@ __device__ __forceinline__ RowAt row_at(int ny, int h) {
 // 1237, 1319, 1470 and 1433 at 320 x 320 x 128 with 40, 87, 83, 90 and 90 at 128
 // x 128 x 64 with 32.
 constexpr int kPulsesNear = 2;
-__host__ __device__ constexpr int pulses_near(int nk) { return (nk + kPulsesNear - 1) / kPulsesNear * kPulsesNear; }
+__host__ __device__ constexpr int pulses_near(int nk) {
+  return (nk + kPulsesNear - 1) / kPulsesNear * kPulsesNear;
+}
 __device__ __forceinline__ RowAt row_at_pulses(int ny, int h) {
   int b = near_order(kPulsesNear);
   RowAt a;
@@ -328,8 +330,8 @@ enum Src { kSrcDepth = 0, kSrcVoxel = 1, kSrcDiag = 2 };
 template <int RND, int SRC>
 __global__ __launch_bounds__(kFftThreads, 4) void spec_x_switch(
     const float* __restrict__ c, const float* __restrict__ phi, const float* phig,
-    const float* __restrict__ stab_t, const float* __restrict__ f16, SwitchParams sw, float2* __restrict__ out, Geo G, FftDim D,
-    Marks M, const int* __restrict__ gate) {
+    const float* __restrict__ stab_t, const float* __restrict__ f16, SwitchParams sw,
+    float2* __restrict__ out, Geo G, FftDim D, Marks M, const int* __restrict__ gate) {
   if (gate && *gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const fft::Lds L = fft::carve(raw, D);
@@ -833,8 +835,8 @@ struct GemmArgs {
 // depths sits in registers, the table's 16 x 16 blocks stream past it (the
 // block's waves share them through the caches).
 template <int ZC>
-__global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_fwd(GemmArgs A,
-                                                                          const unsigned* __restrict__ mask) {
+__global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_fwd(
+    GemmArgs A, const unsigned* __restrict__ mask) {
   if (A.gate && *A.gate) return;  // a device stop test has ended the solve
   const int f = (int)blockIdx.x;
   const Freq F = freq_at(f, A.nyp, A.nxp);
@@ -892,8 +894,8 @@ __global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_
 // G = conj(T)^T R, the accumulators of all depths in registers; ST: S^T over
 // the pulses in LDS, species written instead of pulses.
 template <int ZC, bool ST>
-__global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_adj(GemmArgs A,
-                                                                                        const unsigned* __restrict__ mask) {
+__global__ __launch_bounds__(512, ZC <= 4 ? 8 : ZC <= 8 ? 7 : 4) void spec_gemm_adj(
+    GemmArgs A, const unsigned* __restrict__ mask) {
   if (A.gate && *A.gate) return;  // a device stop test has ended the solve
   extern __shared__ __attribute__((aligned(16))) unsigned char raw[];
   const int f = (int)blockIdx.x;
@@ -1387,8 +1389,8 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
               phi_mode, G, X, MR, gate_now()));
   if (mix) {
     const size_t vol = P->v_elems();
-    SPEC_HIP(go(spec_st, (vol + 255) / 256, 256, 0, s, (const float*)Q.d_y, out, P->d_phi, rates(P), P->sw, vol,
-                gate_now()));
+    SPEC_HIP(go(spec_st, (vol + 255) / 256, 256, 0, s, (const float*)Q.d_y, out, P->d_phi,
+                rates(P), P->sw, vol, gate_now()));
   }
   return hipSuccess;
 }
@@ -1396,8 +1398,8 @@ hipError_t spec_band(const psoam_plan* P, int mode, float* out, const float* pme
 void spec_free(psoam_plan* P) {
   if (!P->spec) return;
   SpecPlan& Q = *P->spec;
-  for (void* b : {Q.d_x, Q.d_y, Q.d_r, Q.d_g, (void*)Q.d_tf, (void*)Q.d_ta, (void*)Q.d_mask, (void*)Q.d_rate, Q.d_twx,
-                  Q.d_twy, (void*)Q.d_marks})
+  for (void* b : {Q.d_x, Q.d_y, Q.d_r, Q.d_g, (void*)Q.d_tf, (void*)Q.d_ta, (void*)Q.d_mask,
+                  (void*)Q.d_rate, Q.d_twx, Q.d_twy, (void*)Q.d_marks})
     if (b) (void)hipFree(b);
   delete P->spec;
   P->spec = nullptr;
@@ -1439,7 +1441,8 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
   const size_t xb = (size_t)g.n_pulses * img * lz * 4;
   // per-voxel fluence: y's spectrum also holds the pulse volumes S^T reads,
   // which are the larger where the depths outnumber the samples
-  const size_t yb = std::max((size_t)g.n_pulses * img * lt * 4, (size_t)g.n_pulses * P->v_elems() * sizeof(float));
+  const size_t yb =
+      std::max((size_t)g.n_pulses * img * lt * 4, (size_t)g.n_pulses * P->v_elems() * sizeof(float));
   const size_t rb = (size_t)g.n_pulses * g.ny * X.n * lt * 4;
   const size_t gb = (size_t)(st ? P->sw.ns : g.n_pulses) * img * lz * 4;
   const size_t tb = (nf * nblk + 2) * 512 * sizeof(float);
@@ -1454,7 +1457,8 @@ bool spec_build(psoam_plan* P, const int32_t* t0, const float* taps_f, const flo
       std::max(X.n, Y.n) >= (1 << 20))
     return false;
   // launch grids are 32-bit counts of blocks
-  if (nf >= (1u << 31) || (size_t)g.n_pulses * ((size_t)X.n * (std::max(lz, lt) / 2) / 16 + 1) >= (1u << 31)) return false;
+  const size_t tiles_y = (size_t)X.n * (std::max(lz, lt) / 2) / 16 + 1;
+  if (nf >= (1u << 31) || g.n_pulses * tiles_y >= (1u << 31)) return false;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return false;
   const size_t need = xb + yb + rb + gb + 2 * tb + pb;
